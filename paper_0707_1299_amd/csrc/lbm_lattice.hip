@@ -1,6 +1,8 @@
 // Lattice entry points: storage dispatch of the step / moment / diagnostic
 // kernels (instantiated in lbm_lattice_<storage>.hip from lbm_lattice_impl.h),
 // the equilibrium initialisation and the tile shapes they support.
+#include <algorithm>
+
 #include "lbm_device.h"
 #include "lbm_internal.h"
 
@@ -21,48 +23,51 @@ bool launch_lattice_mom32(const Geom& G, int mode, int variant, const void* src,
 
 // Equilibrium of Eq. eqf at (rho, u) written so that the next pull sees it at
 // every node: the copy held at node y for population i is the equilibrium of
-// node y + c_i.
+// node y + c_i.  Each thread reads its node's field once and writes population i at
+// the node x - c_i (a gather of the four values from 19 neighbours per node took 47 us at 128 x 96 x 80
+// against 22 us).  A wave is on one row, so the row indices and their divisions are scalar.
+constexpr int EQ_ROWS = BLOCK / 64;
+
 template <int ST>
 __global__ __launch_bounds__(BLOCK) void k_equilibrium(const Geom G, typename StoreT<ST>::S* __restrict__ dst,
                                                        const BoxDev* __restrict__ boxes,
                                                        const double* __restrict__ rho, const double* __restrict__ u)
 {
     using S = typename StoreT<ST>::S;
-    const long long gid = (long long)blockIdx.x * BLOCK + threadIdx.x;
-    if (gid >= G.N * G.nboxes) return;
-    const int box = int(gid / G.N);
-    const long long n = gid % G.N;
-    const int x = int(n % G.nx), y = int((n / G.nx) % G.ny), z = int(n / ((long long)G.nx * G.ny));
-    const long long row = n / G.nx;
-    const double s = ST == ST_FP16 ? ldexp(1.0, boxes[box].e_data) : 1.0;
-    S* db = dst + (long long)box * G.sbox;
-    if constexpr (ST == ST_MOM32) {
-        // the equilibrium of this node taken as its post-collision state
+    const unsigned rows = unsigned(G.ny) * unsigned(G.nz);
+    const int x = int(blockIdx.y) * 64 + int(threadIdx.x & 63);
+    if (x >= G.nx) return;
+    long long r0 = (long long)blockIdx.x * EQ_ROWS + __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    for (; r0 < (long long)rows * G.nboxes; r0 += (long long)gridDim.x * EQ_ROWS) {
+        const int box = int(r0 / rows);
+        const unsigned row = unsigned(r0 - (long long)box * rows);
+        const int z = int(row / unsigned(G.ny)), y = int(row - unsigned(z) * unsigned(G.ny));
+        const long long n = (long long)row * G.nx + x;
+        const double s = ST == ST_FP16 ? ldexp(1.0, boxes[box].e_data) : 1.0;
+        S* db = dst + (long long)box * G.sbox;
         const double r = rho[(long long)box * G.N + n];
         const double v[3] = {u[((long long)box * 3 + 0) * G.N + n], u[((long long)box * 3 + 1) * G.N + n],
                              u[((long long)box * 3 + 2) * G.N + n]};
         const double uu = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
-        const double piece[MP_N] = {(r - G.rho0) - 1.5 * r * uu, 3 * r * v[0], 3 * r * v[1], 3 * r * v[2],
-                                    4.5 * r * v[0] * v[0], 4.5 * r * v[1] * v[1], 4.5 * r * v[2] * v[2],
-                                    9 * r * v[0] * v[1], 9 * r * v[0] * v[2], 9 * r * v[1] * v[2]};
-        for (int k = 0; k < MP_N; ++k) db[pop_index(G.rb, G.kp, k, row, x)] = S(piece[k]);
-        return;
-    }
+        if constexpr (ST == ST_MOM32) {
+            // the equilibrium of this node taken as its post-collision state
+            const double piece[MP_N] = {(r - G.rho0) - 1.5 * r * uu, 3 * r * v[0], 3 * r * v[1], 3 * r * v[2],
+                                        4.5 * r * v[0] * v[0], 4.5 * r * v[1] * v[1], 4.5 * r * v[2] * v[2],
+                                        9 * r * v[0] * v[1], 9 * r * v[0] * v[2], 9 * r * v[1] * v[2]};
+            for (int k = 0; k < MP_N; ++k) db[pop_index(G.rb, G.kp, k, row, x)] = S(piece[k]);
+            continue;
+        }
 #pragma unroll
-    for (int i = 0; i < NQ; ++i) {
-        int xs = x + cvel(i, 0), ys = y + cvel(i, 1), zs = z + cvel(i, 2);
-        xs = xs < 0 ? xs + G.nx : (xs >= G.nx ? xs - G.nx : xs);
-        ys = ys < 0 ? ys + G.ny : (ys >= G.ny ? ys - G.ny : ys);
-        zs = zs < 0 ? zs + G.nz : (zs >= G.nz ? zs - G.nz : zs);
-        const long long m = ((long long)zs * G.ny + ys) * G.nx + xs;
-        const double r = rho[(long long)box * G.N + m];
-        const double vx = u[((long long)box * 3 + 0) * G.N + m];
-        const double vy = u[((long long)box * 3 + 1) * G.N + m];
-        const double vz = u[((long long)box * 3 + 2) * G.N + m];
-        const double cu = cvel(i, 0) * vx + cvel(i, 1) * vy + cvel(i, 2) * vz;
-        const double uu = vx * vx + vy * vy + vz * vz;
-        const double bracket = (r - G.rho0) + 3.0 * r * cu + 4.5 * r * (cu * cu - uu / 3.0);
-        db[pop_index(G.rb, G.kp, i, row, x)] = ST == ST_FP16 ? S(bracket * s) : S(wgt(i) * bracket);
+        for (int i = 0; i < NQ; ++i) {
+            int xs = x - cvel(i, 0), ys = y - cvel(i, 1), zs = z - cvel(i, 2);
+            xs = xs < 0 ? xs + G.nx : (xs >= G.nx ? xs - G.nx : xs);
+            ys = ys < 0 ? ys + G.ny : (ys >= G.ny ? ys - G.ny : ys);
+            zs = zs < 0 ? zs + G.nz : (zs >= G.nz ? zs - G.nz : zs);
+            const double cu = cvel(i, 0) * v[0] + cvel(i, 1) * v[1] + cvel(i, 2) * v[2];
+            const double bracket = (r - G.rho0) + 3.0 * r * cu + 4.5 * r * (cu * cu - uu / 3.0);
+            db[pop_index(G.rb, G.kp, i, (long long)zs * G.ny + ys, xs)] =
+                ST == ST_FP16 ? S(bracket * s) : S(wgt(i) * bracket);
+        }
     }
 }
 
@@ -100,20 +105,20 @@ bool launch_lattice(int storage, const Geom& G, int mode, int variant, const voi
 void launch_equilibrium(int storage, const Geom& G, void* dst, const BoxDev* boxes, const double* rho,
                         const double* u, hipStream_t s)
 {
-    const long long total = G.N * G.nboxes;
-    const unsigned nb = (unsigned)((total + BLOCK - 1) / BLOCK);
+    const long long rows = (long long)G.ny * G.nz * G.nboxes;
+    const dim3 nb((unsigned)std::min<long long>((rows + EQ_ROWS - 1) / EQ_ROWS, 1 << 22), (unsigned)((G.nx + 63) / 64));
     switch (storage) {
     case ST_FP64:
-        hipLaunchKernelGGL(k_equilibrium<ST_FP64>, dim3(nb), dim3(BLOCK), 0, s, G, (double*)dst, boxes, rho, u);
+        hipLaunchKernelGGL(k_equilibrium<ST_FP64>, nb, dim3(BLOCK), 0, s, G, (double*)dst, boxes, rho, u);
         break;
     case ST_FP32:
-        hipLaunchKernelGGL(k_equilibrium<ST_FP32>, dim3(nb), dim3(BLOCK), 0, s, G, (float*)dst, boxes, rho, u);
+        hipLaunchKernelGGL(k_equilibrium<ST_FP32>, nb, dim3(BLOCK), 0, s, G, (float*)dst, boxes, rho, u);
         break;
     case ST_FP16:
-        hipLaunchKernelGGL(k_equilibrium<ST_FP16>, dim3(nb), dim3(BLOCK), 0, s, G, (_Float16*)dst, boxes, rho, u);
+        hipLaunchKernelGGL(k_equilibrium<ST_FP16>, nb, dim3(BLOCK), 0, s, G, (_Float16*)dst, boxes, rho, u);
         break;
     case ST_MOM32:
-        hipLaunchKernelGGL(k_equilibrium<ST_MOM32>, dim3(nb), dim3(BLOCK), 0, s, G, (float*)dst, boxes, rho, u);
+        hipLaunchKernelGGL(k_equilibrium<ST_MOM32>, nb, dim3(BLOCK), 0, s, G, (float*)dst, boxes, rho, u);
         break;
     }
 }
