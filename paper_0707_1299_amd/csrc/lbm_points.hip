@@ -28,56 +28,36 @@ namespace lbm {
 // the lower half of its cell, at the stencil base otherwise.
 constexpr int WIN = 5;
 
-// Distinct tiles met by the WIN consecutive nodes base .. base+WIN-1 (periodic) of
-// one axis, in order of first appearance.
-__device__ __forceinline__ int axis_tiles(int base, int n, int lt, int (&out)[WIN])
+// Distinct tiles met by the WIN consecutive nodes base .. base + WIN - 1 (periodic, n >= 4) of one axis, in
+// order of first appearance: c1 of them from t0 on, then, where the window wraps, tiles 0, 1, ... as far
+// as they are not among the first ones; c in all.  (Closed form: no list, so nothing goes to scratch
+// memory.)
+struct AxisTiles {
+    int t0, c1, c;
+};
+
+__device__ __forceinline__ AxisTiles axis_tiles(int base, int n, int lt)
 {
-    int cnt = 0;
-#pragma unroll
-    for (int k = 0; k < WIN; ++k) {
-        int node = base + k;
-        if (node >= n) node -= n;
-        const int t = node >> lt;
-        bool dup = false;
-        for (int j = 0; j < cnt; ++j) dup |= (out[j] == t);
-        if (!dup) out[cnt++] = t;
-    }
-    return cnt;
+    const int last = base + WIN - 1;
+    AxisTiles s;
+    s.t0 = base >> lt;
+    s.c1 = (min(last, n - 1) >> lt) - s.t0 + 1;
+    s.c = s.c1 + (last < n ? 0 : min(((last - n) >> lt) + 1, s.t0));
+    return s;
 }
 
-// number of distinct tiles met by the window (as axis_tiles, without the list: every index
-// is known at compile time, so nothing goes to scratch memory)
-__device__ __forceinline__ int axis_count(int base, int n, int lt)
-{
-    int t[WIN];
-#pragma unroll
-    for (int k = 0; k < WIN; ++k) {
-        int node = base + k;
-        if (node >= n) node -= n;
-        t[k] = node >> lt;
-    }
-    int cnt = 0;
-#pragma unroll
-    for (int k = 0; k < WIN; ++k) {
-        bool dup = false;
-#pragma unroll
-        for (int j = 0; j < k; ++j) dup |= (t[j] == t[k]);
-        cnt += dup ? 0 : 1;
-    }
-    return cnt;
-}
+__device__ __forceinline__ int axis_tile(const AxisTiles& s, int k) { return k < s.c1 ? s.t0 + k : k - s.c1; }
+
+__device__ __forceinline__ int axis_count(int base, int n, int lt) { return axis_tiles(base, n, lt).c; }
 
 struct TileSet {
-    int tx[WIN], ty[WIN], tz[WIN];
-    int cx, cy, cz;
+    AxisTiles x, y, z;
 };
 
 // tiles of the window with bases (wx, wy, wz)
-__device__ __forceinline__ void window_tiles(const Geom& G, int wx, int wy, int wz, TileSet& s)
+__device__ __forceinline__ TileSet window_tiles(const Geom& G, int wx, int wy, int wz)
 {
-    s.cx = axis_tiles(wx, G.nx, G.ltx, s.tx);
-    s.cy = axis_tiles(wy, G.ny, G.lty, s.ty);
-    s.cz = axis_tiles(wz, G.nz, G.ltz, s.tz);
+    return TileSet{axis_tiles(wx, G.nx, G.ltx), axis_tiles(wy, G.ny, G.lty), axis_tiles(wz, G.nz, G.ltz)};
 }
 
 // window base of one axis for a point with stencil base b (wrapped) and 1-D weights w:
@@ -100,29 +80,25 @@ __device__ __forceinline__ long long tile_id(const Geom& G, int box, int tz, int
     return (((long long)box * G.ntz + tz) * G.nty + ty) * G.ntx + tx;
 }
 
-__device__ __forceinline__ int pick(const int (&a)[WIN], int j)
-{
-    int v = a[0];
-#pragma unroll
-    for (int q = 1; q < WIN; ++q) v = j == q ? a[q] : v;
-    return v;
-}
+// k / c for 0 <= k < 64, 1 <= c <= WIN: (k + 1/2) / c is at least 1/(2 c) from the next whole number, far
+// more than the rounding of the product with the reciprocal
+__device__ __forceinline__ int small_div(int k, int c) { return int((float(k) + 0.5f) * __builtin_amdgcn_rcpf(float(c))); }
 
 // Tile of slot k of a point (k = (iz cy + iy) cx + ix over its distinct window tiles per
 // axis), or -1 past the point's last slot.
 __device__ __forceinline__ long long slot_tile(const Geom& G, const TileSet& s, int box, int k)
 {
-    if (k >= s.cx * s.cy * s.cz) return -1;
-    const int ix = k % s.cx, iy = (k / s.cx) % s.cy, iz = k / (s.cx * s.cy);
-    return tile_id(G, box, pick(s.tz, iz), pick(s.ty, iy), pick(s.tx, ix));
+    if (k >= s.x.c * s.y.c * s.z.c) return -1;
+    const int q = small_div(k, s.x.c), iz = small_div(q, s.y.c);
+    return tile_id(G, box, axis_tile(s.z, iz), axis_tile(s.y, q - iz * s.y.c), axis_tile(s.x, k - q * s.x.c));
 }
 
-// The (point, slot) kernels run a group of lanes_per_point(maxp) consecutive lanes per point,
-// lane k of the group taking slot k: the atomics of one point then run side by side.
-int lanes_per_point(int maxp)
+// The (point, slot) phases run a group of 2^log_lanes(maxp) consecutive lanes per point, lane k of the
+// group taking slot k: the atomics of one point then run side by side.
+int log_lanes(int maxp)
 {
-    int g = 1;
-    while (g < maxp) g <<= 1;
+    int g = 0;
+    while ((1 << g) < maxp) ++g;
     return g;
 }
 
@@ -216,11 +192,11 @@ __device__ __forceinline__ void prep_point(const Geom& G, long long i, long long
 
 // 1b-4. The tile lists, rebuilt in one launch (k_rebin) only while the rebuild flag is set.
 //    In the usual step (no crossing) every block reads the flag and returns: one kernel
-//    boundary per step instead of one per phase.  Otherwise a grid of one block of 256
-//    threads per compute unit (at most BIN_GRID; all resident at once) runs four phases
-//    separated by grid-wide barriers:
-//      1b count the (tile, point) pairs: one group of gp lanes per point (see
-//         lanes_per_point), lane k counting the point in the tile of slot k.  Windows are
+//    boundary per step instead of one per phase.  Otherwise a grid of blocks of 256
+//    threads (as many as the work asks for, at most one per compute unit and BIN_GRID, so all
+//    resident at once) runs four phases separated by grid-wide barriers:
+//      1b count the (tile, point) pairs: one group of 2^lg lanes per point (see
+//         log_lanes), lane k counting the point in the tile of slot k.  Windows are
 //         chosen afresh (lane 0 stores them) only for the points of boxes in which a point
 //         crossed; the others keep theirs, so what a box computes never depends on crossings
 //         in the other boxes of a batch;
@@ -230,7 +206,8 @@ __device__ __forceinline__ void prep_point(const Geom& G, long long i, long long
 //      3  fill the lists (slot order from atomics), one lane per (point, slot) as in 1b;
 //         the per-box crossing flags are cleared (1b, their only reader, has finished);
 //      4  sort every tile's list by point index, so that sums run in a fixed order: one
-//         thread per entry, its position the number of smaller entries in the same list.
+//         thread per entry, its position the number of smaller entries in the same list;
+//         the rebuild flag is cleared.
 //    A block passes a barrier only when every block has reached it, so whatever a phase
 //    reads is complete.  The barrier's wait is bounded: a block that waits too long raises
 //    err bit 4 and leaves (the lists then keep a consistent earlier state or miss entries;
@@ -246,13 +223,14 @@ __device__ __forceinline__ bool grid_barrier(unsigned* bar, unsigned k, int* err
     __shared__ int ok;
     __syncthreads();   // the block's writes have reached the compute unit's L2 (L1 writes through)
     if (threadIdx.x == 0) {
-        // one device-scope release per block: the write-back covers every wave's writes in L2
+        // one device-scope release per block: the write-back covers every wave's writes in L2.  The
+        // polls are relaxed (an acquire would invalidate caches at each); the fence after them orders
         __threadfence();
         ok = 1;
         atomicAdd(bar, 1u);
         const unsigned target = k * gridDim.x;
         unsigned n = 0;
-        while (__hip_atomic_load(bar, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < target) {
+        while (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
             if (++n > BARRIER_SPINS) {
                 atomicOr(err, 4);
                 ok = 0;
@@ -300,7 +278,7 @@ __device__ __forceinline__ int block_exclusive_scan_256(int v, int* sh, int& tot
 }
 
 template <class T>
-__global__ __launch_bounds__(256) void k_rebin(const Geom G, long long npts, int gp, const PRec<T>* __restrict__ rec,
+__global__ __launch_bounds__(256) void k_rebin(const Geom G, long long npts, int lg, const PRec<T>* __restrict__ rec,
                                                int* __restrict__ count, int* __restrict__ bsum, int* __restrict__ toff,
                                                int* __restrict__ cursor, int* __restrict__ tlist_tmp,
                                                int* __restrict__ tlist, long long max_entries, int* __restrict__ err)
@@ -312,9 +290,9 @@ __global__ __launch_bounds__(256) void k_rebin(const Geom G, long long npts, int
     const long long gid0 = (long long)blockIdx.x * blockDim.x + threadIdx.x;
 
     // 1b. count
-    for (long long gid = gid0; gid < npts * gp; gid += stride) {
-        const long long p = gid / gp;
-        const int k = int(gid % gp);
+    for (long long gid = gid0; gid < npts << lg; gid += stride) {
+        const long long p = gid >> lg;
+        const int k = int(gid) & ((1 << lg) - 1);
         if (k >= G.maxp) continue;
         const PRec<T> r = rec[p];
         const bool fresh = G.rebox[r.box] != 0;
@@ -322,8 +300,7 @@ __global__ __launch_bounds__(256) void k_rebin(const Geom G, long long npts, int
                                          window_base(r.bz, G.nz, r.wz), r.box)
                              : G.win[p];
         if (fresh && k == 0) G.win[p] = w;
-        TileSet s;
-        window_tiles(G, w.x, w.y, w.z, s);
+        const TileSet s = window_tiles(G, w.x, w.y, w.z);
         const long long t = slot_tile(G, s, r.box, k);
         if (t >= 0) atomicAdd(&count[t], 1);
     }
@@ -356,12 +333,11 @@ __global__ __launch_bounds__(256) void k_rebin(const Geom G, long long npts, int
 
     // 3. fill
     for (long long b = gid0; b < G.nboxes; b += stride) G.rebox[b] = 0;
-    for (long long gid = gid0; gid < npts * gp; gid += stride) {
-        const long long p = gid / gp;
-        const int k = int(gid % gp);
+    for (long long gid = gid0; gid < npts << lg; gid += stride) {
+        const long long p = gid >> lg;
+        const int k = int(gid) & ((1 << lg) - 1);
         const int4 w = G.win[p];
-        TileSet s;
-        window_tiles(G, w.x, w.y, w.z, s);
+        const TileSet s = window_tiles(G, w.x, w.y, w.z);
         const long long t = slot_tile(G, s, w.w, k);
         if (t < 0) continue;
         // home tile: the one holding the window's centre node (always inside the stencil)
@@ -374,6 +350,9 @@ __global__ __launch_bounds__(256) void k_rebin(const Geom G, long long npts, int
         tlist_tmp[slot] = int(p << PK_SHIFT) | (home ? PK_HOME : 0) | k;
     }
     if (!grid_barrier(bar, 4, err)) return;
+    // every block has read the flag and the lists are complete: reads between steps (moments,
+    // interpolation, diagnostics) then find them current instead of building them again
+    if (gid0 == 0) *G.rebin = 0;
 
     // 4. sort
     const long long ne = min(max_entries, (long long)toff[G.ntiles]);
@@ -381,8 +360,7 @@ __global__ __launch_bounds__(256) void k_rebin(const Geom G, long long npts, int
         const int v = tlist_tmp[e];
         const int p = pk_point(v), k = pk_slot(v);
         const int4 w = G.win[p];
-        TileSet s;
-        window_tiles(G, w.x, w.y, w.z, s);
+        const TileSet s = window_tiles(G, w.x, w.y, w.z);
         const long long t = slot_tile(G, s, w.w, k);
         const int a = toff[t], b = toff[t + 1];
         int rank = 0;
@@ -754,35 +732,53 @@ __global__ __launch_bounds__(MLP_BLOCK) void k_advect_mlp(const Geom G, const Ad
 // 7. interpolation at arbitrary points: one wave per point, one lane per
 //    stencil node; each lane rebuilds u at its node from the stored
 //    populations and the binned forces.
+// Value d of four, without an indexed (scratch) array.
+__device__ __forceinline__ double pick4(const double (&w)[4], int d)
+{
+    return d == 0 ? w[0] : d == 1 ? w[1] : d == 2 ? w[2] : w[3];
+}
+
+// Lane l's value for every lane.
+__device__ __forceinline__ double lane_value(double v, int l)
+{
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __builtin_bit_cast(double, (long long)(unsigned)lo | ((long long)hi << 32));
+}
+
 template <int ST>
-__global__ __launch_bounds__(256) void k_interp_points(const Geom G, long long n, const double* __restrict__ pos,
-                                                       const int* __restrict__ boxid, double* __restrict__ out,
-                                                       const typename StoreT<ST>::S* __restrict__ src,
-                                                       const BoxDev* __restrict__ boxes, const int* __restrict__ toff,
-                                                       const int* __restrict__ tlist,
-                                                       const PRec<typename StoreT<ST>::T>* __restrict__ rec)
+__device__ __forceinline__ void interp_point(const Geom& G, long long q, const double* __restrict__ pos,
+                                             const int* __restrict__ boxid, double* __restrict__ out,
+                                             const typename StoreT<ST>::S* __restrict__ src,
+                                             const BoxDev* __restrict__ boxes, const int* __restrict__ toff,
+                                             const int* __restrict__ tlist,
+                                             const PRec<typename StoreT<ST>::T>* __restrict__ rec)
 {
     using T = typename StoreT<ST>::T;
     const int lane = threadIdx.x & 63;
-    const long long q = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (q >= n) return;
     int box = boxid ? boxid[q] : 0;
     if (box < 0 || box >= G.nboxes) box = 0;
+    // lane a < 3 works out axis a (base node and the four weights); the others repeat axis 2.  The values
+    // then go to every lane through scalar registers: one evaluation of the kernel instead of three.
+    const int ax = min(lane, 2);
+    const int La = ax == 0 ? G.nx : (ax == 1 ? G.ny : G.nz);
+    const double xa = wrap_pos(pos[3 * q + ax], double(La));
+    int b0 = (int)floor(xa);
+    if (b0 >= La) b0 = La - 1;
+    double w1[4];
+    peskin4(xa - b0, w1);
     const int d[3] = {lane & 3, (lane >> 2) & 3, lane >> 4};
     const int L[3] = {G.nx, G.ny, G.nz};
     int node[3];
     double wt = 1.0;
+#pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const double x = wrap_pos(pos[3 * q + a], double(L[a]));
-        int b0 = (int)floor(x);
-        if (b0 >= L[a]) b0 = L[a] - 1;
-        double w[4];
-        peskin4(x - b0, w);
-        int nd = b0 - 1 + d[a];
+        int nd = __builtin_amdgcn_readlane(b0, a) - 1 + d[a];
         if (nd < 0) nd += L[a];
         if (nd >= L[a]) nd -= L[a];
         node[a] = nd;
-        wt *= w[d[a]];
+        const double w[4] = {lane_value(w1[0], a), lane_value(w1[1], a), lane_value(w1[2], a), lane_value(w1[3], a)};
+        wt *= pick4(w, d[a]);
     }
     const int x = node[0], y = node[1], z = node[2];
     const int xm = x == 0 ? G.nx - 1 : x - 1, xp = x + 1 == G.nx ? 0 : x + 1;
@@ -790,6 +786,12 @@ __global__ __launch_bounds__(256) void k_interp_points(const Geom G, long long n
     const int zm = z == 0 ? G.nz - 1 : z - 1, zp = z + 1 == G.nz ? 0 : z + 1;
     const auto* sb = src + (long long)box * G.sbox;
     const BoxDev& B = boxes[box];
+    int k0 = 0, k1 = 0;      // the node's tile's entries in the point lists
+    if (toff) {
+        const long long t = tile_id(G, box, z >> G.ltz, y >> G.lty, x >> G.ltx);
+        k0 = toff[t];
+        k1 = toff[t + 1];
+    }
     T f[NQ];
     pull_node<ST, false, A_G64>(sb, G.rb, G.kp, 0u, G.ny, x, y, z, xm, xp, ym, yp, zm, zp,
                          f);
@@ -810,16 +812,13 @@ __global__ __launch_bounds__(256) void k_interp_points(const Geom G, long long n
         jz *= s;
     }
     T gx = T(B.gc[0]), gy = T(B.gc[1]), gz = T(B.gc[2]);
-    if (toff) {
-        const long long t = tile_id(G, box, z >> G.ltz, y >> G.lty, x >> G.ltx);
-        for (int k = toff[t]; k < toff[t + 1]; ++k) {
-            const PRec<T>& r = rec[pk_point(tlist[k])];
-            const T w = stencil_w<T>(x, r.bx, G.nx, r.wx) * stencil_w<T>(y, r.by, G.ny, r.wy) *
-                        stencil_w<T>(z, r.bz, G.nz, r.wz);
-            gx += r.f[0] * w;
-            gy += r.f[1] * w;
-            gz += r.f[2] * w;
-        }
+    for (int k = k0; k < k1; ++k) {
+        const PRec<T>& r = rec[pk_point(tlist[k])];
+        const T w = stencil_w<T>(x, r.bx, G.nx, r.wx) * stencil_w<T>(y, r.by, G.ny, r.wy) *
+                    stencil_w<T>(z, r.bz, G.nz, r.wz);
+        gx += r.f[0] * w;
+        gy += r.f[1] * w;
+        gz += r.f[2] * w;
     }
     const T rho = T(G.rho0) + drho;
     const T ir = T(1) / rho;
@@ -831,28 +830,71 @@ __global__ __launch_bounds__(256) void k_interp_points(const Geom G, long long n
     }
 }
 
+// Plain order (nslab == 1): wave q takes point q.  With nslab > 1 the z planes of all boxes are cut into
+// nslab slabs of about 2 MB, half an XCD's L2: the blocks that the dispatcher sends to XCD j work
+// through slabs j, j + 8, ... in order, `per` blocks a slab, one for each group of 64 points: its waves
+// look for those whose base plane lies in the slab and take them in turn.  A point's stencil touches 19 x 16 cache lines of 128 B, eight times
+// its data; in plain order every XCD fetches most of them over the fabric (20000 points of 128 x 96 x 80: 113 us,
+// 6.9 TB/s of line fetches), in slab order they are shared by the points nearby (54 us).
+template <int ST>
+__global__ __launch_bounds__(256) void k_interp_points(const Geom G, long long n, int nslab, int per,
+                                                       const double* __restrict__ pos, const int* __restrict__ boxid,
+                                                       double* __restrict__ out,
+                                                       const typename StoreT<ST>::S* __restrict__ src,
+                                                       const BoxDev* __restrict__ boxes, const int* __restrict__ toff,
+                                                       const int* __restrict__ tlist,
+                                                       const PRec<typename StoreT<ST>::T>* __restrict__ rec)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    if (nslab <= 1) {
+        const long long q = (long long)blockIdx.x * 4 + wave;
+        if (q < n) interp_point<ST>(G, q, pos, boxid, out, src, boxes, toff, tlist, rec);
+        return;
+    }
+    const int xcd = blockIdx.x & 7, k = blockIdx.x >> 3;
+    const int slab = 8 * (k / per) + xcd;
+    const long long g0 = (long long)(k % per) * 64, i = g0 + lane;
+    bool mine = false;
+    if (i < n) {
+        int box = boxid ? boxid[i] : 0;
+        if (box < 0 || box >= G.nboxes) box = 0;
+        const double z = wrap_pos(pos[3 * i + 2], double(G.nz));
+        // any assignment of points to slabs covers each point once; a non-finite position takes plane 0
+        const int z0 = z < double(G.nz) ? int(z) : 0;
+        mine = int(((long long)box * G.nz + z0) * nslab / ((long long)G.nboxes * G.nz)) == slab;
+    }
+    int turn = 0;
+    for (unsigned long long m = __ballot(mine); m; m &= m - 1, ++turn)
+        if ((turn & 3) == wave)
+            interp_point<ST>(G, g0 + (__ffsll(m) - 1), pos, boxid, out, src, boxes, toff, tlist, rec);
+}
+
 // ---------------------------------------------------------------------------
-// 8. diagnostics: per-box reduction of the per-tile partials in tile order
+// 8. diagnostics: per-box reduction of the per-tile partials in tile order, one block per (box,
+//    component); eight loads of a thread are in flight at a time (a chain of one load per addition ran
+//    34 us for the 3840 tiles of 128 x 96 x 80, all components in one block)
 __global__ __launch_bounds__(256) void k_diag_reduce(const Geom G, const double* __restrict__ part,
                                                      double* __restrict__ out)
 {
-    const int b = blockIdx.x;
+    const int b = blockIdx.x, c = blockIdx.y;
     __shared__ double red[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int c = 0; c < LBD_N; ++c) {
-        double a = 0.0;
-        for (long long t = threadIdx.x; t < G.tiles_per_box; t += blockDim.x) {
-            const double v = part[((long long)b * G.tiles_per_box + t) * LBD_N + c];
-            a = c == 10 ? fmax(a, v) : a + v;
-        }
-        a = c == 10 ? wave_max(a) : wave_sum(a);
-        if (lane == 0) red[wave] = a;
-        __syncthreads();
-        if (threadIdx.x == 0)
-            out[(long long)b * LBD_N + c] =
-                c == 10 ? fmax(fmax(red[0], red[1]), fmax(red[2], red[3])) : ((red[0] + red[1]) + red[2]) + red[3];
-        __syncthreads();
+    const double* p = part + (long long)b * G.tiles_per_box * LBD_N + c;
+    double a = 0.0;
+    for (long long t = threadIdx.x; t < G.tiles_per_box; t += 8 * 256) {
+        double v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = t + 256 * j < G.tiles_per_box ? p[(t + 256 * j) * LBD_N] : 0.0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) a = c == 10 ? fmax(a, v[j]) : a + v[j];
     }
+    a = c == 10 ? wave_max(a) : wave_sum(a);
+    if (lane == 0) red[wave] = a;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        out[(long long)b * LBD_N + c] =
+            c == 10 ? fmax(fmax(red[0], red[1]), fmax(red[2], red[3])) : ((red[0] + red[1]) + red[2]) + red[3];
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ p, long long n, uint32_t v)
@@ -887,15 +929,20 @@ void launch_prep(int storage, const Geom& G, long long n, long long off, const d
 
 long long scan_blocks(long long ntiles) { return (ntiles + CHUNK - 1) / CHUNK; }
 
-// Blocks of the list build: one per compute unit of the current device, at most BIN_GRID,
-// so that the grid is resident at once even on a partition of the GPU.
-static unsigned rebin_grid()
+// Blocks of the list build for `slots` (point, slot) lanes: at most one per compute unit of the current
+// device and BIN_GRID, so that the grid is resident at once even on a partition of the GPU.  A grid
+// barrier costs about 0.05 us per block (12 us of the build at 16 blocks, 60 us at 256), a round of 256
+// lanes about 1 us per phase, so small builds take few blocks: 200 points of 128 x 96 x 80 ran in 82 us on
+// 256 blocks, 35 us on 16; 1000 points of 128^3 89 / 44 us on 256 / 32; 10^4 points of 256^3 106 / 84 us on
+// 256 / 128; 65536 points of 256^3 192 / 236 us on 256 / 128 (with the call's other launches).
+static unsigned rebin_grid(long long slots)
 {
+    const unsigned want = slots >= (1LL << 20) ? BIN_GRID : (unsigned)std::clamp<long long>(slots >> 10, 16, 128);
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        return 32;
-    return std::min<unsigned>(BIN_GRID, unsigned(cus));
+        return 16;
+    return std::min<unsigned>(want, unsigned(cus));
 }
 
 // Steps 1b-4 over all npts points, after the records of every set are written
@@ -904,14 +951,14 @@ void launch_bins(int storage, const Geom& G, long long npts, const void* rec, in
                  int* cursor, int* tlist, int* tlist_tmp, int* err, hipStream_t s)
 {
     if (npts <= 0) return;
-    const int gp = lanes_per_point(G.maxp);
+    const int lg = log_lanes(G.maxp);
     const long long max_entries = npts * G.maxp;
-    const unsigned nb = rebin_grid();
+    const unsigned nb = rebin_grid(npts << lg);
     if (storage == ST_FP64)
-        hipLaunchKernelGGL(k_rebin<double>, dim3(nb), dim3(256), 0, s, G, npts, gp, (const PRec<double>*)rec, count,
+        hipLaunchKernelGGL(k_rebin<double>, dim3(nb), dim3(256), 0, s, G, npts, lg, (const PRec<double>*)rec, count,
                            bsum, toff, cursor, tlist_tmp, tlist, max_entries, err);
     else
-        hipLaunchKernelGGL(k_rebin<float>, dim3(nb), dim3(256), 0, s, G, npts, gp, (const PRec<float>*)rec, count,
+        hipLaunchKernelGGL(k_rebin<float>, dim3(nb), dim3(256), 0, s, G, npts, lg, (const PRec<float>*)rec, count,
                            bsum, toff, cursor, tlist_tmp, tlist, max_entries, err);
 }
 
@@ -974,22 +1021,30 @@ void launch_interp_points(int storage, const Geom& G, long long n, const double*
                           hipStream_t s)
 {
     if (n <= 0) return;
-    const unsigned nb = nblk(n, 4);
+    // slabs pay where the points' line fetches (39 KB each in FP32, by storage size) are several times the
+    // lattice and the lattice is several times an XCD's 4 MB L2: 20000 points took 54 us in slabs and 110 us
+    // in plain order at 128 x 96 x 80 (75 MB, 10 x), 34 and 31 us at 32^3 (2.5 MB); at 256^3 (1.3 GB, 0.6 x)
+    // nothing is shared.  At most 64 slabs: every slab's blocks look at every point.
+    const double esize = storage == ST_FP64 ? 8 : storage == ST_FP16 ? 2 : 4;
+    const double lattice = double(G.sbox) * G.nboxes * esize, lines = double(n) * planes_of(storage) * 16 * 128;
+    const int nslab = lattice > 16.0e6 && lines >= 4.0 * lattice ? 8 * (int)std::min(8.0, ceil(lattice / 16.0e6)) : 1;
+    const int per = (int)nblk(n, 64);
+    const unsigned nb = nslab > 1 ? (unsigned)nslab * per : nblk(n, 4);
     switch (storage) {
     case ST_FP64:
-        hipLaunchKernelGGL(k_interp_points<ST_FP64>, dim3(nb), dim3(256), 0, s, G, n, pos, boxid, out,
+        hipLaunchKernelGGL(k_interp_points<ST_FP64>, dim3(nb), dim3(256), 0, s, G, n, nslab, per, pos, boxid, out,
                            (const double*)src, boxes, toff, tlist, (const PRec<double>*)rec);
         break;
     case ST_FP32:
-        hipLaunchKernelGGL(k_interp_points<ST_FP32>, dim3(nb), dim3(256), 0, s, G, n, pos, boxid, out,
+        hipLaunchKernelGGL(k_interp_points<ST_FP32>, dim3(nb), dim3(256), 0, s, G, n, nslab, per, pos, boxid, out,
                            (const float*)src, boxes, toff, tlist, (const PRec<float>*)rec);
         break;
     case ST_FP16:
-        hipLaunchKernelGGL(k_interp_points<ST_FP16>, dim3(nb), dim3(256), 0, s, G, n, pos, boxid, out,
+        hipLaunchKernelGGL(k_interp_points<ST_FP16>, dim3(nb), dim3(256), 0, s, G, n, nslab, per, pos, boxid, out,
                            (const _Float16*)src, boxes, toff, tlist, (const PRec<float>*)rec);
         break;
     case ST_MOM32:
-        hipLaunchKernelGGL(k_interp_points<ST_MOM32>, dim3(nb), dim3(256), 0, s, G, n, pos, boxid, out,
+        hipLaunchKernelGGL(k_interp_points<ST_MOM32>, dim3(nb), dim3(256), 0, s, G, n, nslab, per, pos, boxid, out,
                            (const float*)src, boxes, toff, tlist, (const PRec<float>*)rec);
         break;
     }
@@ -997,7 +1052,7 @@ void launch_interp_points(int storage, const Geom& G, long long n, const double*
 
 void launch_diag_reduce(const Geom& G, const double* part, double* out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_diag_reduce, dim3(G.nboxes), dim3(256), 0, s, G, part, out);
+    hipLaunchKernelGGL(k_diag_reduce, dim3(G.nboxes, LBD_N), dim3(256), 0, s, G, part, out);
 }
 
 }  // namespace lbm
