@@ -92,7 +92,9 @@ typedef struct lb_params {
     const double* tau;      /* HOST array [nboxes]: paper's tau (> 0) per box */
     int64_t max_points;     /* capacity: point forces over all sets at once; below 2^24
                                (LB_ERR_SIZE otherwise) */
-    int32_t tile_x;         /* tile shape (nodes); 0 = default. tile_x*tile_y*tile_z = 256 */
+    int32_t tile_x;         /* tile shape (nodes); 0 = default (with variant 0 too, the library
+                               chooses both for the sizes, storage and operator; with another
+                               variant the tile alone). tile_x*tile_y*tile_z = 256 */
     int32_t tile_y;
     int32_t tile_z;
     int32_t fp16_exponent;  /* FP16 only: initial scale exponent in [-100, 120] (the range the

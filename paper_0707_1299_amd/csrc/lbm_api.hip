@@ -71,16 +71,14 @@ struct Plan {
     Layout L;
     int chunks;
     long long cap;
+    int variant;       // the step kernel's variant bits (the caller's, or choose_default's)
+    int plain[3];      // a second tile whose checkpoints are accepted: plain_tile's, for a caller who named none
 };
 
-void choose_tile(const lb_params* p, int& tx, int& ty, int& tz)
+// Tile of a caller who names a variant but no tile (and, before the rules of choose_default, of every
+// caller who named no tile: checkpoints of such contexts carry it).
+void plain_tile(const lb_params* p, int& tx, int& ty, int& tz)
 {
-    if (p->tile_x > 0) {
-        tx = p->tile_x;
-        ty = p->tile_y;
-        tz = p->tile_z;
-        return;
-    }
     const double box_bytes = double(p->nx) * p->ny * p->nz * planes_of(p->storage) * storage_bytes(p->storage);
     if (p->storage == LB_STORAGE_MOM32 && p->nx >= 128) {
         tx = 128; ty = 1; tz = 2;   // long x rows: the gathered pieces are re-read from L1
@@ -92,6 +90,58 @@ void choose_tile(const lb_params* p, int& tx, int& ty, int& tz)
         tx = 32; ty = 4; tz = 2;
     } else {
         tx = 16; ty = 4; tz = 4;
+    }
+}
+
+// Tile and variant of a caller who names neither.  Measured per step with moving points on one
+// MI355X (us; the earlier choice, plain_tile with variant 0, first):
+//  - Tiles.  A tile row of 128 nodes where nx fills it (65 .. 128): fewer blocks share a misaligned row
+//    (101 x 75 x 62 FP32 35.4 -> 31.9).  Sparse FP32 rows of 192 and more: one row per block (256^3 with 10^4
+//    points 496 -> 429; 64 x 2 x 2 with the same variant 448), unless its last tile is mostly empty
+//    (300 nodes: 41.9 -> 44.8); many points per node want compact tiles (65536 chain markers at 256^3: 590 ->
+//    565, one row per block 940).  33 .. 63 nodes: one 64-node tile instead of two of 32 (100 boxes of
+//    48^3: 458 -> 283).  Two FP16 nodes per lane: a whole wave per row from 128 nodes on (256^3: 292 -> 240;
+//    64 x 2 x 2 250).  Moment storage: rows of a z plane together (256^3: 524 -> 460).
+//  - Block order.  Tile rows on one XCD (bit 64) except for lattices near the L2 size, where
+//    nothing is gained (64^3: 19.0 against 19.4).
+//  - Loads.  Cached (bit 2) where neighbouring rows are read again after more than the L2 has passed (planes
+//    over 2.6 MB: 256^3 455 -> 448; 128^3 67.5 -> 66.6 the other way) or where rows do not
+//    start on a cache line, so that two rows share one (300 x 60 x 40: 47.6 -> 41.1; boxes of 16^3: 75 -> 65).
+//  - The kernel for one tile per block (bit 128) where its missing tile loop saves registers: FP16, moment
+//    storage, the general and thermal operators, many points, small lattices; the FP32 and FP64 projected
+//    step is memory bound and faster with the loop (256^3 FP32: 429 against 447).
+// Batches of FP16 boxes keep the plain tile: their checkpoints hold a maximum per tile.
+void choose_default(const lb_params* p, int& tx, int& ty, int& tz, int& variant)
+{
+    const double esz = double(storage_bytes(p->storage)), planes = planes_of(p->storage);
+    const double N = double(p->nx) * p->ny * p->nz;
+    const double box_bytes = N * planes * esz, copies = 2.0 * box_bytes * p->nboxes;
+    const bool fp16 = p->storage == LB_STORAGE_FP16, mom = p->storage == LB_STORAGE_MOM32;
+    const bool pairs = fp16 && p->nx % 2 == 0, general = p->kT > 0.0 || p->collision != LB_COLLISION_PROJECTED;
+    const bool dense = double(p->max_points) * 1024.0 > N * p->nboxes;
+    plain_tile(p, tx, ty, tz);
+    if (fp16 && p->nboxes > 1) {
+    } else if (mom) {
+        if (p->nx >= 64) { tx = 64; ty = 4; tz = 1; }
+    } else if (pairs) {
+        if (p->nx >= 128) { tx = 128; ty = 2; tz = 1; }
+    } else if (p->nx > 64 && p->nx <= 128 && !dense && !(p->kT > 0.0)) {
+        tx = 128; ty = 2; tz = 1;
+    } else if (p->storage == LB_STORAGE_FP32 && p->nx >= 192 && !dense && !general &&
+               3 * ((p->nx + 255) / 256 * 256) <= 4 * p->nx) {
+        tx = 256; ty = 1; tz = 1;
+    } else if (p->nx > 32 && p->nx < 64) {
+        tx = 64; ty = 2; tz = 2;
+    }
+    variant = 0;
+    if (copies <= 48.0e6) {
+        variant = 128;
+    } else {
+        const double plane = double(p->nx) * p->ny * planes * esz;
+        const bool aligned = (long long)(p->nx * esz) % 128 == 0;
+        variant = 64;
+        if (!aligned || (plane > 2.6e6 && !dense)) variant |= 2;
+        if (fp16 || mom || general || dense) variant |= 128;
     }
 }
 
@@ -128,7 +178,18 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
         return LB_ERR_ARG;
     }
     int tx, ty, tz;
-    choose_tile(p, tx, ty, tz);
+    plain_tile(p, P.plain[0], P.plain[1], P.plain[2]);
+    P.variant = p->variant;
+    if (p->tile_x > 0) {
+        tx = p->tile_x;
+        ty = p->tile_y;
+        tz = p->tile_z;
+        P.plain[0] = tx; P.plain[1] = ty; P.plain[2] = tz;
+    } else if (p->variant == 0) {
+        choose_default(p, tx, ty, tz, P.variant);
+    } else {
+        tx = P.plain[0]; ty = P.plain[1]; tz = P.plain[2];
+    }
     if (!tile_supported(tx, ty, tz)) { why = "unsupported tile shape"; return LB_ERR_ARG; }
     Geom& G = P.G;
     memset(&G, 0, sizeof(G));
@@ -149,7 +210,7 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
         // lanes along x of one tile row: a wave on one row addresses each row block from
         // its own descriptor; narrower rows of lanes address the box from one descriptor
         // with 32-bit offsets
-        const bool pairs = p->storage == LB_STORAGE_FP16 && p->nx % 2 == 0 && !((p->variant >> 5) & 1);
+        const bool pairs = p->storage == LB_STORAGE_FP16 && p->nx % 2 == 0 && !((P.variant >> 5) & 1);
         const int lanes_x = pairs ? tx / 2 : tx;
         if (lanes_x < 64 && (unsigned long long)G.sbox * storage_bytes(p->storage) >= (1ULL << 32)) {
             why = "tiles with fewer than 64 lanes along x (64 nodes, or 128 with two FP16 nodes per lane) need a "
@@ -174,10 +235,10 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     }
     if (G.maxp > (1 << PK_BITS)) { why = "tile too small for the stencil"; return LB_ERR_ARG; }
     G.bchunks = int(std::min<long long>(256, (G.tiles_per_box + 255) / 256));
-    G.tpb = 1 << ((p->variant >> 2) & 3);
-    G.order = (p->variant >> 4) & 1;
+    G.tpb = 1 << ((P.variant >> 2) & 3);
+    G.order = (P.variant >> 4) & 1;
     G.lgrp = 0;
-    if ((p->variant >> 6) & 1) {
+    if ((P.variant >> 6) & 1) {
         // the runs of one tile row on one XCD: needs a power-of-two count of whole runs per row
         // (otherwise launch order)
         G.order = 1;
@@ -186,7 +247,7 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
             G.lgrp = __builtin_ctz(unsigned(G.ntx / G.tpb));
         }
     }
-    G.pairs = p->storage == LB_STORAGE_FP16 && p->nx % 2 == 0 && !((p->variant >> 5) & 1);
+    G.pairs = p->storage == LB_STORAGE_FP16 && p->nx % 2 == 0 && !((P.variant >> 5) & 1);
     G.coll = p->kT > 0.0 ? 2 : (p->collision != LB_COLLISION_PROJECTED ? 1 : 0);
     G.seed_lo = uint32_t(p->seed);
     G.seed_hi = uint32_t(p->seed >> 32);
@@ -446,7 +507,7 @@ void enqueue_step(lb_ctx* c, hipStream_t s, bool rebuild)
     }
     unsigned long long* tin = G.coll == 2 ? c->tctr() + c->cur : nullptr;
     unsigned long long* tout = G.coll == 2 ? c->tctr() + (c->cur ^ 1) : nullptr;
-    launch_lattice(c->p.storage, G, 0, c->p.variant, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(),
+    launch_lattice(c->p.storage, G, 0, c->P.variant, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(),
                    npts > 0 ? c->toff() : nullptr, c->tlist(), c->rec(), c->partial(), (double*)c->tmax(), tin, tout,
                    s, e0, e1);
     long long off = 0;
@@ -918,7 +979,8 @@ int lb_sync(lb_ctx* c)
     return read_flags(c);
 }
 
-static CkptHeader ckpt_layout(const lb_ctx* c)
+// Layout of a checkpoint of this context, or of one whose tile list has `tiles` entries.
+static CkptHeader ckpt_layout(const lb_ctx* c, int64_t tiles)
 {
     CkptHeader h;
     memset(&h, 0, sizeof(h));
@@ -930,12 +992,12 @@ static CkptHeader ckpt_layout(const lb_ctx* c)
     h.steps = c->steps;
     h.npoints = total_points(c);
     h.pop_bytes = (int64_t)G.sbox * G.nboxes * (int64_t)storage_bytes(c->p.storage);
-    h.tiles = G.ntiles;
+    h.tiles = tiles;
     size_t o = align_up(sizeof(CkptHeader));
     auto take = [&](size_t b) { const size_t at = o; o = align_up(o + std::max<size_t>(b, 1)); return (int64_t)at; };
     h.off_pop = take(h.pop_bytes);
     h.off_boxes = take(sizeof(BoxDev) * G.nboxes);
-    h.off_tmax = take(sizeof(float) * G.ntiles);
+    h.off_tmax = take(sizeof(float) * tiles);
     h.off_smax = take(sizeof(unsigned) * SMAX_SLOTS * SMAX_STRIDE);
     h.off_tctr = take(sizeof(unsigned long long));
     h.off_nf = take(sizeof(int) * G.nboxes);
@@ -947,7 +1009,7 @@ static CkptHeader ckpt_layout(const lb_ctx* c)
 int lb_checkpoint_bytes(const lb_ctx* c, size_t* bytes)
 {
     if (!c || !bytes) return LB_ERR_ARG;
-    *bytes = (size_t)ckpt_layout(c).total;
+    *bytes = (size_t)ckpt_layout(c, c->P.G.ntiles).total;
     return LB_OK;
 }
 
@@ -959,7 +1021,7 @@ int lb_checkpoint_save(lb_ctx* c, void* dst)
     // the binning windows are part of the state once the registered sets have been binned
     if (total_points(c) > 0 && c->binned_gen != c->gen)
         return fail(c, LB_ERR_STATE, "checkpoint: step once after changing the point sets");
-    c->ckpt = ckpt_layout(c);
+    c->ckpt = ckpt_layout(c, c->P.G.ntiles);
     const CkptHeader& h = c->ckpt;
     char* d = (char*)dst;
     hipStream_t s = c->stream;
@@ -987,20 +1049,28 @@ int lb_checkpoint_load(lb_ctx* c, const void* src)
     int r = hip_check(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize");
     if (!r) r = hip_check(c, hipMemcpy(&h, src, sizeof(h), hipMemcpyDefault), "checkpoint header");
     if (r) return r;
-    const CkptHeader want = ckpt_layout(c);
     if (memcmp(h.magic, CKPT_MAGIC, 8) != 0) return fail(c, LB_ERR_ARG, "not a checkpoint");
+    // the context's own tile, or plain_tile's where the caller named none (only the per-tile maxima depend on
+    // the tile, and those matter for batches of FP16 boxes alone, whose default is the plain tile)
+    const Geom& G = c->P.G;
+    const int* q = c->P.plain;
+    const bool same = h.tx == G.tx && h.ty == G.ty && h.tz == G.tz;
+    const bool plain = h.tx == q[0] && h.ty == q[1] && h.tz == q[2];
+    CkptHeader want = ckpt_layout(c, same || !plain ? G.ntiles
+                                     : (int64_t)((G.nx + q[0] - 1) / q[0]) * ((G.ny + q[1] - 1) / q[1]) *
+                                           ((G.nz + q[2] - 1) / q[2]) * G.nboxes);
     if (h.nx != want.nx || h.ny != want.ny || h.nz != want.nz || h.nboxes != want.nboxes ||
-        h.storage != want.storage || h.collision != want.collision || h.tx != want.tx || h.ty != want.ty ||
-        h.tz != want.tz || h.npoints != want.npoints || h.total != want.total)
+        h.storage != want.storage || h.collision != want.collision || !(same || plain) || h.tiles != want.tiles ||
+        h.npoints != want.npoints || h.total != want.total)
         return fail(c, LB_ERR_ARG, "checkpoint of another lattice, tiling or point count");
     const char* d = (const char*)src;
     hipStream_t s = c->stream;
     auto cp = [&](void* dst, int64_t off, size_t n) {
         if (!r) r = hip_check(c, hipMemcpyAsync(dst, d + off, n, hipMemcpyDefault, s), "checkpoint copy");
     };
-    cp(c->pop(c->cur), h.off_pop, (size_t)h.pop_bytes);
-    cp(c->boxes(), h.off_boxes, sizeof(BoxDev) * c->p.nboxes);
-    cp(c->tmax(), h.off_tmax, sizeof(float) * c->P.G.ntiles);
+    cp(c->pop(c->cur), want.off_pop, (size_t)want.pop_bytes);
+    cp(c->boxes(), want.off_boxes, sizeof(BoxDev) * c->p.nboxes);
+    if (same) cp(c->tmax(), h.off_tmax, sizeof(float) * G.ntiles);
     cp(c->smax(), h.off_smax, sizeof(unsigned) * SMAX_SLOTS * SMAX_STRIDE);
     cp(c->tctr() + c->cur, h.off_tctr, sizeof(unsigned long long));
     cp(c->nf(), h.off_nf, sizeof(int) * c->p.nboxes);
