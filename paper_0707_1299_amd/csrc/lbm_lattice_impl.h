@@ -40,7 +40,7 @@ enum Mode { M_STEP = 0, M_MOMENTS = 1, M_DIAG = 2 };
 // COLL: 1 = general collision of Eq. mrtlbe (bulk mode at its own rate, ghost
 // moments multiplied by kappa_g instead of projected out); 2 = the same plus
 // thermal noise on the fifteen non-conserved modes, drawn for step *tin.
-template <int ST, int TX, int TY, int TZ, int MODE, int VAR, int COLL = 0, int NPL = 1>
+template <int ST, int TX, int TY, int TZ, int MODE, int VAR, int COLL = 0, int NPL = 1, bool ONE = false>
 __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
                                              const typename StoreT<ST>::S* __restrict__ src,
                                              typename StoreT<ST>::S* __restrict__ dst,
@@ -99,6 +99,17 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
     // FP16: stored values are (deviation / w_i) 2^e; the conversion multiplies by w_i 2^-e (exact:
     // a power of two times w_i), so the moments come out in deviation units
     [[maybe_unused]] const float sc = ST == ST_FP16 ? (MODE == M_STEP ? B.s_in : ldexpf(1.0f, -B.e_data)) : 1.0f;
+    // the tile's entries in the point lists (read before the pull where they may be staged, after the moments
+    // otherwise)
+    int k0 = 0, k1 = 0;
+    auto entries = [&] {
+        if (toff) {
+            k0 = toff[tile];
+            k1 = toff[tile + 1];
+        }
+    };
+    constexpr bool STAGE = NPL == 1 && (MODE != M_STEP || (ONE && COLL == 0));
+    if constexpr (STAGE) entries();
     T f[NQ];
     if constexpr (NPL == 2) {
         const int xl = x == 0 ? G.nx - 2 : x - 2, xr = x + 2 == G.nx ? 0 : x + 2;
@@ -108,7 +119,38 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
         pull_node<ST, NTL, ADDR>(sb, G.rb, G.kp, box_bytes, G.ny, x, y, z, xm, xp, ym, yp, zm, zp, f, sc);
     }
 
-    int k0 = 0, k1 = 0;         // the tile's entries in the point lists (read below)
+    // A crowded tile's points are staged in LDS, RPT records at a time, each thread fetching one 16-byte word:
+    // one chain of two dependent loads for all of them, in flight behind the populations.  Read one after the
+    // other through the scalar cache, each point costs every wave that chain twice (spreading and
+    // interpolation), but a few points less than the staging does.  Chains at 256^3 (65536 markers)
+    // 520 -> 480 us per step kernel, 48^3 with 321 colloids 9.8 -> 9.0; staged from one point on, the
+    // single force in 32^3 FP64 lost 6 %, while moment storage, which waits on the vector memory pipe,
+    // gained 3 % (256^3 with 10^4 colloids) and keeps no scalar form.  Only where the registers
+    // suffice: reads between steps and the projected step built for one tile per block (38 -> 48 VGPRs; the
+    // general and thermal operators and the tile loop would spill or lose waves).
+    constexpr int STAGE_MIN = ST == ST_MOM32 ? 1 : 4;
+    constexpr int RW = int(sizeof(PRec<T>) / 16), RPT = STAGE ? BLOCK / RW : 1;
+    __shared__ uint4 sraw[STAGE ? RPT * RW : 1];
+    __shared__ int sent[RPT];
+    const PRec<T>* srec = reinterpret_cast<const PRec<T>*>(sraw);
+    [[maybe_unused]] const int sp = int(threadIdx.x) / RW, sw = int(threadIdx.x) - sp * RW;   // record and word
+    [[maybe_unused]] uint4 fword;
+    [[maybe_unused]] int fent = 0;
+    auto fetch = [&](int kb) {
+        if (sp < min(RPT, k1 - kb)) {
+            fent = tlist[kb + sp];
+            fword = reinterpret_cast<const uint4*>(rec + pk_point(fent))[sw];
+        }
+    };
+    auto stage = [&](int kb) {
+        if (sp < min(RPT, k1 - kb)) {
+            sraw[threadIdx.x] = fword;
+            if (sw == 0) sent[sp] = fent;
+        }
+        __syncthreads();
+    };
+    const bool staged = STAGE && k1 - k0 >= STAGE_MIN;
+    if (staged) fetch(k0);
     S* db = dst + (long long)box * G.sbox;
     const unsigned row = unsigned(z) * unsigned(G.ny) + unsigned(y);
     typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
@@ -210,23 +252,32 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
 
         // ---- force density at this node: counter-force + the tile's points
         T gx = gcx, gy = gcy, gz = gcz;
-        if (h == 0 && toff) {
-            k0 = toff[tile];
-            k1 = toff[tile + 1];
-        }
-        for (int k = k0; k < k1; ++k) {
-            const PRec<T>& r = rec[pk_point(tlist[k])];
-            // rows the point's stencil misses take nothing from it: skip them (a scalar branch
-            // when y and z are wave-uniform; otherwise waves whose lanes all miss skip it)
+        auto spread = [&](const PRec<T>& r) {
+            // rows the point's stencil misses take nothing from it: skip them (a branch taken by
+            // whole waves when y and z are wave-uniform; otherwise waves whose lanes all miss skip it)
             int dy = y - r.by, dz = z - r.bz;
             if (dy < 0) dy += G.ny;
             if (dz < 0) dz += G.nz;
-            if (dy > 3 || dz > 3) continue;
+            if (dy > 3 || dz > 3) return;
             const T w = stencil_w<T>(xh, r.bx, G.nx, r.wx) * stencil_w<T>(y, r.by, G.ny, r.wy) *
                         stencil_w<T>(z, r.bz, G.nz, r.wz);
             gx += r.f[0] * w;
             gy += r.f[1] * w;
             gz += r.f[2] * w;
+        };
+        if (!STAGE && h == 0) entries();
+        if (staged) {
+            for (int kb = k0; kb < k1; kb += RPT) {
+                if (kb > k0) {
+                    __syncthreads();   // every wave has read the records before
+                    fetch(kb);
+                }
+                stage(kb);
+                const int n = min(RPT, k1 - kb);
+                for (int p = 0; p < n; ++p) spread(srec[p]);
+            }
+        } else if constexpr (!STAGE || STAGE_MIN > 1) {
+            for (int k = k0; k < k1; ++k) spread(rec[pk_point(tlist[k])]);
         }
 
         const T rho = rho0 + drho;
@@ -548,9 +599,7 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
         __syncthreads();
         const int dx = lane & 3, dy = (lane >> 2) & 3, dz = lane >> 4;
         const int x0 = itx * TX, y0 = ity * TY, z0 = itz * TZ;
-        for (int kk = k0 + wave; kk < k1; kk += NW) {
-            const int ent = tlist[kk];
-            const PRec<T>& r = rec[pk_point(ent)];
+        auto interpolate = [&](const int ent, const PRec<T>& r) {
             int gx = r.bx + dx, gy = r.by + dy, gz = r.bz + dz;
             if (gx >= G.nx) gx -= G.nx;
             if (gy >= G.ny) gy -= G.ny;
@@ -563,7 +612,7 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
             // a tile of the point's window that holds no node of its stencil: its partial is zero
             if (!__any(in)) {
                 if (lane == 0) o[0] = o[1] = o[2] = T(0);
-                continue;
+                return;
             }
             const int li = in ? lx2 + TX * (ly2 + TY * lz2) : 0;
             const T w = in ? r.wx[dx] * r.wy[dy] * r.wz[dz] : T(0);
@@ -575,8 +624,25 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
                 o[1] = sy;
                 o[2] = sz;
             }
+        };
+        if (staged) {
+            // the records of one chunk are still staged
+            for (int kb = k0; kb < k1; kb += RPT) {
+                if (k1 - k0 > RPT) {
+                    if (kb > k0) __syncthreads();
+                    fetch(kb);
+                    stage(kb);
+                }
+                const int n = min(RPT, k1 - kb);
+                for (int p = wave; p < n; p += NW) interpolate(sent[p], srec[p]);
+            }
+        } else if constexpr (!STAGE || STAGE_MIN > 1) {
+            for (int kk = k0 + wave; kk < k1; kk += NW) {
+                const int ent = tlist[kk];
+                interpolate(ent, rec[pk_point(ent)]);
+            }
         }
-        if (G.tpb > 1) __syncthreads();   // su is rewritten by the block's next tile
+        if (G.tpb > 1) __syncthreads();   // su and the staged records are rewritten by the block's next tile
     }
 }
 
@@ -624,7 +690,7 @@ void k_lattice(const Geom G, const typename StoreT<ST>::S* __restrict__ src,
     const int first = (G.order == 1 ? b : G.order == 0 ? xcd_tile(b, nb) : row_group_run(b, nb, G.lgrp)) * G.tpb;
     if constexpr (ONE) {
         if (first < G.ntiles)
-            lattice_tile<ST, TX, TY, TZ, MODE, VAR, COLL, NPL>(G, first, src, dst, boxes, toff, tlist, rec, out0, out1,
+            lattice_tile<ST, TX, TY, TZ, MODE, VAR, COLL, NPL, true>(G, first, src, dst, boxes, toff, tlist, rec, out0, out1,
                                                                tin);
     } else {
         const int last = min((long long)first + G.tpb, G.ntiles);
