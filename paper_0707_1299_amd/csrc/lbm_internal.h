@@ -23,6 +23,9 @@ struct AdvectLaunch {
     float in_shift[4], in_scale[4], out_scale;
     int advect;
     const unsigned long long* tin;   // thermal runs: step counter of this step (else NULL)
+    void* rec;                       // records to write for a following step (else NULL), with its error flags
+    int* err;
+    int fp16_exp;                    // with rec: also set the next FP16 exponent (one box)
 };
 
 // marker forces of a chain (kind 0) or surface (kind 1) set
@@ -58,8 +61,7 @@ void launch_bins(int storage, const Geom& G, long long npts, const void* rec, in
 void launch_box_update(int storage, const Geom& G, const void* rec, const int* toff, const int* tlist,
                        const double* psum, long long npsum, const float* tmax, double* part, float* pmax,
                        unsigned* ticket, BoxDev* boxes, int zero_net, int fp16_exp, hipStream_t s);
-void launch_advect(int storage, const Geom& G, const AdvectLaunch& a, const BoxDev* boxes, void* partial,
-                   hipStream_t s);
+void launch_advect(int storage, const Geom& G, const AdvectLaunch& a, BoxDev* boxes, void* partial, hipStream_t s);
 void launch_interp_points(int storage, const Geom& G, long long n, const double* pos, const int* boxid, double* out,
                           const void* src, const BoxDev* boxes, const int* toff, const int* tlist, const void* rec,
                           hipStream_t s);

@@ -108,48 +108,15 @@ int log_lanes(int maxp)
 //    With psum set (one box), each block also writes the sum of its points'
 //    forces (as the records hold them) to psum[blockIdx.x]: the counter-force
 //    then needs no pass over the tile lists.
+// Record of point p at position R with force F in box `box`; fs: the force as the record holds it.
 template <class T>
-__device__ __forceinline__ void prep_point(const Geom& G, long long i, long long p, const double* __restrict__ pos,
-                                           const double* __restrict__ frc, const int* __restrict__ boxid,
-                                           PRec<T>* __restrict__ rec, int* __restrict__ err, double (&fs)[3]);
-
-template <class T>
-__global__ __launch_bounds__(256) void k_prep(const Geom G, long long n, long long off, const double* __restrict__ pos,
-                                              const double* __restrict__ frc, const int* __restrict__ boxid,
-                                              PRec<T>* __restrict__ rec, int* __restrict__ err,
-                                              double* __restrict__ psum)
+__device__ __forceinline__ void write_record(const Geom& G, long long p, double (&R)[3], double (&F)[3], int box,
+                                             PRec<T>* __restrict__ rec, int* __restrict__ err, double (&fs)[3])
 {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    // the list build's grid-barrier counter (err[2]) starts every build at zero
-    if (i == 0) err[2] = 0;
-    double fs[3] = {0.0, 0.0, 0.0};
-    if (i < n) prep_point<T>(G, i, off + i, pos, frc, boxid, rec, err, fs);
-    if (!psum) return;
-    __shared__ double red[4][3];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int k = 0; k < 3; ++k) {
-        const double v = wave_sum(fs[k]);
-        if (lane == 0) red[wave][k] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < 3) {
-        const int k = threadIdx.x;
-        psum[3 * (long long)blockIdx.x + k] = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
-    }
-}
-
-template <class T>
-__device__ __forceinline__ void prep_point(const Geom& G, long long i, long long p, const double* __restrict__ pos,
-                                           const double* __restrict__ frc, const int* __restrict__ boxid,
-                                           PRec<T>* __restrict__ rec, int* __restrict__ err, double (&fs)[3])
-{
-    int box = boxid ? boxid[i] : 0;
     if (box < 0 || box >= G.nboxes) {
         atomicOr(err, 1);
         box = 0;
     }
-    double R[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
-    double F[3] = {frc[3 * i], frc[3 * i + 1], frc[3 * i + 2]};
     bool ok = true;
     for (int a = 0; a < 3; ++a) ok = ok && (fabs(R[a]) < 1e300) && (fabs(F[a]) < 1e300);
     if (!ok) {
@@ -187,6 +154,35 @@ __device__ __forceinline__ void prep_point(const Geom& G, long long i, long long
     if (!(in_window(r.bx, w.x, G.nx) && in_window(r.by, w.y, G.ny) && in_window(r.bz, w.z, G.nz) && w.w == box)) {
         if (!G.rebox[box]) atomicOr(&G.rebox[box], 1);
         if (!*G.rebin) atomicOr(G.rebin, 1);
+    }
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void k_prep(const Geom G, long long n, long long off, const double* __restrict__ pos,
+                                              const double* __restrict__ frc, const int* __restrict__ boxid,
+                                              PRec<T>* __restrict__ rec, int* __restrict__ err,
+                                              double* __restrict__ psum)
+{
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    // the list build's grid-barrier counter (err[2]) starts every build at zero
+    if (i == 0) err[2] = 0;
+    double fs[3] = {0.0, 0.0, 0.0};
+    if (i < n) {
+        double R[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
+        double F[3] = {frc[3 * i], frc[3 * i + 1], frc[3 * i + 2]};
+        write_record<T>(G, off + i, R, F, boxid ? boxid[i] : 0, rec, err, fs);
+    }
+    if (!psum) return;
+    __shared__ double red[4][3];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int k = 0; k < 3; ++k) {
+        const double v = wave_sum(fs[k]);
+        if (lane == 0) red[wave][k] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        const int k = threadIdx.x;
+        psum[3 * (long long)blockIdx.x + k] = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
     }
 }
 
@@ -523,6 +519,11 @@ struct AdvectArgs {
     float in_shift[4], in_scale[4], out_scale;
     int advect;
     const unsigned long long* tin;
+    // a step that another one follows in the same call (see enqueue_step): the points' records for it are
+    // written here, and one block more sets the FP16 exponent
+    void* rec;
+    int* err;
+    int fp16_exp;
 };
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float(uint32_t(h) << 16); }
@@ -534,20 +535,21 @@ template <class T>
 __device__ __forceinline__ void group_sum(const Geom& G, const T* __restrict__ partial, long long p, int r,
                                           double (&U)[3])
 {
-    // the point's partials, one per tile of its window (nt <= maxp <= 64 slots)
-    const int4 win = G.win[p];
-    const int nt = axis_count(win.x, G.nx, G.ltx) * axis_count(win.y, G.ny, G.lty) * axis_count(win.z, G.nz, G.ltz);
+    // the point's partials, one per tile of its window (nt <= maxp <= 64 slots); the loads cover all maxp slots,
+    // so that they do not wait for the window
     const T* pp = partial + p * G.maxp * 3;
-    double v[64 / ADV_GP][3];
+    T v[64 / ADV_GP][3];
 #pragma unroll
     for (int m = 0; m < 64 / ADV_GP; ++m)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) v[m][c] = r + m * ADV_GP < nt ? double(pp[(r + m * ADV_GP) * 3 + c]) : 0.0;
+        for (int c = 0; c < 3; ++c) v[m][c] = r + m * ADV_GP < G.maxp ? pp[(r + m * ADV_GP) * 3 + c] : T(0);
+    const int4 win = G.win[p];
+    const int nt = axis_count(win.x, G.nx, G.ltx) * axis_count(win.y, G.ny, G.lty) * axis_count(win.z, G.nz, G.ltz);
     U[0] = U[1] = U[2] = 0.0;
 #pragma unroll
     for (int m = 0; m < 64 / ADV_GP; ++m)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) U[c] += v[m][c];
+        for (int c = 0; c < 3; ++c) U[c] += r + m * ADV_GP < nt ? double(v[m][c]) : 0.0;
 #pragma unroll
     for (int d = 1; d < ADV_GP; d <<= 1)
 #pragma unroll
@@ -560,8 +562,9 @@ __device__ __forceinline__ int point_box(const Geom& G, const AdvectArgs& A, lon
     return (box < 0 || box >= G.nboxes) ? 0 : box;
 }
 
-// Outputs and the move of point i (set-local; p = A.off + i) with interpolated velocity U;
-// y: the network's output for the point (used only with A.mlp).
+// Outputs and the move of point i (set-local; p = A.off + i) with interpolated velocity U, and its record
+// for the next step if A.rec is set; y: the network's output for the point (used only with A.mlp).
+template <class T>
 __device__ __forceinline__ void finish_point(const Geom& G, const AdvectArgs& A, const BoxDev* __restrict__ boxes,
                                              long long i, long long p, const double (&U)[3], float y)
 {
@@ -586,22 +589,52 @@ __device__ __forceinline__ void finish_point(const Geom& G, const AdvectArgs& A,
         const double amp = sqrt(boxes[box].pn * fmax(A.inv_a - inv_aL, 0.0));
         for (int a = 0; a < 3; ++a) zeta[a] = amp * z[a];
     }
-    for (int a = 0; a < 3; ++a)
-        A.pos[3 * i + a] = wrap_pos(R[a] + (U[a] + zeta[a]) + A.frc[3 * i + a] * mob, L[a]);
+    double F[3] = {A.frc[3 * i], A.frc[3 * i + 1], A.frc[3 * i + 2]}, Rn[3];
+    for (int a = 0; a < 3; ++a) {
+        Rn[a] = wrap_pos(R[a] + (U[a] + zeta[a]) + F[a] * mob, L[a]);
+        A.pos[3 * i + a] = Rn[a];
+    }
+    if (A.rec) {
+        double fs[3];
+        write_record<T>(G, p, Rn, F, A.boxid ? A.boxid[i] : 0, static_cast<PRec<T>*>(A.rec), A.err, fs);
+    }
+}
+
+// What the first thread and the last block of a move kernel do for a step that follows: the list build's
+// barrier counter starts at zero, and (one box, FP16) the exponent comes from the maxima the step
+// kernel left in the slots.  Returns true for the block that is not one of points.
+__device__ __forceinline__ bool next_step(const Geom& G, const AdvectArgs& A, BoxDev* __restrict__ boxes)
+{
+    if (!A.rec) return false;
+    if (blockIdx.x == 0 && threadIdx.x == 0) A.err[2] = 0;
+    if (!A.fp16_exp || blockIdx.x != gridDim.x - 1) return false;
+    __shared__ float redm[4];
+    float m = 0.0f;
+    for (int u = threadIdx.x; u < SMAX_SLOTS; u += blockDim.x) {
+        m = fmaxf(m, __uint_as_float(G.smax[u * SMAX_STRIDE]));
+        G.smax[u * SMAX_STRIDE] = 0u;
+    }
+    m = wave_max(m);
+    if ((threadIdx.x & 63) == 0) redm[threadIdx.x >> 6] = m;
+    __syncthreads();
+    const double none[4][3] = {};
+    if (threadIdx.x == 0) finish_box(G, boxes[0], none, redm, 0, 1);
+    return true;
 }
 
 // Without the MLP: one group per point, lane 0 of the group finishes it.
 template <class T>
-__global__ __launch_bounds__(256) void k_advect(const Geom G, const AdvectArgs A, const BoxDev* __restrict__ boxes,
+__global__ __launch_bounds__(256) void k_advect(const Geom G, const AdvectArgs A, BoxDev* boxes,
                                                 const T* __restrict__ partial)
 {
+    if (next_step(G, A, boxes)) return;
     const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long i = gid / ADV_GP;
     const int r = int(gid % ADV_GP);
     if (i >= A.n) return;   // whole groups: a group is 8 aligned lanes of one wave
     double U[3];
     group_sum(G, partial, A.off + i, r, U);
-    if (r == 0) finish_point(G, A, boxes, i, A.off + i, U, 0.0f);
+    if (r == 0) finish_point<T>(G, A, boxes, i, A.off + i, U, 0.0f);
 }
 
 // With the MLP correction to 1/a_L (4 -> 64 tanh -> 64 tanh -> 1, bf16 weights staged in LDS
@@ -628,10 +661,10 @@ __device__ __forceinline__ float tanh_fast(float s)
 typedef float mfma_acc16 __attribute__((ext_vector_type(16)));
 
 template <class T>
-__global__ __launch_bounds__(MLP_BLOCK) void k_advect_mlp(const Geom G, const AdvectArgs A,
-                                                          const BoxDev* __restrict__ boxes,
+__global__ __launch_bounds__(MLP_BLOCK) void k_advect_mlp(const Geom G, const AdvectArgs A, BoxDev* boxes,
                                                           const T* __restrict__ partial)
 {
+    if (next_step(G, A, boxes)) return;
     __shared__ float4 W1[MLP_H];                         // rows of W1 (4 inputs)
     __shared__ float b1[MLP_H], b2[MLP_H], W3[MLP_H];
     __shared__ float W2T[MLP_H][MLP_H + 1];              // W2 transposed: [input k][unit] (padded row)
@@ -724,7 +757,7 @@ __global__ __launch_bounds__(MLP_BLOCK) void k_advect_mlp(const Geom G, const Ad
     __syncthreads();
     if (wave == 0 && live) {
         const double U[3] = {Us[lane][0], Us[lane][1], Us[lane][2]};
-        finish_point(G, A, boxes, i, A.off + i, U, (ys[0][lane] + ys[1][lane]) + b3);
+        finish_point<T>(G, A, boxes, i, A.off + i, U, (ys[0][lane] + ys[1][lane]) + b3);
     }
 }
 
@@ -979,8 +1012,7 @@ void launch_box_update(int storage, const Geom& G, const void* rec, const int* t
 }
 
 
-void launch_advect(int storage, const Geom& G, const AdvectLaunch& a, const BoxDev* boxes, void* partial,
-                   hipStream_t s)
+void launch_advect(int storage, const Geom& G, const AdvectLaunch& a, BoxDev* boxes, void* partial, hipStream_t s)
 {
     if (a.n <= 0) return;
     AdvectArgs A;
@@ -1001,8 +1033,12 @@ void launch_advect(int storage, const Geom& G, const AdvectLaunch& a, const BoxD
     A.out_scale = a.out_scale;
     A.advect = a.advect;
     A.tin = a.tin;
-    const unsigned nb = nblk(a.n * ADV_GP, 256);
-    const unsigned nbm = nblk(a.n, 64);   // with the network: 64 points per block
+    A.rec = a.rec;
+    A.err = a.err;
+    A.fp16_exp = a.fp16_exp;
+    const unsigned more = a.rec && a.fp16_exp ? 1 : 0;
+    const unsigned nb = nblk(a.n * ADV_GP, 256) + more;
+    const unsigned nbm = nblk(a.n, 64) + more;   // with the network: 64 points per block
     if (storage == ST_FP64) {
         if (A.mlp)
             hipLaunchKernelGGL(k_advect_mlp<double>, dim3(nbm), dim3(MLP_BLOCK), 0, s, G, A, boxes, (const double*)partial);
