@@ -20,7 +20,7 @@ LIBDIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(LIBDIR, "liblbm.so")
 SOURCES = ["lbm_lattice_fp64.hip", "lbm_lattice_fp32.hip", "lbm_lattice_fp16.hip", "lbm_lattice_mom32.hip",
            "lbm_lattice_fp64_one.hip", "lbm_lattice_fp32_one.hip", "lbm_lattice_fp16_one.hip", "lbm_lattice_mom32_one.hip",
-           "lbm_lattice.hip", "lbm_points.hip", "lbm_elastic.hip", "lbm_api.hip", "lbm_mlp.hip", "lbm_probe.hip"]
+           "lbm_lattice.hip", "lbm_march.hip", "lbm_points.hip", "lbm_elastic.hip", "lbm_api.hip", "lbm_mlp.hip", "lbm_probe.hip"]
 ARCH = os.environ.get("LBM_OFFLOAD_ARCH", "gfx950")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

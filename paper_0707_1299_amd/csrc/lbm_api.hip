@@ -62,15 +62,18 @@ struct Layout {
     size_t pop[2], boxes, rec, psum, count, cursor, toff, bsum, tlist, tlist_tmp, partial, fpart, pmax, tmax, smax, ticket,
         tctr,
         err, nf, rebin, rebox, win,
-        diag, diagout;
+        diag, diagout, field;
     size_t total;
 };
 
 struct Plan {
-    Geom G;
+    Geom G;            // the geometry in use: Gp, or Gm while the marching kernels may take the steps (see set_geometry)
+    Geom Gp, Gm;
     Layout L;
     int chunks;
     long long cap;
+    int march;         // z planes per block of the marching step kernels (see choose_march); 0: none
+    double march_blocks;   // plane iterations of one marching launch, rims left out: blocks times planes
     int variant;       // the step kernel's variant bits (the caller's, or choose_default's)
     int plain[3];      // a second tile whose checkpoints are accepted: plain_tile's, for a caller who named none
 };
@@ -145,6 +148,110 @@ void choose_default(const lb_params* p, int& tx, int& ty, int& tz, int& variant)
     }
 }
 
+// Geometry of the lattice with tiles of tx x ty x tz (checked against the storage, the box size and cap points).
+int fill_geometry(const lb_params* p, int variant, long long cap, int tx, int ty, int tz, Geom& G, std::string& why)
+{
+    memset(&G, 0, sizeof(G));
+    G.nx = p->nx; G.ny = p->ny; G.nz = p->nz; G.nboxes = p->nboxes;
+    G.tx = tx; G.ty = ty; G.tz = tz;
+    G.ltx = __builtin_ctz(tx); G.lty = __builtin_ctz(ty); G.ltz = __builtin_ctz(tz);
+    G.ntx = (p->nx + tx - 1) / tx;
+    G.nty = (p->ny + ty - 1) / ty;
+    G.ntz = (p->nz + tz - 1) / tz;
+    set_div_magic(G.ntx, G.mtx, G.stx);
+    set_div_magic(G.nty, G.mty, G.sty);
+    set_div_magic(G.ntz, G.mtz, G.stz);
+    G.N = (long long)p->nx * p->ny * p->nz;
+    G.kp = p->nx;
+    G.rb = (long long)planes_of(p->storage) * p->nx;
+    G.sbox = ((long long)p->ny * p->nz * G.rb + 255) / 256 * 256 + 64;
+    {
+        // lanes along x of one tile row: a wave on one row addresses each row block from
+        // its own descriptor; narrower rows of lanes address the box from one descriptor
+        // with 32-bit offsets
+        const bool pairs = p->storage == LB_STORAGE_FP16 && p->nx % 2 == 0 && !((variant >> 5) & 1);
+        const int lanes_x = pairs ? tx / 2 : tx;
+        if (lanes_x < 64 && (unsigned long long)G.sbox * storage_bytes(p->storage) >= (1ULL << 32)) {
+            why = "tiles with fewer than 64 lanes along x (64 nodes, or 128 with two FP16 nodes per lane) need a "
+                  "box of under 4 GiB";
+            return LB_ERR_ARG;
+        }
+        // two FP16 nodes per lane on whole-wave rows address each z plane of rows from one descriptor
+        if (pairs && lanes_x >= 64 && (unsigned long long)p->ny * G.rb * storage_bytes(p->storage) >= (1ULL << 32)) {
+            why = "two FP16 nodes per lane need a z plane (ny * nx nodes) of under 4 GiB";
+            return LB_ERR_SIZE;
+        }
+    }
+    G.tiles_per_box = (long long)G.ntx * G.nty * G.ntz;
+    G.ntiles = G.tiles_per_box * p->nboxes;
+    G.rho0 = p->rho0 > 0.0 ? p->rho0 : 1.0;
+    G.maxp = max_axis_tiles(p->nx, tx) * max_axis_tiles(p->ny, ty) * max_axis_tiles(p->nz, tz);
+    if (G.ntiles >= (1LL << 31) - 1) { why = "too many tiles"; return LB_ERR_SIZE; }
+    if (cap * G.maxp >= (1LL << 31) - 1 || cap >= (1LL << (31 - PK_SHIFT))) {
+        why = "max_points too large";
+        return LB_ERR_SIZE;
+    }
+    if (G.maxp > (1 << PK_BITS)) { why = "tile too small for the stencil"; return LB_ERR_ARG; }
+    G.bchunks = int(std::min<long long>(256, (G.tiles_per_box + 255) / 256));
+    G.tpb = 1 << ((variant >> 2) & 3);
+    G.order = (variant >> 4) & 1;
+    G.lgrp = 0;
+    if ((variant >> 6) & 1) {
+        // the runs of one tile row on one XCD: needs a power-of-two count of whole runs per row
+        // (otherwise launch order)
+        G.order = 1;
+        if (G.ntx % G.tpb == 0 && ((G.ntx / G.tpb) & (G.ntx / G.tpb - 1)) == 0) {
+            G.order = 2;
+            G.lgrp = __builtin_ctz(unsigned(G.ntx / G.tpb));
+        }
+    }
+    G.pairs = p->storage == LB_STORAGE_FP16 && p->nx % 2 == 0 && !((variant >> 5) & 1);
+    G.coll = p->kT > 0.0 ? 2 : (p->collision != LB_COLLISION_PROJECTED ? 1 : 0);
+    G.seed_lo = uint32_t(p->seed);
+    G.seed_hi = uint32_t(p->seed >> 32);
+    G.one = 1.0f;
+    return LB_OK;
+}
+
+// Planes per block of the marching kernels (lbm_march.hip), or 0 where the kernels of one node per thread are
+// faster.  A launch takes as many rounds as its blocks fill the chip; a round costs the block's planes and two
+// repeated ones; the planes per block are chosen for the fewest.  Time of one plane of a block, measured: 8.4 us for
+// whole planes of up to 1024 nodes, 5.9 up to 576, 5.3 up to 256 (three blocks per compute unit), 4.8 for a cut of
+// 64 x 8 nodes with rim; half of it with moment storage (2.7 cut).  The other kernels: 4 us and 40 nodes per ns, by
+// their tiles' lanes for whole planes, 1.3 times as long where the rows of small boxes do not fill cache lines.
+// (us per step, other kernels -> two FP32 steps per launch: 512 boxes of 32^3 404 -> 260, of 24^3 323 -> 146, of 16^3
+// 65.5 -> 49.5, 200 of 25 x 30 x 20 157 -> 82; 128^3 with 149 points 55.8 -> 43.9, 256^3 with 1000 439 -> 321; left
+// alone: 64^3 9.0 / 10.6, 96^3 25 / 32, one box of 32^3 4.3 / 9.0.  Moment storage without points: 128^3
+// 53.5 -> 46, 256^3 415 -> 307, 512 boxes of 32^3 495 -> 277, of 16^3 112 -> 50; left alone: 192^3 177 / 182.)
+int choose_march(const lb_params* p, const Geom& G, double& plane_blocks)
+{
+    const bool fp32 = p->storage == LB_STORAGE_FP32 && p->collision == LB_COLLISION_PROJECTED && !(p->kT > 0.0);
+    const bool mom = p->storage == LB_STORAGE_MOM32;
+    const double nodes = double(G.N) * G.nboxes;
+    // (a plane is addressed with 32-bit byte offsets; lattices near the memory's size have no room for the force field)
+    if (!(fp32 || mom) || double(G.ny) * G.rb * 4.0 >= 4.0e9 || double(p->max_points) * 1024.0 > nodes || nodes > 1.5e9) return 0;
+    const bool whole = march_whole(G.nx, G.ny);
+    const int plane = G.nx * G.ny;
+    const double cols = whole ? 1.0 : double((G.nx + 63) / 64) * ((G.ny + 7) / 8);
+    const double slots = whole && plane <= 256 ? 768 : 256;
+    const double unit = whole ? (plane > 576 ? 8.4 : plane > 256 ? 5.9 : 5.3) * (mom ? 0.5 : 1.0) : mom ? 2.7 : 4.8;
+    int best = 0;
+    double t = 0;
+    for (int n = 1; n <= (G.nz + 3) / 4; ++n) {
+        const int zc = (G.nz + n - 1) / n;
+        const double blocks = cols * ((G.nz + zc - 1) / zc) * G.nboxes, cost = ceil(blocks / slots) * (zc + 2) * unit;
+        if (blocks < 2.0e9 && (best == 0 || cost < t)) {
+            best = zc;
+            t = cost;
+        }
+    }
+    const bool rows = (long long)G.nx * 4 % 128 == 0;
+    const double lanes = whole ? double(G.ntiles) * BLOCK * (rows ? 1.0 : 1.3) : nodes;
+    const double other = (4.0 + lanes / 40.0e3) * (mom ? 1.0 : 2.0);
+    plane_blocks = cols * G.nz * G.nboxes;
+    return best > 0 && t < 0.93 * other ? best : 0;
+}
+
 int make_plan(const lb_params* p, Plan& P, std::string& why)
 {
     if (!p) { why = "params is NULL"; return LB_ERR_ARG; }
@@ -191,68 +298,19 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
         tx = P.plain[0]; ty = P.plain[1]; tz = P.plain[2];
     }
     if (!tile_supported(tx, ty, tz)) { why = "unsupported tile shape"; return LB_ERR_ARG; }
-    Geom& G = P.G;
-    memset(&G, 0, sizeof(G));
-    G.nx = p->nx; G.ny = p->ny; G.nz = p->nz; G.nboxes = p->nboxes;
-    G.tx = tx; G.ty = ty; G.tz = tz;
-    G.ltx = __builtin_ctz(tx); G.lty = __builtin_ctz(ty); G.ltz = __builtin_ctz(tz);
-    G.ntx = (p->nx + tx - 1) / tx;
-    G.nty = (p->ny + ty - 1) / ty;
-    G.ntz = (p->nz + tz - 1) / tz;
-    set_div_magic(G.ntx, G.mtx, G.stx);
-    set_div_magic(G.nty, G.mty, G.sty);
-    set_div_magic(G.ntz, G.mtz, G.stz);
-    G.N = (long long)p->nx * p->ny * p->nz;
-    G.kp = p->nx;
-    G.rb = (long long)planes_of(p->storage) * p->nx;
-    G.sbox = ((long long)p->ny * p->nz * G.rb + 255) / 256 * 256 + 64;
-    {
-        // lanes along x of one tile row: a wave on one row addresses each row block from
-        // its own descriptor; narrower rows of lanes address the box from one descriptor
-        // with 32-bit offsets
-        const bool pairs = p->storage == LB_STORAGE_FP16 && p->nx % 2 == 0 && !((P.variant >> 5) & 1);
-        const int lanes_x = pairs ? tx / 2 : tx;
-        if (lanes_x < 64 && (unsigned long long)G.sbox * storage_bytes(p->storage) >= (1ULL << 32)) {
-            why = "tiles with fewer than 64 lanes along x (64 nodes, or 128 with two FP16 nodes per lane) need a "
-                  "box of under 4 GiB";
-            return LB_ERR_ARG;
-        }
-        // two FP16 nodes per lane on whole-wave rows address each z plane of rows from one descriptor
-        if (pairs && lanes_x >= 64 && (unsigned long long)p->ny * G.rb * storage_bytes(p->storage) >= (1ULL << 32)) {
-            why = "two FP16 nodes per lane need a z plane (ny * nx nodes) of under 4 GiB";
-            return LB_ERR_SIZE;
-        }
-    }
-    G.tiles_per_box = (long long)G.ntx * G.nty * G.ntz;
-    G.ntiles = G.tiles_per_box * p->nboxes;
-    G.rho0 = p->rho0 > 0.0 ? p->rho0 : 1.0;
-    G.maxp = max_axis_tiles(p->nx, tx) * max_axis_tiles(p->ny, ty) * max_axis_tiles(p->nz, tz);
-    if (G.ntiles >= (1LL << 31) - 1) { why = "too many tiles"; return LB_ERR_SIZE; }
     P.cap = p->max_points;
-    if (P.cap * G.maxp >= (1LL << 31) - 1 || P.cap >= (1LL << (31 - PK_SHIFT))) {
-        why = "max_points too large";
-        return LB_ERR_SIZE;
-    }
-    if (G.maxp > (1 << PK_BITS)) { why = "tile too small for the stencil"; return LB_ERR_ARG; }
-    G.bchunks = int(std::min<long long>(256, (G.tiles_per_box + 255) / 256));
-    G.tpb = 1 << ((P.variant >> 2) & 3);
-    G.order = (P.variant >> 4) & 1;
-    G.lgrp = 0;
-    if ((P.variant >> 6) & 1) {
-        // the runs of one tile row on one XCD: needs a power-of-two count of whole runs per row
-        // (otherwise launch order)
-        G.order = 1;
-        if (G.ntx % G.tpb == 0 && ((G.ntx / G.tpb) & (G.ntx / G.tpb - 1)) == 0) {
-            G.order = 2;
-            G.lgrp = __builtin_ctz(unsigned(G.ntx / G.tpb));
-        }
-    }
-    G.pairs = p->storage == LB_STORAGE_FP16 && p->nx % 2 == 0 && !((P.variant >> 5) & 1);
-    G.coll = p->kT > 0.0 ? 2 : (p->collision != LB_COLLISION_PROJECTED ? 1 : 0);
-    G.seed_lo = uint32_t(p->seed);
-    G.seed_hi = uint32_t(p->seed >> 32);
-    G.one = 1.0f;
-    P.chunks = G.bchunks;
+    if (int r = fill_geometry(p, P.variant, P.cap, tx, ty, tz, P.Gp, why)) return r;
+    P.march = p->tile_x == 0 && p->variant == 0 ? choose_march(p, P.Gp, P.march_blocks) : 0;
+    std::string none;
+    int mx, my;
+    march_tile(p->nx, p->ny, mx, my);
+    if (P.march > 0 && fill_geometry(p, P.variant, P.cap, mx, my, 1, P.Gm, none)) P.march = 0;
+    if (P.march == 0) P.Gm = P.Gp;
+    P.G = P.Gp;
+    const Geom& G = P.Gp;
+    const long long ntiles = std::max(P.Gp.ntiles, P.Gm.ntiles);     // the lists serve both geometries
+    const long long maxp = std::max(P.Gp.maxp, P.Gm.maxp);
+    P.chunks = std::max(P.Gp.bchunks, P.Gm.bchunks);
     Layout& L = P.L;
     size_t o = 0;
     auto take = [&](size_t bytes) { const size_t at = o; o = align_up(o + std::max<size_t>(bytes, 1)); return at; };
@@ -262,16 +320,16 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     L.boxes = take(sizeof(BoxDev) * p->nboxes);
     L.rec = take(rec_bytes(p->storage) * P.cap);
     L.psum = take(sizeof(double) * 3 * (prep_blocks(P.cap) + LB_MAX_SETS));
-    L.count = take(sizeof(int) * G.ntiles);
-    L.cursor = take(sizeof(int) * G.ntiles);
-    L.toff = take(sizeof(int) * (G.ntiles + 1));
-    L.bsum = take(sizeof(int) * scan_blocks(G.ntiles));
-    L.tlist = take(sizeof(int) * P.cap * G.maxp);
-    L.tlist_tmp = take(sizeof(int) * P.cap * G.maxp);
-    L.partial = take(sizeof(double) * 3 * P.cap * G.maxp);
+    L.count = take(sizeof(int) * ntiles);
+    L.cursor = take(sizeof(int) * ntiles);
+    L.toff = take(sizeof(int) * (ntiles + 1));
+    L.bsum = take(sizeof(int) * scan_blocks(ntiles));
+    L.tlist = take(sizeof(int) * P.cap * maxp);
+    L.tlist_tmp = take(sizeof(int) * P.cap * maxp);
+    L.partial = take(sizeof(double) * 3 * P.cap * maxp);
     L.fpart = take(sizeof(double) * 3 * p->nboxes * P.chunks);
     L.pmax = take(sizeof(float) * p->nboxes * P.chunks);
-    L.tmax = take(sizeof(float) * G.ntiles);
+    L.tmax = take(sizeof(float) * ntiles);
     L.smax = take(sizeof(unsigned) * SMAX_SLOTS * SMAX_STRIDE);
     L.ticket = take(sizeof(unsigned) * p->nboxes);
     L.tctr = take(2 * sizeof(unsigned long long));
@@ -280,8 +338,11 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     L.rebin = take(sizeof(int));
     L.rebox = take(sizeof(int) * p->nboxes);
     L.win = take(sizeof(int4) * P.cap);
-    L.diag = take(sizeof(double) * LBD_N * G.ntiles);
+    L.diag = take(sizeof(double) * LBD_N * ntiles);
     L.diagout = take(sizeof(double) * LBD_N * p->nboxes);
+    // the fixed points' force density, for the two-step kernel of cut planes
+    const bool field = P.march > 0 && p->storage == LB_STORAGE_FP32 && P.cap > 0 && !march_whole(p->nx, p->ny);
+    L.field = take(field ? sizeof(float) * 3 * G.N * p->nboxes : 0);
     L.total = o;
     return LB_OK;
 }
@@ -336,6 +397,7 @@ struct lb_ctx {
     unsigned long long binned_gen;   // gen the tile lists were last forced to rebuild for
     bool bins_valid;
     bool gc_valid;   // counter-force sums current for the registered static sets
+    bool field_valid;   // ... and the force field of the two-step kernel
     std::vector<GraphEntry> graphs;
     bool timing;
     std::vector<hipEvent_t> ev;
@@ -371,6 +433,7 @@ struct lb_ctx {
     int4* win() const { return (int4*)(ws + P.L.win); }
     double* diag() const { return (double*)(ws + P.L.diag); }
     double* diagout() const { return (double*)(ws + P.L.diagout); }
+    float* field() const { return (float*)(ws + P.L.field); }
 };
 
 namespace {
@@ -409,6 +472,25 @@ bool has_kind(const lb_ctx* c, int kind)
         if (s.kind == kind) return true;
     return false;
 }
+
+// Whether the marching kernels take the steps of the registered sets: two FP32 steps per launch where no point
+// moves, moment storage with any sets; in both cases with few points per plane of a block (a point is in the
+// lists of five planes and about two of their tiles).  FP32: 4 list entries per plane of a block, where 512 boxes of 32^3
+// with 5900 points still take 300 us a step against 421, and 256^3 with 8000 330 against 448.  Moment storage: the
+// same for whole planes (4096 points in the 512 boxes: 279 against 502); cut ones without points only (128^3
+// with 30: 57 against 56).
+bool marches(const lb_ctx* c)
+{
+    if (c->P.march == 0) return false;
+    const bool fp32 = c->p.storage == LB_STORAGE_FP32;
+    if (fp32 && (has_kind(c, LB_COLLOIDS) || has_kind(c, KIND_ELASTIC))) return false;
+    const double most = march_whole(c->P.Gm.nx, c->P.Gm.ny) ? 4.0 : fp32 ? 4.0 : 0.0;
+    return 11.0 * double(total_points(c)) <= most * c->P.march_blocks;
+}
+
+// The geometry (tiles of the point lists) for the registered sets; called when they change, which also
+// makes the lists be built again.
+void set_geometry(lb_ctx* c) { c->P.G = marches(c) ? c->P.Gm : c->P.Gp; }
 
 // After the sets change, the next list build must run whatever the positions:
 // raise the rebuild flag once per change.  Enqueued eagerly, never into a
@@ -449,6 +531,7 @@ void build_points(lb_ctx* c, hipStream_t s)
     }
     build_lists(c, s);
     c->gc_valid = false;
+    c->field_valid = false;
 }
 
 // per-box work before a step or a read: the counter-force sums (only when the
@@ -500,6 +583,63 @@ bool hands_over(const lb_ctx* c)
     return has_kind(c, LB_COLLOIDS) && !has_kind(c, KIND_ELASTIC) && !has_kind(c, LB_FORCES_NEXT_STEP);
 }
 
+// Whether a set takes its points' velocities from a step: to move them or to hand them out.
+bool takes_velocity(const Set& st)
+{
+    return st.kind == LB_COLLOIDS || st.kind == KIND_ELASTIC ||
+           (st.has_model && (st.model.d_vel_out || st.model.d_vel_sum));
+}
+
+bool wants_velocity(const lb_ctx* c)
+{
+    for (auto& st : c->sets)
+        if (takes_velocity(st)) return true;
+    return false;
+}
+
+// Outputs and moves of the sets' points from a step's interpolation partials; before and fp16_exp as in
+// enqueue_step.
+void move_points(lb_ctx* c, hipStream_t s, void* partial, const unsigned long long* tin, bool before, bool fp16_exp)
+{
+    const Geom& G = c->P.G;
+    long long off = 0;
+    for (auto& st : c->sets) {
+        const bool adv = st.kind == LB_COLLOIDS || st.kind == KIND_ELASTIC;
+        if (takes_velocity(st)) {
+            AdvectLaunch a;
+            memset(&a, 0, sizeof(a));
+            a.n = st.n;
+            a.off = off;
+            a.frc = st.frc;
+            a.pos = (double*)st.pos;
+            a.boxid = st.box;
+            a.advect = adv ? 1 : 0;
+            a.tin = st.kind == LB_COLLOIDS ? tin : nullptr;   // markers of curves and surfaces: no zeta'
+
+            if (st.has_model) {
+                a.vel_out = st.model.d_vel_out;
+                a.vel_sum = st.model.d_vel_sum;
+                a.inv_a = st.model.inv_a;
+                a.inv_aL = st.model.inv_aL;
+                a.mlp = st.model.d_mlp;
+                for (int k = 0; k < 4; ++k) {
+                    a.in_shift[k] = st.model.in_shift[k];
+                    a.in_scale[k] = st.model.in_scale[k];
+                }
+                a.out_scale = st.model.out_scale;
+            }
+            if (before && st.kind == LB_COLLOIDS) {
+                a.rec = c->rec();
+                a.err = c->errw();
+                a.fp16_exp = fp16_exp ? 1 : 0;
+                fp16_exp = false;
+            }
+            launch_advect(c->p.storage, G, a, c->boxes(), partial, s);
+        }
+        off += st.n;
+    }
+}
+
 // one step on stream s; flips c->cur.  after: the step before it in this call handed over; before: this
 // one hands over to another
 void enqueue_step(lb_ctx* c, hipStream_t s, bool rebuild, bool after = false, bool before = false)
@@ -529,51 +669,38 @@ void enqueue_step(lb_ctx* c, hipStream_t s, bool rebuild, bool after = false, bo
     }
     unsigned long long* tin = G.coll == 2 ? c->tctr() + c->cur : nullptr;
     unsigned long long* tout = G.coll == 2 ? c->tctr() + (c->cur ^ 1) : nullptr;
-    launch_lattice(c->p.storage, G, 0, c->P.variant, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(),
-                   npts > 0 ? c->toff() : nullptr, c->tlist(), c->rec(), c->partial(), (double*)c->tmax(), tin, tout,
-                   s, e0, e1);
-    long long off = 0;
-    for (auto& st : c->sets) {
-        const bool adv = st.kind == LB_COLLOIDS || st.kind == KIND_ELASTIC;
-        const bool outs = st.has_model && (st.model.d_vel_out || st.model.d_vel_sum);
-        if (adv || outs) {
-            AdvectLaunch a;
-            memset(&a, 0, sizeof(a));
-            a.n = st.n;
-            a.off = off;
-            a.frc = st.frc;
-            a.pos = (double*)st.pos;
-            a.boxid = st.box;
-            a.advect = adv ? 1 : 0;
-            a.tin = st.kind == LB_COLLOIDS ? tin : nullptr;   // markers of curves and surfaces: no zeta'
-
-            if (st.has_model) {
-                a.vel_out = st.model.d_vel_out;
-                a.vel_sum = st.model.d_vel_sum;
-                a.inv_a = st.model.inv_a;
-                a.inv_aL = st.model.inv_aL;
-                a.mlp = st.model.d_mlp;
-                for (int k = 0; k < 4; ++k) {
-                    a.in_shift[k] = st.model.in_shift[k];
-                    a.in_scale[k] = st.model.in_scale[k];
-                }
-                a.out_scale = st.model.out_scale;
-            }
-            if (before && st.kind == LB_COLLOIDS) {
-                a.rec = c->rec();
-                a.err = c->errw();
-                a.fp16_exp = fp16_exp ? 1 : 0;
-                fp16_exp = false;
-            }
-            launch_advect(c->p.storage, G, a, c->boxes(), c->partial(), s);
-        }
-        off += st.n;
-    }
+    const int* toff = npts > 0 ? c->toff() : nullptr;
+    if (c->p.storage == LB_STORAGE_MOM32 && marches(c))
+        launch_march(c->p.storage, G, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->tlist(), c->rec(),
+                     nullptr, wants_velocity(c) ? c->partial() : nullptr, nullptr, s, e0, e1);
+    else
+        launch_lattice(c->p.storage, G, 0, c->P.variant, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->tlist(),
+                       c->rec(), c->partial(), (double*)c->tmax(), tin, tout, s, e0, e1);
+    move_points(c, s, c->partial(), tin, before, fp16_exp);
     c->cur ^= 1;
 }
 
+// n steps.  FP32 runs that the marching kernel takes go two steps a launch, by fours, so that calls end on the
+// population copy they always ended on (which captured graphs, the caller's too, rely on).
 void enqueue_steps(lb_ctx* c, hipStream_t s, bool rebuild, int n)
 {
+    if (c->p.storage == LB_STORAGE_FP32 && !c->timing && marches(c)) {
+        // the partials of the second step behind those of the first (the workspace holds FP64's)
+        const int* toff = total_points(c) > 0 ? c->toff() : nullptr;
+        float* p0 = wants_velocity(c) ? (float*)c->partial() : nullptr;
+        float* p1 = p0 ? p0 + 3 * c->P.cap * c->P.G.maxp : nullptr;
+        for (int pairs = n / 4 * 2; pairs > 0; --pairs) {
+            box_update(c, s, true);
+            launch_march(c->p.storage, c->P.G, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->tlist(),
+                         c->rec(), c->field(), p0, p1, s);
+            if (p0) {
+                move_points(c, s, p0, nullptr, false, false);
+                move_points(c, s, p1, nullptr, false, false);
+            }
+            c->cur ^= 1;
+        }
+        n %= 4;
+    }
     const bool over = rebuild && hands_over(c);
     for (int k = 0; k < n; ++k) enqueue_step(c, s, rebuild, over && k > 0, over && k + 1 < n);
 }
@@ -665,11 +792,14 @@ int lb_init(const lb_params* p, void* d_workspace, size_t bytes, void* hip_strea
     c->p.tau_bulk = nullptr;   // read below, not kept
     c->P = P;
     c->ws = (char*)d_workspace;
-    c->P.G.nf = c->nf();
-    c->P.G.rebin = c->rebin();
-    c->P.G.rebox = c->rebox();
-    c->P.G.win = c->win();
-    c->P.G.smax = (p->storage == LB_STORAGE_FP16 && p->nboxes == 1) ? c->smax() : nullptr;
+    for (Geom* g : {&c->P.Gp, &c->P.Gm}) {
+        g->nf = c->nf();
+        g->rebin = c->rebin();
+        g->rebox = c->rebox();
+        g->win = c->win();
+        g->smax = (p->storage == LB_STORAGE_FP16 && p->nboxes == 1) ? c->smax() : nullptr;
+    }
+    set_geometry(c);
     c->stream = (hipStream_t)hip_stream;
     c->cap_stream = nullptr;
     c->cur = 0;
@@ -677,6 +807,7 @@ int lb_init(const lb_params* p, void* d_workspace, size_t bytes, void* hip_strea
     c->binned_gen = 0;
     c->bins_valid = false;
     c->gc_valid = false;
+    c->field_valid = false;
     c->timing = false;
     c->ev_used = 0;
     c->timed_ms = 0.0;
@@ -721,12 +852,13 @@ int lb_init(const lb_params* p, void* d_workspace, size_t bytes, void* hip_strea
     const size_t popb = (size_t)G.sbox * p->nboxes * storage_bytes(p->storage);
     launch_fill_u32(c->pop(0), (long long)(popb / 4), 0u, s);
     launch_fill_u32(c->pop(1), (long long)(popb / 4), 0u, s);
-    launch_fill_u32(c->count(), G.ntiles, 0u, s);
-    launch_fill_u32(c->cursor(), G.ntiles, 0u, s);
-    launch_fill_u32(c->toff(), G.ntiles + 1, 0u, s);
+    const long long ntiles = std::max(c->P.Gp.ntiles, c->P.Gm.ntiles);
+    launch_fill_u32(c->count(), ntiles, 0u, s);
+    launch_fill_u32(c->cursor(), ntiles, 0u, s);
+    launch_fill_u32(c->toff(), ntiles + 1, 0u, s);
     launch_fill_u32(c->ticket(), p->nboxes, 0u, s);
     launch_fill_u32(c->tctr(), 4, 0u, s);
-    launch_fill_u32(c->tmax(), G.ntiles, 0u, s);
+    launch_fill_u32(c->tmax(), ntiles, 0u, s);
     launch_fill_u32(c->smax(), SMAX_SLOTS * SMAX_STRIDE, 0u, s);
     launch_fill_u32(c->errw(), 4, 0u, s);
     launch_fill_u32(c->nf(), p->nboxes, 0u, s);
@@ -789,9 +921,11 @@ int lb_add_point_forces(lb_ctx* c, int64_t n, const double* d_pos, const double*
     else
         memset(&s.model, 0, sizeof(s.model));
     c->sets.push_back(s);
+    set_geometry(c);
     c->gen++;
     c->bins_valid = false;
     c->gc_valid = false;
+    c->field_valid = false;
     return LB_OK;
 }
 
@@ -825,9 +959,11 @@ int lb_add_elastic(lb_ctx* c, const lb_elastic* e)
     s.has_model = true;   // inv_a = inv_aL = 0: the markers move with U alone
     s.el = *e;
     c->sets.push_back(s);
+    set_geometry(c);
     c->gen++;
     c->bins_valid = false;
     c->gc_valid = false;
+    c->field_valid = false;
     return LB_OK;
 }
 
@@ -835,9 +971,11 @@ int lb_clear_forces(lb_ctx* c)
 {
     if (!c) return LB_ERR_ARG;
     c->sets.clear();
+    set_geometry(c);
     c->gen++;
     c->bins_valid = false;
     c->gc_valid = false;
+    c->field_valid = false;
     return LB_OK;
 }
 
@@ -854,9 +992,11 @@ int lb_step(lb_ctx* c, int32_t nsteps)
         c->sets.erase(std::remove_if(c->sets.begin(), c->sets.end(),
                                      [](const Set& s) { return s.kind == LB_FORCES_NEXT_STEP; }),
                       c->sets.end());
+        set_geometry(c);
         c->gen++;
         c->bins_valid = false;
         c->gc_valid = false;
+        c->field_valid = false;
         c->steps++;
         left--;
         force_rebin(c, c->stream);
@@ -867,7 +1007,15 @@ int lb_step(lb_ctx* c, int32_t nsteps)
         build_points(c, c->stream);
         c->bins_valid = true;
     }
-    if (left > 0 && !moving) box_update(c, c->stream, false);   // static sums outside any captured graph
+    if (left > 0 && !moving) {
+        // static sums and the force field outside any captured graph
+        box_update(c, c->stream, false);
+        if (pts && left >= 4 && c->p.storage == LB_STORAGE_FP32 && !march_whole(c->P.G.nx, c->P.G.ny) && marches(c) &&
+            !c->timing && !c->field_valid) {
+            launch_force_field(c->P.G, c->boxes(), c->toff(), c->tlist(), c->rec(), c->field(), c->stream);
+            c->field_valid = true;
+        }
+    }
     const bool rebuild = moving;
     if (c->timing || left < 4) {
         enqueue_steps(c, c->stream, rebuild, left);
@@ -1084,17 +1232,23 @@ int lb_checkpoint_load(lb_ctx* c, const void* src)
     if (!r) r = hip_check(c, hipMemcpy(&h, src, sizeof(h), hipMemcpyDefault), "checkpoint header");
     if (r) return r;
     if (memcmp(h.magic, CKPT_MAGIC, 8) != 0) return fail(c, LB_ERR_ARG, "not a checkpoint");
-    // the context's own tile, or plain_tile's where the caller named none (only the per-tile maxima depend on
+    // the tile in use, or another one that contexts of these parameters have used (only the per-tile maxima depend on
     // the tile, and those matter for batches of FP16 boxes alone, whose default is the plain tile)
     const Geom& G = c->P.G;
     const int* q = c->P.plain;
+    const int tiles[4][3] = {{G.tx, G.ty, G.tz}, {c->P.Gp.tx, c->P.Gp.ty, c->P.Gp.tz}, {c->P.Gm.tx, c->P.Gm.ty, c->P.Gm.tz},
+                             {q[0], q[1], q[2]}};
     const bool same = h.tx == G.tx && h.ty == G.ty && h.tz == G.tz;
-    const bool plain = h.tx == q[0] && h.ty == q[1] && h.tz == q[2];
-    CkptHeader want = ckpt_layout(c, same || !plain ? G.ntiles
-                                     : (int64_t)((G.nx + q[0] - 1) / q[0]) * ((G.ny + q[1] - 1) / q[1]) *
-                                           ((G.nz + q[2] - 1) / q[2]) * G.nboxes);
+    CkptHeader want = ckpt_layout(c, G.ntiles);
+    bool known = false;
+    for (auto& t : tiles)
+        if (!known && h.tx == t[0] && h.ty == t[1] && h.tz == t[2]) {
+            known = true;
+            want = ckpt_layout(c, (int64_t)((G.nx + t[0] - 1) / t[0]) * ((G.ny + t[1] - 1) / t[1]) *
+                                      ((G.nz + t[2] - 1) / t[2]) * G.nboxes);
+        }
     if (h.nx != want.nx || h.ny != want.ny || h.nz != want.nz || h.nboxes != want.nboxes ||
-        h.storage != want.storage || h.collision != want.collision || !(same || plain) || h.tiles != want.tiles ||
+        h.storage != want.storage || h.collision != want.collision || !known || h.tiles != want.tiles ||
         h.npoints != want.npoints || h.total != want.total)
         return fail(c, LB_ERR_ARG, "checkpoint of another lattice, tiling or point count");
     const char* d = (const char*)src;
@@ -1117,6 +1271,7 @@ int lb_checkpoint_load(lb_ctx* c, const void* src)
     c->binned_gen = c->gen;
     c->bins_valid = false;
     c->gc_valid = false;
+    c->field_valid = false;
     c->steps = h.steps;
     return check_async(c);
 }

@@ -48,6 +48,15 @@ bool launch_lattice(int storage, const Geom& G, int mode, int variant, const voi
                     const int* toff, const int* tlist, const void* rec, double* out0, double* out1,
                     const unsigned long long* tin, unsigned long long* tout, hipStream_t s, hipEvent_t ev0 = nullptr,
                     hipEvent_t ev1 = nullptr);
+// marching step kernels: one step of moment storage, two steps of FP32 populations with fixed points or
+// none; zc planes per block.  march_whole: planes are taken whole; march_tile: tx x ty x 1 tiles of the point lists
+bool march_whole(int nx, int ny);
+void march_tile(int nx, int ny, int& tx, int& ty);
+void launch_march(int storage, const Geom& G, int zc, const void* src, void* dst, const BoxDev* boxes, const int* toff,
+                  const int* tlist, const void* rec, const float* field, void* part0, void* part1, hipStream_t s,
+                  hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+void launch_force_field(const Geom& G, const BoxDev* boxes, const int* toff, const int* tlist, const void* rec, float* field,
+                        hipStream_t s);
 void launch_equilibrium(int storage, const Geom& G, void* dst, const BoxDev* boxes, const double* rho,
                         const double* u, hipStream_t s);
 

@@ -25,6 +25,7 @@
 
 #include <hip/hip_ext.h>
 
+#include "lbm_collide.h"
 #include "lbm_device.h"
 #include "lbm_internal.h"
 #include "lbm_noise.h"
@@ -52,6 +53,7 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
 {
     using S = typename StoreT<ST>::S;
     using T = typename StoreT<ST>::T;
+    constexpr bool SHARED = MODE == M_STEP && (ST == ST_FP32 || ST == ST_FP64) && COLL == 0;   // lbm_collide.h's collision
     static_assert(TX * TY * TZ == BLOCK, "tiles of BLOCK nodes");
     // NPL = 2: each lane takes the two adjacent nodes x, x + 1 (FP16 storage, nx even),
     // half as many threads per tile
@@ -233,37 +235,30 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
             pxz *= u;
             pyz *= u;
         } else {
-            drho = f[0];
-            bool s_jx = false, s_jy = false, s_jz = false, s_pxx = false, s_pyy = false, s_pzz = false,
-                 s_pxy = false, s_pxz = false, s_pyz = false;
-#pragma unroll
-            for (int i = 1; i < NQ; i += 2) {
-                const T sm = f[i] + f[i + 1], df = f[i] - f[i + 1];
-                const int cx = cvel(i, 0), cy = cvel(i, 1), cz = cvel(i, 2);
-                drho += sm;
-                if (cx != 0) { acc_first(jx, s_jx, cx > 0 ? df : -df); acc_first(pxx, s_pxx, sm); }
-                if (cy != 0) { acc_first(jy, s_jy, cy > 0 ? df : -df); acc_first(pyy, s_pyy, sm); }
-                if (cz != 0) { acc_first(jz, s_jz, cz > 0 ? df : -df); acc_first(pzz, s_pzz, sm); }
-                if (cx * cy != 0) acc_first(pxy, s_pxy, cx * cy > 0 ? sm : -sm);
-                if (cx * cz != 0) acc_first(pxz, s_pxz, cx * cz > 0 ? sm : -sm);
-                if (cy * cz != 0) acc_first(pyz, s_pyz, cy * cz > 0 ? sm : -sm);
-            }
+            const Node<T> m = moments_of(f);
+            drho = m.drho;
+            jx = m.jx; jy = m.jy; jz = m.jz;
+            pxx = m.pxx; pyy = m.pyy; pzz = m.pzz;
+            pxy = m.pxy; pxz = m.pxz; pyz = m.pyz;
         }
 
         // ---- force density at this node: counter-force + the tile's points
+        // (where no other kernel shares the collision, the compiler fuses the sums, also into those below)
         T gx = gcx, gy = gcy, gz = gcz;
         auto spread = [&](const PRec<T>& r) {
-            // rows the point's stencil misses take nothing from it: skip them (a branch taken by
-            // whole waves when y and z are wave-uniform; otherwise waves whose lanes all miss skip it)
-            int dy = y - r.by, dz = z - r.bz;
-            if (dy < 0) dy += G.ny;
-            if (dz < 0) dz += G.nz;
-            if (dy > 3 || dz > 3) return;
-            const T w = stencil_w<T>(xh, r.bx, G.nx, r.wx) * stencil_w<T>(y, r.by, G.ny, r.wy) *
-                        stencil_w<T>(z, r.bz, G.nz, r.wz);
-            gx += r.f[0] * w;
-            gy += r.f[1] * w;
-            gz += r.f[2] * w;
+            if constexpr (SHARED) {
+                add_point(G, r, xh, y, z, gx, gy, gz);
+            } else {
+                int dy = y - r.by, dz = z - r.bz;
+                if (dy < 0) dy += G.ny;
+                if (dz < 0) dz += G.nz;
+                if (dy > 3 || dz > 3) return;
+                const T w = stencil_w<T>(xh, r.bx, G.nx, r.wx) * stencil_w<T>(y, r.by, G.ny, r.wy) *
+                            stencil_w<T>(z, r.bz, G.nz, r.wz);
+                gx += r.f[0] * w;
+                gy += r.f[1] * w;
+                gz += r.f[2] * w;
+            }
         };
         if (!STAGE && h == 0) entries();
         if (staged) {
@@ -339,6 +334,29 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
                 out0[(long long)tile * LBD_N + c] = a;
             }
             return;
+        }
+
+        // ---- M_STEP, FP32 or FP64 populations and projected operator: the collision that the two-step kernel shares
+        if constexpr (SHARED) {
+            const Node<T> m{drho, jx, jy, jz, pxx, pyy, pzz, pxy, pxz, pyz};
+            const T g[3] = {gx, gy, gz};
+            T p[MP_N], u[3];
+            pieces_of<0>(m, g, rates_of<0, T>(G, B), p, u);
+            bad = bad || (valid && !finite_node(m, g));
+            if (valid) {
+                store_pop<S, ADDR>(S(T(wgt(0)) * p[MP_R0]), db, G.rb, G.kp, box_bytes, 0, row, x);
+#pragma unroll
+                for (int i = 1; i < NQ; i += 2) {
+                    T bp, bm;
+                    rebuild_pair(p, i, bp, bm);
+                    store_pop<S, ADDR>(S(T(wgt(i)) * bp), db, G.rb, G.kp, box_bytes, i, row, x);
+                    store_pop<S, ADDR>(S(T(wgt(i)) * bm), db, G.rb, G.kp, box_bytes, i + 1, row, x);
+                }
+            }
+            uxs[h] = u[0];
+            uys[h] = u[1];
+            uzs[h] = u[2];
+            continue;
         }
 
         // ---- M_STEP: collide
@@ -810,6 +828,11 @@ static bool launch_lattice_s(const Geom& G, int mode, int variant, const void* s
     LBM_TILE(128, 2, 1)
     LBM_TILE(128, 1, 2)
     LBM_TILE(256, 1, 1)
+    if constexpr (ST == ST_FP32 || ST == ST_MOM32) {
+        // point lists of the marching kernels (march_tile): one z plane of a narrow box
+        LBM_TILE(32, 8, 1)
+        LBM_TILE(16, 16, 1)
+    }
 #undef LBM_TILE
     return false;
 }
