@@ -216,13 +216,13 @@ int fill_geometry(const lb_params* p, int variant, long long cap, int tx, int ty
 // Planes per block of the marching kernels (lbm_march.hip), or 0 where the kernels of one node per thread are
 // faster.  A launch takes as many rounds as its blocks fill the chip; a round costs the block's planes and two
 // repeated ones; the planes per block are chosen for the fewest.  Time of one plane of a block, measured: 8.4 us for
-// whole planes of up to 1024 nodes, 5.9 up to 576, 5.3 up to 256 (three blocks per compute unit), 4.8 for a cut of
-// 64 x 8 nodes with rim; half of it with moment storage (2.7 cut).  The other kernels: 4 us and 40 nodes per ns, by
+// whole planes of up to 1024 nodes, 5.9 up to 576, 5.3 up to 256 (three blocks per compute unit), 4.3 for a cut of
+// 64 x 8 nodes with rim; half of it with moment storage.  The other kernels: 4 us and 40 nodes per ns, by
 // their tiles' lanes for whole planes, 1.3 times as long where the rows of small boxes do not fill cache lines.
 // (us per step, other kernels -> two FP32 steps per launch: 512 boxes of 32^3 404 -> 260, of 24^3 323 -> 146, of 16^3
-// 65.5 -> 49.5, 200 of 25 x 30 x 20 157 -> 82; 128^3 with 149 points 55.8 -> 43.9, 256^3 with 1000 439 -> 321; left
+// 65.5 -> 49.5, 200 of 25 x 30 x 20 157 -> 82; 128^3 with 149 points 55.8 -> 43.9, 256^3 with 1000 439 -> 293; left
 // alone: 64^3 9.0 / 10.6, 96^3 25 / 32, one box of 32^3 4.3 / 9.0.  Moment storage without points: 128^3
-// 53.5 -> 46, 256^3 415 -> 307, 512 boxes of 32^3 495 -> 277, of 16^3 112 -> 50; left alone: 192^3 177 / 182.)
+// 53.5 -> 40, 256^3 415 -> 258, 512 boxes of 32^3 495 -> 277, of 16^3 112 -> 50.)
 int choose_march(const lb_params* p, const Geom& G, double& plane_blocks)
 {
     const bool fp32 = p->storage == LB_STORAGE_FP32 && p->collision == LB_COLLISION_PROJECTED && !(p->kT > 0.0);
@@ -234,7 +234,7 @@ int choose_march(const lb_params* p, const Geom& G, double& plane_blocks)
     const int plane = G.nx * G.ny;
     const double cols = whole ? 1.0 : double((G.nx + 63) / 64) * ((G.ny + 7) / 8);
     const double slots = whole && plane <= 256 ? 768 : 256;
-    const double unit = whole ? (plane > 576 ? 8.4 : plane > 256 ? 5.9 : 5.3) * (mom ? 0.5 : 1.0) : mom ? 2.7 : 4.8;
+    const double unit = whole ? (plane > 576 ? 8.4 : plane > 256 ? 5.9 : 5.3) * (mom ? 0.5 : 1.0) : mom ? 2.1 : 4.3;
     int best = 0;
     double t = 0;
     for (int n = 1; n <= (G.nz + 3) / 4; ++n) {
@@ -476,7 +476,7 @@ bool has_kind(const lb_ctx* c, int kind)
 // Whether the marching kernels take the steps of the registered sets: two FP32 steps per launch where no point
 // moves, moment storage with any sets; in both cases with few points per plane of a block (a point is in the
 // lists of five planes and about two of their tiles).  FP32: 4 list entries per plane of a block, where 512 boxes of 32^3
-// with 5900 points still take 300 us a step against 421, and 256^3 with 8000 330 against 448.  Moment storage: the
+// with 5900 points still take 300 us a step against 421, and 256^3 with 8000 294 against 448.  Moment storage: the
 // same for whole planes (4096 points in the 512 boxes: 279 against 502); cut ones without points only (128^3
 // with 30: 57 against 56).
 bool marches(const lb_ctx* c)

@@ -16,16 +16,19 @@
 //
 // Planes of at most 1024 nodes are taken whole (the column's neighbours wrap round inside the block); larger
 // ones are cut into MX x MY output nodes with a rim of one node, whose first step is repeated by
-// every block that shares it (29 % more of it).  A block makes zc planes and repeats one below and above.
+// every block that shares it (29 % more of it).  A block makes zc planes and repeats one below and above.  The inner
+// nodes of a cut row are one wave's, the two outer columns the last wave's: loads start on a cache line, and
+// the waves of the rim skip the second half (256^3: 297 -> 268 us a step, moment storage 307 -> 258, against threads
+// in the order of the 66 x 10 nodes; cuts of 32 x 8 or 32 x 16, two blocks per compute unit, 387 and 430).
 //
 // What bounds it: the two barriers a plane and the arithmetic between them, with one block of 11 or 16 waves per compute
 // unit (42 KB of LDS for the populations, 24 B a node for velocities, 128 registers); the memory side is at half
-// the copy rate (256^3: 297 us a step, 76 B a node, 4.3 TB/s; 440 us and 5.8 TB/s one step at a time).
+// the copy rate (256^3: 268 us a step, 76 B a node, 4.8 TB/s; 440 us and 5.8 TB/s one step at a time).
 //
 // Points: the entries of a plane in the point lists are looked up, fetched and staged in LDS over the two planes
 // before it; more than RPT of them at once are fetched in rounds.  Where two steps are taken of cut planes, whose rim
 // touches the lists of twelve tiles, the force density is laid out once as a field instead (launch_force_field) and read
-// with the plane before it where the lists have points near the block (128^3 with 600 points: 60.8 -> 43.4 us a
+// with the plane before it where the lists have points near the block (128^3 with 600 points: 60.8 -> 42.5 us a
 // step; whole planes lose 3 % to the three registers), and only velocities that are wanted need the records.  The
 // interpolation partials are taken after the plane's last barrier, beside the next plane.
 #include <hip/hip_ext.h>
@@ -92,21 +95,26 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
     const int x0 = CUT ? bx * MX : 0, y0 = CUT ? by * MY : 0, z0 = ch * A.zc, nzc = min(A.zc, G.nz - z0);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
 
-    // the thread's column, whether it makes output, and where its neighbours' values lie in LDS
-    const int ne = CUT ? NE : G.nx * G.ny, e = min(tid, ne - 1);
-    int x, y, at = 0;
+    // The thread's column, whether it makes output, and where its values (e) and those of its neighbours lie in LDS.
+    // Of a cut plane each wave takes the inner nodes of one row, so that its loads start on a line, and the last
+    // wave the two outer columns; only the waves of output rows take part in the second half of an iteration.
+    const int ne = CUT ? NE : G.nx * G.ny;
+    int x, y, e = min(tid, ne - 1), at = 0;
     bool out;
     if constexpr (CUT) {
-        const int ex = e % EX, ey = e / EX;
+        const int rim = min(max(tid - MX * EY, 0), 2 * EY - 1);
+        const int ex = tid < MX * EY ? 1 + tid % MX : (rim & 1) * (EX - 1), ey = tid < MX * EY ? tid / MX : rim >> 1;
+        e = ex + EX * ey;
         x = (x0 - 1 + ex + G.nx) % G.nx;
         y = (y0 - 1 + ey + G.ny) % G.ny;
-        out = tid < NE && ex >= 1 && ex <= MX && ey >= 1 && ey <= MY && x0 + ex - 1 < G.nx && y0 + ey - 1 < G.ny;
+        out = tid < MX * EY && ey >= 1 && ey <= MY && x0 + ex - 1 < G.nx && y0 + ey - 1 < G.ny;
         at = min(max(e, EX + 1), NE - EX - 2);     // threads of the rim: some place inside
     } else {
         x = e % G.nx;
         y = e / G.nx;
         out = tid < ne;
     }
+    const bool active = !CUT || __any(out);
     const int xm = x == 0 ? G.nx - 1 : x - 1, xp = x + 1 == G.nx ? 0 : x + 1;
     const int ym = y == 0 ? G.ny - 1 : y - 1, yp = y + 1 == G.ny ? 0 : y + 1;
     auto from = [&](int i) {                       // column x - c_i
@@ -274,9 +282,9 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
     };
     auto keep = [&](float (&v)[3][NE], const float (&u)[3]) {
         if (tid < ne) {
-            v[0][tid] = u[0];
-            v[1][tid] = u[1];
-            v[2][tid] = u[2];
+            v[0][e] = u[0];
+            v[1][e] = u[1];
+            v[2][e] = u[2];
         }
     };
 
@@ -346,50 +354,51 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
             if (tid < ne) {
 #pragma unroll
                 for (int i = 1; i < NQ; ++i)
-                    if (moves(i)) pops[place(i)][tid] = cvel(i, 2) > 0 ? up2[i] : (cvel(i, 2) == 0 ? lev[i] : cur[i]);
+                    if (moves(i)) pops[place(i)][e] = cvel(i, 2) > 0 ? up2[i] : (cvel(i, 2) == 0 ? lev[i] : cur[i]);
             }
             __syncthreads();
-            float f[NQ];
+            if constexpr (KIND == KIND_MOM) spread(b1, l1, t1, z0 + k - 1, g);
+            if (active) {
+                float f[NQ];
 #pragma unroll
-            for (int i = 0; i < NQ; ++i) {
-                if (moves(i))
-                    f[i] = pops[place(i)][from(i)];
-                else
-                    f[i] = cvel(i, 2) > 0 ? up2[i] : (cvel(i, 2) == 0 ? lev[i] : cur[i]);
-            }
-            const int zo = z0 + k - 1;
-            const rsrc_t r = plane_rsrc(db + (unsigned long long)zo * pbytes, pbytes);
-            Node<float> m;
-            float p[MP_N];
-            if constexpr (KIND == KIND_PAIR) {
-                m = moments_of(f);
-                pieces_of<0>(m, gp, R, p, u);
-                if (out) {
-                    bad = bad || !finite_node(m, gp);
-                    bstore<float, 2>(float(wgt(0)) * p[MP_R0], r, own, 0u);
+                for (int i = 0; i < NQ; ++i) {
+                    if (moves(i))
+                        f[i] = pops[place(i)][from(i)];
+                    else
+                        f[i] = cvel(i, 2) > 0 ? up2[i] : (cvel(i, 2) == 0 ? lev[i] : cur[i]);
+                }
+                const rsrc_t r = plane_rsrc(db + (unsigned long long)(z0 + k - 1) * pbytes, pbytes);
+                Node<float> m;
+                float p[MP_N];
+                if constexpr (KIND == KIND_PAIR) {
+                    m = moments_of(f);
+                    pieces_of<0>(m, gp, R, p, u);
+                    if (out) {
+                        bad = bad || !finite_node(m, gp);
+                        bstore<float, 2>(float(wgt(0)) * p[MP_R0], r, own, 0u);
 #pragma unroll
-                    for (int i = 1; i < NQ; i += 2) {
-                        float bp, bm;
-                        rebuild_pair(p, i, bp, bm);
-                        bstore<float, 2>(float(wgt(i)) * bp, r, own, unsigned(i) * kp);
-                        bstore<float, 2>(float(wgt(i)) * bm, r, own, unsigned(i + 1) * kp);
+                        for (int i = 1; i < NQ; i += 2) {
+                            float bp, bm;
+                            rebuild_pair(p, i, bp, bm);
+                            bstore<float, 2>(float(wgt(i)) * bp, r, own, unsigned(i) * kp);
+                            bstore<float, 2>(float(wgt(i)) * bm, r, own, unsigned(i + 1) * kp);
+                        }
+                    }
+                } else {
+                    // f are brackets f*_i / w_i: the weights 12, 2, 1 (times 1/36) go on the sums
+                    float q[NQ];
+#pragma unroll
+                    for (int i = 0; i < NQ; ++i) q[i] = float(wgt(i)) * f[i];
+                    m = moments_of(q);
+                    pieces_of<COLL>(m, g, R, p, u);
+                    if (out) {
+                        bad = bad || !finite_node(m, g);
+#pragma unroll
+                        for (int v = 0; v < MP_N; ++v) bstore<float, 2>(p[v], r, own, unsigned(v) * kp);
                     }
                 }
-            } else {
-                // f are brackets f*_i / w_i: the weights 12, 2, 1 (times 1/36) go on the sums
-                float q[NQ];
-#pragma unroll
-                for (int i = 0; i < NQ; ++i) q[i] = float(wgt(i)) * f[i];
-                m = moments_of(q);
-                spread(b1, l1, t1, zo, g);
-                pieces_of<COLL>(m, g, R, p, u);
-                if (out) {
-                    bad = bad || !finite_node(m, g);
-#pragma unroll
-                    for (int v = 0; v < MP_N; ++v) bstore<float, 2>(p[v], r, own, unsigned(v) * kp);
-                }
+                if ((KIND == KIND_PAIR ? A.part1 : A.part0) && t1 > 0) keep(su[k & 1][NU - 1], u);
             }
-            if ((KIND == KIND_PAIR ? A.part1 : A.part0) && t1 > 0) keep(su[k & 1][NU - 1], u);
         }
         const int bn = 3 - b0 - b1;                // the third buffer
         put(bn, idx, ent, tile, word);
