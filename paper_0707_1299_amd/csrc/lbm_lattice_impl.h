@@ -53,7 +53,7 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
 {
     using S = typename StoreT<ST>::S;
     using T = typename StoreT<ST>::T;
-    constexpr bool SHARED = MODE == M_STEP && (ST == ST_FP32 || ST == ST_FP64) && COLL == 0;   // lbm_collide.h's collision
+    constexpr bool SHARED = MODE == M_STEP && ST == ST_FP32 && COLL == 0;   // the collision of the marching kernels
     static_assert(TX * TY * TZ == BLOCK, "tiles of BLOCK nodes");
     // NPL = 2: each lane takes the two adjacent nodes x, x + 1 (FP16 storage, nx even),
     // half as many threads per tile
@@ -272,7 +272,24 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
                 for (int p = 0; p < n; ++p) spread(srec[p]);
             }
         } else if constexpr (!STAGE || STAGE_MIN > 1) {
-            for (int k = k0; k < k1; ++k) spread(rec[pk_point(tlist[k])]);
+            for (int k = k0; k < k1; ++k) {
+                const PRec<T>& r = rec[pk_point(tlist[k])];
+                if constexpr (SHARED) {
+                    spread(r);
+                } else {
+                    // (spread's lines in the loop itself: through the function the compiler fuses the thermal step's
+                    // sums in another way, a rounding that FP16 storage carries on)
+                    int dy = y - r.by, dz = z - r.bz;
+                    if (dy < 0) dy += G.ny;
+                    if (dz < 0) dz += G.nz;
+                    if (dy > 3 || dz > 3) continue;
+                    const T w = stencil_w<T>(xh, r.bx, G.nx, r.wx) * stencil_w<T>(y, r.by, G.ny, r.wy) *
+                                stencil_w<T>(z, r.bz, G.nz, r.wz);
+                    gx += r.f[0] * w;
+                    gy += r.f[1] * w;
+                    gz += r.f[2] * w;
+                }
+            }
         }
 
         const T rho = rho0 + drho;
@@ -336,7 +353,7 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
             return;
         }
 
-        // ---- M_STEP, FP32 or FP64 populations and projected operator: the collision that the two-step kernel shares
+        // ---- M_STEP, FP32 populations and projected operator: the collision that the two-step kernel shares
         if constexpr (SHARED) {
             const Node<T> m{drho, jx, jy, jz, pxx, pyy, pzz, pxy, pxz, pyz};
             const T g[3] = {gx, gy, gz};
