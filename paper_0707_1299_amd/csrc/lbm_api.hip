@@ -216,25 +216,26 @@ int fill_geometry(const lb_params* p, int variant, long long cap, int tx, int ty
 // Planes per block of the marching kernels (lbm_march.hip), or 0 where the kernels of one node per thread are
 // faster.  A launch takes as many rounds as its blocks fill the chip; a round costs the block's planes and two
 // repeated ones; the planes per block are chosen for the fewest.  Time of one plane of a block, measured: 8.4 us for
-// whole planes of up to 1024 nodes, 5.9 up to 576, 5.3 up to 256 (three blocks per compute unit), 4.3 for a cut of
+// whole planes of up to 1024 nodes, 5.9 up to 576, 5.3 up to 256 (three blocks per compute unit), 4.1 for a cut of
 // 64 x 8 nodes with rim; half of it with moment storage.  The other kernels: 4 us and 40 nodes per ns, by
 // their tiles' lanes for whole planes, 1.3 times as long where the rows of small boxes do not fill cache lines.
-// (us per step, other kernels -> two FP32 steps per launch: 512 boxes of 32^3 404 -> 260, of 24^3 323 -> 146, of 16^3
-// 65.5 -> 49.5, 200 of 25 x 30 x 20 157 -> 82; 128^3 with 149 points 55.8 -> 43.9, 256^3 with 1000 439 -> 293; left
+// (us per step, other kernels -> two FP32 steps per launch: 512 boxes of 32^3 404 -> 255, of 24^3 323 -> 133, of 16^3
+// 65.5 -> 49.5, 200 of 25 x 30 x 20 157 -> 82; 128^3 with 149 points 55.8 -> 43.4, 256^3 with 1000 439 -> 284; left
 // alone: 64^3 9.0 / 10.6, 96^3 25 / 32, one box of 32^3 4.3 / 9.0.  Moment storage without points: 128^3
-// 53.5 -> 40, 256^3 415 -> 258, 512 boxes of 32^3 495 -> 277, of 16^3 112 -> 50.)
+// 53.5 -> 37, 256^3 415 -> 236, 512 boxes of 32^3 495 -> 275, of 16^3 112 -> 50; with a few colloids the estimate
+// is short by a tenth: left alone 250 x 60 x 33 26.2 / 26.9.)
 int choose_march(const lb_params* p, const Geom& G, double& plane_blocks)
 {
     const bool fp32 = p->storage == LB_STORAGE_FP32 && p->collision == LB_COLLISION_PROJECTED && !(p->kT > 0.0);
     const bool mom = p->storage == LB_STORAGE_MOM32;
     const double nodes = double(G.N) * G.nboxes;
-    // (a plane is addressed with 32-bit byte offsets; lattices near the memory's size have no room for the force field)
-    if (!(fp32 || mom) || double(G.ny) * G.rb * 4.0 >= 4.0e9 || double(p->max_points) * 1024.0 > nodes || nodes > 1.5e9) return 0;
+    // (a plane is addressed with 31-bit byte offsets; lattices near the memory's size have no room for the force field)
+    if (!(fp32 || mom) || double(G.ny) * G.rb * 4.0 >= 2.0e9 || double(p->max_points) * 1024.0 > nodes || nodes > 1.5e9) return 0;
     const bool whole = march_whole(G.nx, G.ny);
     const int plane = G.nx * G.ny;
     const double cols = whole ? 1.0 : double((G.nx + 63) / 64) * ((G.ny + 7) / 8);
     const double slots = whole && plane <= 256 ? 768 : 256;
-    const double unit = whole ? (plane > 576 ? 8.4 : plane > 256 ? 5.9 : 5.3) * (mom ? 0.5 : 1.0) : mom ? 2.1 : 4.3;
+    const double unit = whole ? (plane > 576 ? 8.4 : plane > 256 ? 5.9 : 5.3) * (mom ? 0.5 : 1.0) : mom ? 2.0 : 4.1;
     int best = 0;
     double t = 0;
     for (int n = 1; n <= (G.nz + 3) / 4; ++n) {
@@ -249,7 +250,7 @@ int choose_march(const lb_params* p, const Geom& G, double& plane_blocks)
     const double lanes = whole ? double(G.ntiles) * BLOCK * (rows ? 1.0 : 1.3) : nodes;
     const double other = (4.0 + lanes / 40.0e3) * (mom ? 1.0 : 2.0);
     plane_blocks = cols * G.nz * G.nboxes;
-    return best > 0 && t < 0.93 * other ? best : 0;
+    return best > 0 && t < (mom ? 0.85 : 0.93) * other ? best : 0;
 }
 
 int make_plan(const lb_params* p, Plan& P, std::string& why)
@@ -474,18 +475,19 @@ bool has_kind(const lb_ctx* c, int kind)
 }
 
 // Whether the marching kernels take the steps of the registered sets: two FP32 steps per launch where no point
-// moves, moment storage with any sets; in both cases with few points per plane of a block (a point is in the
-// lists of five planes and about two of their tiles).  FP32: 4 list entries per plane of a block, where 512 boxes of 32^3
-// with 5900 points still take 300 us a step against 421, and 256^3 with 8000 294 against 448.  Moment storage: the
-// same for whole planes (4096 points in the 512 boxes: 279 against 502); cut ones without points only (128^3
-// with 30: 57 against 56).
+// moves, moment storage with any sets.  Up to the bound of choose_march they gain with any number of points (one
+// per 1024 nodes, us: FP32 256^3 425 -> 295, 128^3 56.5 -> 41, 512 boxes of 32^3 417 -> 300, moment storage 504 -> 278),
+// except on cut planes with moment storage, where a block whose planes have more points than others' holds up its
+// round: up to 2.5 list entries per plane of a block at 16 planes per compute unit, 4 at 115 and more (a point is
+// in the lists of five planes and about two of their tiles; 128^3 with 500 colloids 65 -> 59, 1000 66 -> 65, 2000 66 / 74;
+// 192^3 with 3000 196 -> 183, 6000 197 / 212; 256^3 with 1000 433 -> 290, 10^4 437 -> 394, 16000 440 / 445).
 bool marches(const lb_ctx* c)
 {
-    if (c->P.march == 0) return false;
-    const bool fp32 = c->p.storage == LB_STORAGE_FP32;
-    if (fp32 && (has_kind(c, LB_COLLOIDS) || has_kind(c, KIND_ELASTIC))) return false;
-    const double most = march_whole(c->P.Gm.nx, c->P.Gm.ny) ? 4.0 : fp32 ? 4.0 : 0.0;
-    return 11.0 * double(total_points(c)) <= most * c->P.march_blocks;
+    const Plan& P = c->P;
+    if (P.march == 0) return false;
+    if (c->p.storage == LB_STORAGE_FP32) return !has_kind(c, LB_COLLOIDS) && !has_kind(c, KIND_ELASTIC);
+    const double most = std::min(4.0, 2.2 + P.march_blocks / 256.0 / 64.0);
+    return march_whole(P.Gm.nx, P.Gm.ny) || 11.0 * double(total_points(c)) <= most * P.march_blocks;
 }
 
 // The geometry (tiles of the point lists) for the registered sets; called when they change, which also

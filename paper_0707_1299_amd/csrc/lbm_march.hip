@@ -22,18 +22,23 @@
 // in the order of the 66 x 10 nodes; cuts of 32 x 8 or 32 x 16, two blocks per compute unit, 387 and 430).
 //
 // What bounds it: the two barriers a plane and the arithmetic between them, with one block of 11 or 16 waves per compute
-// unit (42 KB of LDS for the populations, 24 B a node for velocities, 128 registers); the memory side is at half
-// the copy rate (256^3: 268 us a step, 76 B a node, 4.8 TB/s; 440 us and 5.8 TB/s one step at a time).
+// unit (42 KB of LDS for the populations, 24 B a node for velocities, 128 to 140 registers); the memory side is at
+// three quarters of the copy rate (256^3: 259 us a step, 76 B a node, 4.9 TB/s, without points; 440 us and
+// 5.8 TB/s one step at a time; moment storage 236 us, 80 B, 5.7 TB/s).
 //
-// Points: the entries of a plane in the point lists are looked up, fetched and staged in LDS over the two planes
-// before it; more than RPT of them at once are fetched in rounds.  Where two steps are taken of cut planes, whose rim
-// touches the lists of twelve tiles, the force density is laid out once as a field instead (launch_force_field) and read
-// with the plane before it where the lists have points near the block (128^3 with 600 points: 60.8 -> 42.5 us a
-// step; whole planes lose 3 % to the three registers), and only velocities that are wanted need the records.  The
-// interpolation partials are taken after the plane's last barrier, beside the next plane.
+// Points: the entries of a plane in the point lists are looked up, fetched and staged in LDS over the planes before
+// it; more than RPT of them at once are fetched in rounds.  Every iteration issues the same loads for them,
+// needed or not: on a path with fewer loads in flight a wait for one is a wait for all that came after it too (256^3
+// with 1000 colloids and moment storage: 350 us a step with loads where needed, 290 so).  Where two steps are taken of
+// cut planes, whose rim touches the lists of twelve tiles, the force density is laid out once as a field instead
+// (launch_force_field) and read with the plane before it where the lists have points near the block (128^3 with 600
+// points: 60.8 -> 42 us a step; 512 whole boxes of 32^3 lose with it, 255 -> 277, to its three registers), and only
+// velocities that are wanted need the records.  Interpolation partials are taken after the plane's last barrier, beside the
+// next plane.  Runs without points have kernels of their own (256^3: 274 -> 259, moment storage 259 -> 236).
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "lbm_collide.h"
 #include "lbm_device.h"
@@ -50,6 +55,7 @@ constexpr int EX = MX + 2, EY = MY + 2;    // ... with the rim
 constexpr int NE_CUT = EX * EY;
 constexpr int NE_MAX = 1024;               // nodes of the largest plane taken whole
 constexpr int LY = 2, LX = 6;              // point-list tiles of cut planes: 64 x 4 x 1 nodes (base-2 logarithms)
+constexpr unsigned NOWHERE = 1u << 31;     // offset past every descriptor's range: loads give 0, stores are dropped
 constexpr int RW = int(sizeof(PRec<float>) / 16), RPT = 48;   // staged records of a plane
 
 // populations that change column, and their place in LDS
@@ -74,12 +80,13 @@ struct MarchArgs {
     float *part0, *part1;          // interpolation partials of the (first, second) step, or NULL
 };
 
-template <int KIND, int COLL, int NE, bool CUT>
+template <int KIND, int COLL, int NE, bool CUT, bool LISTS>
 __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, const MarchArgs A)
 {
     constexpr int NV = KIND == KIND_PAIR ? NQ : MP_N;   // values a thread loads per plane
     constexpr int NU = KIND == KIND_PAIR ? 2 : 1;       // velocities per iteration
     constexpr bool FIELD = KIND == KIND_PAIR && CUT;    // forces from the laid-out field
+    constexpr bool EARLY = KIND == KIND_PAIR && !CUT;   // a plane's records are needed at its first collision
     __shared__ float pops[NP][NE];
     __shared__ float su[2][NU][3][NE];
     __shared__ uint4 sraw[3][RPT * RW];
@@ -129,22 +136,23 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
 
     // memory: a descriptor per z plane, lane offset of a node, plane offset of a value
     const unsigned rbb = unsigned(G.rb) * 4u, kp = unsigned(G.kp) * 4u, pbytes = unsigned(G.ny) * rbb;
-    const unsigned own = unsigned(y) * rbb + unsigned(x) * 4u;
+    const unsigned own = unsigned(y) * rbb + unsigned(x) * 4u, dest = out ? own : NOWHERE;
     const char* sb = reinterpret_cast<const char*>(A.src + (long long)box * G.sbox);
     char* db = reinterpret_cast<char*>(A.dst + (long long)box * G.sbox);
     auto plane = [&](int z) { return z < 0 ? z + G.nz : (z >= G.nz ? z - G.nz : z); };
     auto load = [&](int k, float (&p)[NV]) {       // what iteration k starts from
+        const unsigned size = k <= nzc ? pbytes : 0u;   // past the last iteration: nothing
         if constexpr (KIND == KIND_PAIR) {
-            const rsrc_t r[3] = {plane_rsrc(sb + (unsigned long long)plane(z0 + k + 1) * pbytes, pbytes),
-                                 plane_rsrc(sb + (unsigned long long)plane(z0 + k) * pbytes, pbytes),
-                                 plane_rsrc(sb + (unsigned long long)plane(z0 + k - 1) * pbytes, pbytes)};
+            const rsrc_t r[3] = {plane_rsrc(sb + (unsigned long long)plane(z0 + k + 1) * pbytes, size),
+                                 plane_rsrc(sb + (unsigned long long)plane(z0 + k) * pbytes, size),
+                                 plane_rsrc(sb + (unsigned long long)plane(z0 + k - 1) * pbytes, size)};
             const unsigned ro[3] = {unsigned(yp) * rbb, unsigned(y) * rbb, unsigned(ym) * rbb};
             const unsigned xo[3] = {unsigned(xp) * 4u, unsigned(x) * 4u, unsigned(xm) * 4u};
 #pragma unroll
             for (int i = 0; i < NQ; ++i)
                 p[i] = bload<float, 0>(r[cvel(i, 2) + 1], ro[cvel(i, 1) + 1] + xo[cvel(i, 0) + 1], unsigned(i) * kp);
         } else {
-            const rsrc_t r = plane_rsrc(sb + (unsigned long long)plane(z0 + k) * pbytes, pbytes);
+            const rsrc_t r = plane_rsrc(sb + (unsigned long long)plane(z0 + k) * pbytes, size);
 #pragma unroll
             for (int q = 0; q < MP_N; ++q) p[q] = bload<float, 0>(r, own, unsigned(q) * kp);
         }
@@ -176,27 +184,24 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
     struct List {
         int a, c;        // this lane's tile: entries a .. c - 1
     };
+    const rsrc_t rtoff = plane_rsrc(A.toff, A.toff ? unsigned(G.ntiles + 1) * 4u : 0u);
+    const rsrc_t rlist = plane_rsrc(A.tlist, NOWHERE), rrec = plane_rsrc(A.rec, NOWHERE);   // (offsets from the lists)
     auto entries = [&](int k) {                    // of plane z0 + k (none past the last plane)
-        List l{0, 0};
-        if (A.toff && mytile >= 0 && k <= nzc) {
-            const long long t = ((long long)box * G.ntz + plane(z0 + k)) * G.nty * G.ntx + mytile;
-            l.a = A.toff[t];
-            l.c = A.toff[t + 1];
-        }
-        return l;
+        typedef int i32x2 __attribute__((ext_vector_type(2)));
+        const unsigned t = unsigned((box * G.ntz + plane(z0 + k)) * G.nty * G.ntx + mytile);
+        const i32x2 v = __builtin_bit_cast(
+            i32x2, __builtin_amdgcn_raw_buffer_load_b64(rtoff, mytile >= 0 && k <= nzc ? t * 4u : NOWHERE, 0, 0));
+        return List{v.x, v.y};
     };
-    // force density of plane z0 + k at the thread's node: the counter-force, or where the lists have points near
-    // the block the field that launch_force_field left
-    auto force = [&](int k, const List& l, float (&g)[3]) {
-        if constexpr (FIELD) {
+    // force density of plane z0 + k at the thread's node, where the lists have points near the block: from the field
+    // that launch_force_field left
+    auto force = [&](int k, bool any, float (&g)[3]) {
+        const unsigned row = unsigned(G.nx) * 4u, size = unsigned(G.ny) * 3u * row;
+        const rsrc_t r = plane_rsrc(reinterpret_cast<const char*>(A.field) +
+                                        (unsigned long long)(box * G.nz + plane(z0 + k)) * size, size);
+        const unsigned off = any ? unsigned(y) * 3u * row + unsigned(x) * 4u : NOWHERE;
 #pragma unroll
-            for (int q = 0; q < 3; ++q) g[q] = gc[q];
-            if (__ballot(l.c > l.a)) {
-                const float* f = A.field + (((long long)box * G.nz + plane(z0 + k)) * G.ny + y) * 3 * G.nx + x;
-#pragma unroll
-                for (int q = 0; q < 3; ++q) g[q] = f[q * G.nx];
-            }
-        }
+        for (int q = 0; q < 3; ++q) g[q] = bload<float, 0>(r, off, unsigned(q) * row);
     };
     // the thread's word of the plane's staged records: entry index and tile (or -1), and how many there are
     const int sp = tid / RW, sw = tid - sp * RW;
@@ -216,7 +221,11 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
         if (sp >= RPT) idx = -1;
         return total;
     };
-    auto record = [&](int ent) { return reinterpret_cast<const uint4*>(A.rec + pk_point(ent))[sw]; };
+    auto entry = [&](int idx) { return bload<int, 0>(rlist, idx >= 0 ? unsigned(idx) * 4u : NOWHERE); };
+    auto record = [&](int idx, int ent) {
+        const unsigned at = unsigned(pk_point(ent)) * unsigned(sizeof(PRec<float>)) + unsigned(sw) * 16u;
+        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rrec, idx >= 0 ? at : NOWHERE, 0, 0));
+    };
     auto put = [&](int buf, int idx, int ent, int tile, const uint4& w) {
         if (idx >= 0) {
             sraw[buf][tid] = w;
@@ -236,8 +245,8 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
                 const int n = min(RPT, e1 - kb);
                 __syncthreads();
                 if (sp < n) {
-                    const int ent = A.tlist[kb + sp];
-                    put(buf, kb + sp, ent, tile, record(ent));
+                    const int ent = entry(kb + sp);
+                    put(buf, kb + sp, ent, tile, record(kb + sp, ent));
                 }
                 __syncthreads();
                 for (int p = 0; p < n; ++p) f(staged(buf, p), sent[buf][p], tile, p);
@@ -288,33 +297,44 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
         }
     };
 
-    // lev: level populations of the plane before; up1, up2: upward ones of the plane before and the one before it
+    // nxt: what the next iteration starts from; lev: level populations of the plane before; up1, up2: upward ones of
+    // the plane before and the one before it
     float nxt[NV], lev[NQ], up1[NQ], up2[NQ], gp[3] = {0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) lev[i] = up1[i] = up2[i] = 0.0f;
     bool bad = false;
     // lists: l0, l1 of planes k and k - 1 with t0, t1 entries (staged in buffers b0, b1), la of plane k + 1
-    List l0 = entries(-1), l1{0, 0}, la = entries(0);
-    int t0, t1 = 0, b0 = 0, b1 = 2;
-    auto look = [&](const List& l, int& idx, int& tile, int& ent) {
+    List l0 = LISTS ? entries(-1) : List{0, 0}, l1{0, 0}, la = LISTS ? entries(0) : List{0, 0};
+    int t0 = 0, t1 = 0, b0 = 0, b1 = 2;
+    auto look = [&](const List& l, int& idx, int& tile) {
         const int total = stages ? assign(l, idx, tile) : 0;
         if (!stages || total > RPT) idx = -1;
-        ent = idx >= 0 ? A.tlist[idx] : 0;
         return total;
     };
-    {
-        int idx, tile, ent;
-        t0 = look(l0, idx, tile, ent);
-        put(b0, idx, ent, tile, idx >= 0 ? record(ent) : uint4{});
+    int idx = -1, tile = -1, ent = 0;          // the thread's word: its entry's index, tile and value
+    if constexpr (LISTS) {
+        t0 = look(l0, idx, tile);
+        ent = entry(idx);
+        if constexpr (EARLY) put(b0, idx, ent, tile, record(idx, ent));
     }
-    float gn[3];                               // plane k + 1's force density (from the field)
-    if constexpr (FIELD) force(-1, l0, gn);
+    float gn[3];                               // plane k + 1's force density (from the field), if there is any
+    bool any = __ballot(l0.c > l0.a) != 0;
+    if constexpr (FIELD && LISTS) force(-1, any, gn);
     load(-1, nxt);
     __syncthreads();
     for (int k = -1; k <= nzc; ++k) {
-        // plane k + 1: its entries now, their records below; the tile offsets of plane k + 2
-        int idx, tile, ent;
+        // Point lists: the records of plane k, whose entries are here (EARLY: those of plane k + 1 at the end), the
+        // entries of plane k + 1, the tile offsets of plane k + 2.
+        const int idx0 = idx, tile0 = tile, ent0 = ent;
         uint4 word{};
-        const int ta = look(la, idx, tile, ent);
-        const List lb = entries(k + 2);
+        const List lc = la;
+        int ta = 0;
+        if constexpr (LISTS) {
+            if constexpr (!EARLY) word = record(idx0, ent0);
+            ta = look(lc, idx, tile);
+            if (!EARLY || ta > 0) ent = entry(idx);
+            la = entries(k + 2);
+        }
 
         float cur[NQ], u[3];
         if constexpr (KIND == KIND_PAIR) {
@@ -331,12 +351,13 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
         float g[3] = {gc[0], gc[1], gc[2]};
         if constexpr (FIELD) {
 #pragma unroll
-            for (int q = 0; q < 3; ++q) g[q] = gn[q];
+            for (int q = 0; q < 3; ++q) g[q] = LISTS && any ? gn[q] : gc[q];
+            if constexpr (LISTS) {
+                any = __ballot(lc.c > lc.a) != 0;
+                force(k + 1, any, gn);
+            }
         }
-        if (k < nzc) {
-            if constexpr (FIELD) force(k + 1, la, gn);
-            load(k + 1, nxt);
-        }
+        load(k + 1, nxt);
         if constexpr (KIND == KIND_PAIR) {
             // the first step's collision of plane k
             if constexpr (!FIELD) spread(b0, l0, t0, plane(z0 + k), g);
@@ -347,61 +368,57 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
             populations_of(p, cur);
             if (A.part0 && t0 > 0) keep(su[k & 1][0], u);
         }
-        if (idx >= 0) word = record(ent);
 
-        if (k >= 1) {
-            // pull of plane k - 1 and its collision
-            if (tid < ne) {
+        // pull of plane k - 1 and its collision
+        if (tid < ne) {
 #pragma unroll
-                for (int i = 1; i < NQ; ++i)
-                    if (moves(i)) pops[place(i)][e] = cvel(i, 2) > 0 ? up2[i] : (cvel(i, 2) == 0 ? lev[i] : cur[i]);
+            for (int i = 1; i < NQ; ++i)
+                if (moves(i)) pops[place(i)][e] = cvel(i, 2) > 0 ? up2[i] : (cvel(i, 2) == 0 ? lev[i] : cur[i]);
+        }
+        __syncthreads();
+        if constexpr (KIND == KIND_MOM) spread(b1, l1, t1, z0 + k - 1, g);
+        if (active && k >= 1) {
+            float f[NQ];
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) {
+                if (moves(i))
+                    f[i] = pops[place(i)][from(i)];
+                else
+                    f[i] = cvel(i, 2) > 0 ? up2[i] : (cvel(i, 2) == 0 ? lev[i] : cur[i]);
             }
-            __syncthreads();
-            if constexpr (KIND == KIND_MOM) spread(b1, l1, t1, z0 + k - 1, g);
-            if (active) {
-                float f[NQ];
+            const rsrc_t r = plane_rsrc(db + (unsigned long long)(z0 + k - 1) * pbytes, pbytes);
+            float p[MP_N];
+            if constexpr (KIND == KIND_PAIR) {
+                const Node<float> m = moments_of(f);
+                pieces_of<0>(m, gp, R, p, u);
+                bad = bad || (out && !finite_node(m, gp));
+                bstore<float, 2>(float(wgt(0)) * p[MP_R0], r, dest, 0u);
 #pragma unroll
-                for (int i = 0; i < NQ; ++i) {
-                    if (moves(i))
-                        f[i] = pops[place(i)][from(i)];
-                    else
-                        f[i] = cvel(i, 2) > 0 ? up2[i] : (cvel(i, 2) == 0 ? lev[i] : cur[i]);
+                for (int i = 1; i < NQ; i += 2) {
+                    float bp, bm;
+                    rebuild_pair(p, i, bp, bm);
+                    bstore<float, 2>(float(wgt(i)) * bp, r, dest, unsigned(i) * kp);
+                    bstore<float, 2>(float(wgt(i)) * bm, r, dest, unsigned(i + 1) * kp);
                 }
-                const rsrc_t r = plane_rsrc(db + (unsigned long long)(z0 + k - 1) * pbytes, pbytes);
-                Node<float> m;
-                float p[MP_N];
-                if constexpr (KIND == KIND_PAIR) {
-                    m = moments_of(f);
-                    pieces_of<0>(m, gp, R, p, u);
-                    if (out) {
-                        bad = bad || !finite_node(m, gp);
-                        bstore<float, 2>(float(wgt(0)) * p[MP_R0], r, own, 0u);
+            } else {
+                // f are brackets f*_i / w_i: the weights 12, 2, 1 (times 1/36) go on the sums
+                float q[NQ];
 #pragma unroll
-                        for (int i = 1; i < NQ; i += 2) {
-                            float bp, bm;
-                            rebuild_pair(p, i, bp, bm);
-                            bstore<float, 2>(float(wgt(i)) * bp, r, own, unsigned(i) * kp);
-                            bstore<float, 2>(float(wgt(i)) * bm, r, own, unsigned(i + 1) * kp);
-                        }
-                    }
-                } else {
-                    // f are brackets f*_i / w_i: the weights 12, 2, 1 (times 1/36) go on the sums
-                    float q[NQ];
+                for (int i = 0; i < NQ; ++i) q[i] = float(wgt(i)) * f[i];
+                const Node<float> m = moments_of(q);
+                pieces_of<COLL>(m, g, R, p, u);
+                bad = bad || (out && !finite_node(m, g));
 #pragma unroll
-                    for (int i = 0; i < NQ; ++i) q[i] = float(wgt(i)) * f[i];
-                    m = moments_of(q);
-                    pieces_of<COLL>(m, g, R, p, u);
-                    if (out) {
-                        bad = bad || !finite_node(m, g);
-#pragma unroll
-                        for (int v = 0; v < MP_N; ++v) bstore<float, 2>(p[v], r, own, unsigned(v) * kp);
-                    }
-                }
-                if ((KIND == KIND_PAIR ? A.part1 : A.part0) && t1 > 0) keep(su[k & 1][NU - 1], u);
+                for (int v = 0; v < MP_N; ++v) bstore<float, 2>(p[v], r, dest, unsigned(v) * kp);
             }
+            if ((KIND == KIND_PAIR ? A.part1 : A.part0) && t1 > 0) keep(su[k & 1][NU - 1], u);
         }
         const int bn = 3 - b0 - b1;                // the third buffer
-        put(bn, idx, ent, tile, word);
+        if constexpr (EARLY) {
+            if (ta > 0) put(bn, idx, ent, tile, record(idx, ent));
+        } else {
+            put(b0, idx0, ent0, tile0, word);
+        }
         __syncthreads();
         if constexpr (KIND == KIND_PAIR) {
             if (A.part0 && t0 > 0 && k >= 0 && k < nzc) interpolate(b0, l0, t0, z0 + k, su[k & 1][0], A.part0);
@@ -420,8 +437,7 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
         gp[1] = g[1];
         gp[2] = g[2];
         l1 = l0;
-        l0 = la;
-        la = lb;
+        l0 = lc;
         t1 = t0;
         t0 = ta;
         b1 = b0;
@@ -494,22 +510,22 @@ void launch_march(int storage, const Geom& G, int zc, const void* src, void* dst
             hipLaunchKernelGGL(kern, grid, block, 0, s, G, A);
     };
     const int n = G.nx * G.ny;
-    if (storage == ST_FP32) {
-        if (!whole) go(k_march<KIND_PAIR, 0, NE_CUT, true>, NE_CUT);
-        else if (n <= 256) go(k_march<KIND_PAIR, 0, 256, false>, std::max(n, RPT * RW));
-        else if (n <= 576) go(k_march<KIND_PAIR, 0, 576, false>, n);
-        else go(k_march<KIND_PAIR, 0, NE_MAX, false>, n);
-    } else if (G.coll) {
-        if (!whole) go(k_march<KIND_MOM, 1, NE_CUT, true>, NE_CUT);
-        else if (n <= 256) go(k_march<KIND_MOM, 1, 256, false>, std::max(n, RPT * RW));
-        else if (n <= 576) go(k_march<KIND_MOM, 1, 576, false>, n);
-        else go(k_march<KIND_MOM, 1, NE_MAX, false>, n);
-    } else {
-        if (!whole) go(k_march<KIND_MOM, 0, NE_CUT, true>, NE_CUT);
-        else if (n <= 256) go(k_march<KIND_MOM, 0, 256, false>, std::max(n, RPT * RW));
-        else if (n <= 576) go(k_march<KIND_MOM, 0, 576, false>, n);
-        else go(k_march<KIND_MOM, 0, NE_MAX, false>, n);
-    }
+    auto by_size = [&](auto kind, auto coll, auto lists) {
+        constexpr int KIND = decltype(kind)::value, COLL = decltype(coll)::value;
+        constexpr bool LISTS = decltype(lists)::value;
+        if (!whole) go(k_march<KIND, COLL, NE_CUT, true, LISTS>, NE_CUT);
+        else if (n <= 256) go(k_march<KIND, COLL, 256, false, LISTS>, std::max(n, RPT * RW));
+        else if (n <= 576) go(k_march<KIND, COLL, 576, false, LISTS>, n);
+        else go(k_march<KIND, COLL, NE_MAX, false, LISTS>, n);
+    };
+    auto by_kind = [&](auto lists) {
+        using std::integral_constant;
+        if (storage == ST_FP32) by_size(integral_constant<int, KIND_PAIR>{}, integral_constant<int, 0>{}, lists);
+        else if (G.coll) by_size(integral_constant<int, KIND_MOM>{}, integral_constant<int, 1>{}, lists);
+        else by_size(integral_constant<int, KIND_MOM>{}, integral_constant<int, 0>{}, lists);
+    };
+    if (toff) by_kind(std::true_type{});
+    else by_kind(std::false_type{});
 }
 
 }  // namespace lbm

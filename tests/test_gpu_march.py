@@ -142,6 +142,8 @@ def test_checkpoints(shape, nboxes, n):
     ((21, 20, 50), 200, 300, {}),
     ((128, 128, 128), 1, 0, {}),
     ((128, 128, 128), 1, 0, dict(collision="mrt", tau_bulk=0.9)),
+    ((128, 128, 128), 1, 300, {}),
+    ((160, 100, 190), 1, 400, dict(collision="mrt", tau_bulk=0.9)),
 ])
 def test_moment_storage(shape, nboxes, n, kw):
     kind = lbm.LB_COLLOIDS
