@@ -106,13 +106,17 @@ void plain_tile(const lb_params* p, int& tx, int& ty, int& tz)
 //    48^3: 458 -> 283).  Two FP16 nodes per lane: a whole wave per row from 128 nodes on (256^3: 292 -> 240;
 //    64 x 2 x 2 250).  Moment storage: rows of a z plane together (256^3: 524 -> 460).
 //  - Block order.  Tile rows on one XCD (bit 64) except for lattices near the L2 size, where
-//    nothing is gained (64^3: 19.0 against 19.4).
+//    nothing is gained (64^3: 19.0 against 19.4; two boxes of 61^3 21.6 / 22.1).
 //  - Loads.  Cached (bit 2) where neighbouring rows are read again after more than the L2 has passed (planes
 //    over 2.6 MB: 256^3 455 -> 448; 128^3 67.5 -> 66.6 the other way) or where rows do not
-//    start on a cache line, so that two rows share one (300 x 60 x 40: 47.6 -> 41.1; boxes of 16^3: 75 -> 65).
+//    start on a cache line, so that two rows share one (300 x 60 x 40: 47.6 -> 41.1; boxes of 16^3: 75 -> 65), unless
+//    rows of 32 nodes and more are in the L2 all the same (61^3 FP64 22.8 -> 20.4, 75^3 FP32 23.5 -> 22.3, the other
+//    way from 0.46e6 nodes on: 90^3 FP32 33.1 -> 31.1, 101 x 75 x 62 with the general operator 34.3 -> 30.8); and in
+//    the smallest lattices (20^3 FP32 10.0 -> 9.8).
 //  - The kernel for one tile per block (bit 128) where its missing tile loop saves registers: FP16, moment
 //    storage, the general and thermal operators, many points, small lattices; the FP32 and FP64 projected
-//    step is memory bound and faster with the loop (256^3 FP32: 429 against 447).
+//    step is memory bound and faster with the loop (256^3 FP32: 429 against 447).  FP16 with one node per
+//    lane and narrow rows likewise, and with cached loads (18 boxes of 31^3: 25.2 -> 23.4, 40 of 25^3 32.1 -> 27.5).
 // Batches of FP16 boxes keep the plain tile: their checkpoints hold a maximum per tile.
 void choose_default(const lb_params* p, int& tx, int& ty, int& tz, int& variant)
 {
@@ -126,8 +130,10 @@ void choose_default(const lb_params* p, int& tx, int& ty, int& tz, int& variant)
     if (fp16 && p->nboxes > 1) {
     } else if (mom) {
         if (p->nx >= 64) { tx = 64; ty = 4; tz = 1; }
+        else if (p->nx > 32) { tx = 64; ty = 2; tz = 2; }
     } else if (pairs) {
         if (p->nx >= 128) { tx = 128; ty = 2; tz = 1; }
+        else if (p->nx > 32 && p->nx < 64) { tx = 64; ty = 2; tz = 2; }
     } else if (p->nx > 64 && p->nx <= 128 && !dense && !(p->kT > 0.0)) {
         tx = 128; ty = 2; tz = 1;
     } else if (p->storage == LB_STORAGE_FP32 && p->nx >= 192 && !dense && !general &&
@@ -136,14 +142,14 @@ void choose_default(const lb_params* p, int& tx, int& ty, int& tz, int& variant)
     } else if (p->nx > 32 && p->nx < 64) {
         tx = 64; ty = 2; tz = 2;
     }
-    variant = 0;
-    if (copies <= 48.0e6) {
-        variant = 128;
+    const bool aligned = (long long)(p->nx * esz) % 128 == 0, narrow = !aligned && p->nx < 32;
+    if (copies <= (narrow ? 48.0e6 : 70.0e6)) {
+        variant = fp16 && !pairs && p->nx < 64 ? 2 : 128;
+        if (copies <= 9.0e6) variant |= 2;
     } else {
         const double plane = double(p->nx) * p->ny * planes * esz;
-        const bool aligned = (long long)(p->nx * esz) % 128 == 0;
         variant = 64;
-        if (!aligned || (plane > 2.6e6 && !dense)) variant |= 2;
+        if ((!aligned && (narrow || N * p->nboxes > 0.46e6)) || (plane > 2.6e6 && !dense)) variant |= 2;
         if (fp16 || mom || general || dense) variant |= 128;
     }
 }
