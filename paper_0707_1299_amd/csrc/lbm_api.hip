@@ -62,7 +62,7 @@ struct Layout {
     size_t pop[2], boxes, rec, psum, count, cursor, toff, bsum, tlist, tlist_tmp, partial, fpart, pmax, tmax, smax, ticket,
         tctr,
         err, nf, rebin, rebox, win,
-        diag, diagout, field;
+        diag, diagout, field, vel[2];
     size_t total;
 };
 
@@ -73,7 +73,6 @@ struct Plan {
     int chunks;
     long long cap;
     int march;         // z planes per block of the marching step kernels (see choose_march); 0: none
-    double march_blocks;   // plane iterations of one marching launch, rims left out: blocks times planes
     int variant;       // the step kernel's variant bits (the caller's, or choose_default's)
     int plain[3];      // a second tile whose checkpoints are accepted: plain_tile's, for a caller who named none
 };
@@ -225,18 +224,18 @@ int fill_geometry(const lb_params* p, int variant, long long cap, int tx, int ty
 // whole planes of up to 1024 nodes, 5.9 up to 576, 5.3 up to 256 (three blocks per compute unit), 4.1 for a cut of
 // 64 x 8 nodes with rim; half of it with moment storage.  The other kernels: 4 us and 40 nodes per ns, by
 // their tiles' lanes for whole planes, 1.3 times as long where the rows of small boxes do not fill cache lines.
-// (us per step, other kernels -> two FP32 steps per launch: 512 boxes of 32^3 404 -> 255, of 24^3 323 -> 133, of 16^3
-// 65.5 -> 49.5, 200 of 25 x 30 x 20 157 -> 82; 128^3 with 149 points 55.8 -> 43.4, 256^3 with 1000 439 -> 284; left
+// (us per step, other kernels -> two FP32 steps per launch: 512 boxes of 32^3 404 -> 264, of 24^3 323 -> 138, of 16^3
+// 65.5 -> 52, 200 of 25 x 30 x 20 157 -> 82; 128^3 with 149 points 55.8 -> 42.0, 256^3 with 1000 439 -> 260; left
 // alone: 64^3 9.0 / 10.6, 96^3 25 / 32, one box of 32^3 4.3 / 9.0.  Moment storage without points: 128^3
-// 53.5 -> 37, 256^3 415 -> 236, 512 boxes of 32^3 495 -> 275, of 16^3 112 -> 50; with a few colloids the estimate
+// 53.5 -> 37, 256^3 415 -> 236, 512 boxes of 32^3 495 -> 286, of 16^3 112 -> 50; with a few colloids the estimate
 // is short by a tenth: left alone 250 x 60 x 33 26.2 / 26.9.)
-int choose_march(const lb_params* p, const Geom& G, double& plane_blocks)
+int choose_march(const lb_params* p, const Geom& G)
 {
     const bool fp32 = p->storage == LB_STORAGE_FP32 && p->collision == LB_COLLISION_PROJECTED && !(p->kT > 0.0);
     const bool mom = p->storage == LB_STORAGE_MOM32;
     const double nodes = double(G.N) * G.nboxes;
-    // (a plane is addressed with 31-bit byte offsets; lattices near the memory's size have no room for the force field)
-    if (!(fp32 || mom) || double(G.ny) * G.rb * 4.0 >= 2.0e9 || double(p->max_points) * 1024.0 > nodes || nodes > 1.5e9) return 0;
+    // (a plane is addressed with 31-bit byte offsets; lattices near the memory's size have no room for the fields)
+    if (!(fp32 || mom) || double(G.ny) * G.rb * 4.0 >= 2.0e9 || double(p->max_points) * 1024.0 > nodes || nodes > 1.1e9) return 0;
     const bool whole = march_whole(G.nx, G.ny);
     const int plane = G.nx * G.ny;
     const double cols = whole ? 1.0 : double((G.nx + 63) / 64) * ((G.ny + 7) / 8);
@@ -255,7 +254,6 @@ int choose_march(const lb_params* p, const Geom& G, double& plane_blocks)
     const bool rows = (long long)G.nx * 4 % 128 == 0;
     const double lanes = whole ? double(G.ntiles) * BLOCK * (rows ? 1.0 : 1.3) : nodes;
     const double other = (4.0 + lanes / 40.0e3) * (mom ? 1.0 : 2.0);
-    plane_blocks = cols * G.nz * G.nboxes;
     return best > 0 && t < (mom ? 0.85 : 0.93) * other ? best : 0;
 }
 
@@ -307,7 +305,7 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     if (!tile_supported(tx, ty, tz)) { why = "unsupported tile shape"; return LB_ERR_ARG; }
     P.cap = p->max_points;
     if (int r = fill_geometry(p, P.variant, P.cap, tx, ty, tz, P.Gp, why)) return r;
-    P.march = p->tile_x == 0 && p->variant == 0 ? choose_march(p, P.Gp, P.march_blocks) : 0;
+    P.march = p->tile_x == 0 && p->variant == 0 ? choose_march(p, P.Gp) : 0;
     std::string none;
     int mx, my;
     march_tile(p->nx, p->ny, mx, my);
@@ -347,9 +345,11 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     L.win = take(sizeof(int4) * P.cap);
     L.diag = take(sizeof(double) * LBD_N * ntiles);
     L.diagout = take(sizeof(double) * LBD_N * p->nboxes);
-    // the fixed points' force density, for the two-step kernel of cut planes
-    const bool field = P.march > 0 && p->storage == LB_STORAGE_FP32 && P.cap > 0 && !march_whole(p->nx, p->ny);
-    L.field = take(field ? sizeof(float) * 3 * G.N * p->nboxes : 0);
+    // the marching kernels' force density and velocities (of one step or two) near points
+    const size_t field = P.march > 0 && P.cap > 0 ? sizeof(float) * 3 * G.N * p->nboxes : 0;
+    L.field = take(field);
+    L.vel[0] = take(field);
+    L.vel[1] = take(p->storage == LB_STORAGE_FP32 ? field : 0);
     L.total = o;
     return LB_OK;
 }
@@ -404,7 +404,7 @@ struct lb_ctx {
     unsigned long long binned_gen;   // gen the tile lists were last forced to rebuild for
     bool bins_valid;
     bool gc_valid;   // counter-force sums current for the registered static sets
-    bool field_valid;   // ... and the force field of the two-step kernel
+    bool field_valid;   // ... and the marching kernels' force field
     std::vector<GraphEntry> graphs;
     bool timing;
     std::vector<hipEvent_t> ev;
@@ -441,6 +441,7 @@ struct lb_ctx {
     double* diag() const { return (double*)(ws + P.L.diag); }
     double* diagout() const { return (double*)(ws + P.L.diagout); }
     float* field() const { return (float*)(ws + P.L.field); }
+    float* vel(int k) const { return (float*)(ws + P.L.vel[k]); }
 };
 
 namespace {
@@ -481,19 +482,19 @@ bool has_kind(const lb_ctx* c, int kind)
 }
 
 // Whether the marching kernels take the steps of the registered sets: two FP32 steps per launch where no point
-// moves, moment storage with any sets.  Up to the bound of choose_march they gain with any number of points (one
-// per 1024 nodes, us: FP32 256^3 425 -> 295, 128^3 56.5 -> 41, 512 boxes of 32^3 417 -> 300, moment storage 504 -> 278),
-// except on cut planes with moment storage, where a block whose planes have more points than others' holds up its
-// round: up to 2.5 list entries per plane of a block at 16 planes per compute unit, 4 at 115 and more (a point is
-// in the lists of five planes and about two of their tiles; 128^3 with 500 colloids 65 -> 59, 1000 66 -> 65, 2000 66 / 74;
-// 192^3 with 3000 196 -> 183, 6000 197 / 212; 256^3 with 1000 433 -> 290, 10^4 437 -> 394, 16000 440 / 445).
+// moves, moment storage with any sets, but with moving ones, whose forces and velocities cost two launches more a
+// step, only whole planes and large lattices.  Up to the bound of choose_march they gain with any number of
+// points, spread out or in one place (us per step, other kernels -> marching; fixed points: FP32 256^3 with
+// 16000 425 -> 279, 128^3 with 2000 57 -> 40, 512 boxes of 32^3 with 512 and their velocities 410 -> 264, all in one
+// box 411 -> 261; moment storage 128^3 with 100 56 -> 41; colloids: moment storage 256^3 with 1000 432 -> 309, 10^4 437
+// -> 389, 10^4 within 32^3 nodes 503 -> 362, 512 boxes of 24^3 with 2000 327 -> 184; left alone: 192^3 with 3000
+// 196 / 190, 6000 196 / 204, 128^3 with 500 65 / 67).
 bool marches(const lb_ctx* c)
 {
-    const Plan& P = c->P;
-    if (P.march == 0) return false;
-    if (c->p.storage == LB_STORAGE_FP32) return !has_kind(c, LB_COLLOIDS) && !has_kind(c, KIND_ELASTIC);
-    const double most = std::min(4.0, 2.2 + P.march_blocks / 256.0 / 64.0);
-    return march_whole(P.Gm.nx, P.Gm.ny) || 11.0 * double(total_points(c)) <= most * P.march_blocks;
+    if (c->P.march == 0) return false;
+    const Geom& G = c->P.Gm;
+    if (!has_kind(c, LB_COLLOIDS) && !has_kind(c, KIND_ELASTIC)) return true;
+    return c->p.storage == LB_STORAGE_MOM32 && (march_whole(G.nx, G.ny) || double(G.N) * G.nboxes >= 8.0e6);
 }
 
 // The geometry (tiles of the point lists) for the registered sets; called when they change, which also
@@ -678,10 +679,13 @@ void enqueue_step(lb_ctx* c, hipStream_t s, bool rebuild, bool after = false, bo
     unsigned long long* tin = G.coll == 2 ? c->tctr() + c->cur : nullptr;
     unsigned long long* tout = G.coll == 2 ? c->tctr() + (c->cur ^ 1) : nullptr;
     const int* toff = npts > 0 ? c->toff() : nullptr;
-    if (c->p.storage == LB_STORAGE_MOM32 && marches(c))
-        launch_march(c->p.storage, G, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->tlist(), c->rec(),
-                     nullptr, wants_velocity(c) ? c->partial() : nullptr, nullptr, s, e0, e1);
-    else
+    if (c->p.storage == LB_STORAGE_MOM32 && marches(c)) {
+        float* v = npts > 0 && wants_velocity(c) ? c->vel(0) : nullptr;
+        if (npts > 0 && rebuild) launch_force_field(G, c->boxes(), toff, c->tlist(), c->rec(), c->field(), s);
+        launch_march(c->p.storage, G, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->field(), v, nullptr,
+                     s, e0, e1);
+        if (v) launch_partials(G, npts, c->rec(), v, nullptr, (float*)c->partial(), nullptr, s);
+    } else
         launch_lattice(c->p.storage, G, 0, c->P.variant, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->tlist(),
                        c->rec(), c->partial(), (double*)c->tmax(), tin, tout, s, e0, e1);
     move_points(c, s, c->partial(), tin, before, fp16_exp);
@@ -694,14 +698,17 @@ void enqueue_steps(lb_ctx* c, hipStream_t s, bool rebuild, int n)
 {
     if (c->p.storage == LB_STORAGE_FP32 && !c->timing && marches(c)) {
         // the partials of the second step behind those of the first (the workspace holds FP64's)
-        const int* toff = total_points(c) > 0 ? c->toff() : nullptr;
+        const long long npts = total_points(c);
+        const int* toff = npts > 0 ? c->toff() : nullptr;
         float* p0 = wants_velocity(c) ? (float*)c->partial() : nullptr;
-        float* p1 = p0 ? p0 + 3 * c->P.cap * c->P.G.maxp : nullptr;
+        float* p1 = p0 + 3 * c->P.cap * c->P.G.maxp;
+        float *v0 = p0 ? c->vel(0) : nullptr, *v1 = p0 ? c->vel(1) : nullptr;
         for (int pairs = n / 4 * 2; pairs > 0; --pairs) {
             box_update(c, s, true);
-            launch_march(c->p.storage, c->P.G, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->tlist(),
-                         c->rec(), c->field(), p0, p1, s);
+            launch_march(c->p.storage, c->P.G, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->field(), v0,
+                         v1, s);
             if (p0) {
+                launch_partials(c->P.G, npts, c->rec(), v0, v1, p0, p1, s);
                 move_points(c, s, p0, nullptr, false, false);
                 move_points(c, s, p1, nullptr, false, false);
             }
@@ -1018,8 +1025,8 @@ int lb_step(lb_ctx* c, int32_t nsteps)
     if (left > 0 && !moving) {
         // static sums and the force field outside any captured graph
         box_update(c, c->stream, false);
-        if (pts && left >= 4 && c->p.storage == LB_STORAGE_FP32 && !march_whole(c->P.G.nx, c->P.G.ny) && marches(c) &&
-            !c->timing && !c->field_valid) {
+        if (pts && marches(c) && !c->field_valid &&
+            (c->p.storage == LB_STORAGE_MOM32 || (left >= 4 && !c->timing))) {
             launch_force_field(c->P.G, c->boxes(), c->toff(), c->tlist(), c->rec(), c->field(), c->stream);
             c->field_valid = true;
         }

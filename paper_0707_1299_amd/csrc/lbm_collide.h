@@ -37,17 +37,18 @@ template <class T> __device__ __forceinline__ Node<T> moments_of(const T (&f)[NQ
     return m;
 }
 
-// Force density of one point at node (x, y, z), added to (gx, gy, gz) (Sec. III).  Rows the point's stencil misses take
-// nothing from it and are skipped (a branch taken by whole waves when y and z are wave-uniform; otherwise
-// waves whose lanes all miss skip it).
+// Force density of one point, whose stencil starts at (bx, by, bz), at node (x, y, z), added to (gx, gy, gz) (Sec. III).
+// Rows the point's stencil misses take nothing from it and are skipped (a branch taken by whole waves when y and
+// z are wave-uniform; otherwise waves whose lanes all miss skip it).
 template <class T>
-__device__ __forceinline__ void add_point(const Geom& G, const PRec<T>& r, int x, int y, int z, T& gx, T& gy, T& gz)
+__device__ __forceinline__ void add_point(const Geom& G, int bx, int by, int bz, const PRec<T>& r, int x, int y, int z, T& gx,
+                                          T& gy, T& gz)
 {
-    int dy = y - r.by, dz = z - r.bz;
+    int dy = y - by, dz = z - bz;
     if (dy < 0) dy += G.ny;
     if (dz < 0) dz += G.nz;
     if (dy > 3 || dz > 3) return;
-    const T w = stencil_w<T>(x, r.bx, G.nx, r.wx) * stencil_w<T>(y, r.by, G.ny, r.wy) * stencil_w<T>(z, r.bz, G.nz, r.wz);
+    const T w = stencil_w<T>(x, bx, G.nx, r.wx) * stencil_w<T>(y, by, G.ny, r.wy) * stencil_w<T>(z, bz, G.nz, r.wz);
     gx = fm(r.f[0], w, gx);
     gy = fm(r.f[1], w, gy);
     gz = fm(r.f[2], w, gz);

@@ -247,7 +247,7 @@ __device__ __forceinline__ void lattice_tile(const Geom& G, const int tile,
         T gx = gcx, gy = gcy, gz = gcz;
         auto spread = [&](const PRec<T>& r) {
             if constexpr (SHARED) {
-                add_point(G, r, xh, y, z, gx, gy, gz);
+                add_point(G, r.bx, r.by, r.bz, r, xh, y, z, gx, gy, gz);
             } else {
                 int dy = y - r.by, dz = z - r.bz;
                 if (dy < 0) dy += G.ny;

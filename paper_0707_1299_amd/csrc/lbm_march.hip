@@ -21,20 +21,19 @@
 // the waves of the rim skip the second half (256^3: 297 -> 268 us a step, moment storage 307 -> 258, against threads
 // in the order of the 66 x 10 nodes; cuts of 32 x 8 or 32 x 16, two blocks per compute unit, 387 and 430).
 //
-// What bounds it: the two barriers a plane and the arithmetic between them, with one block of 11 or 16 waves per compute
-// unit (42 KB of LDS for the populations, 24 B a node for velocities, 128 to 140 registers); the memory side is at
-// three quarters of the copy rate (256^3: 259 us a step, 76 B a node, 4.9 TB/s, without points; 440 us and
-// 5.8 TB/s one step at a time; moment storage 236 us, 80 B, 5.7 TB/s).
+// What bounds it: the two barriers a plane and the arithmetic between them, with one or two blocks of 8 to 16 waves per
+// compute unit (42 KB of LDS for the populations, 72 to 117 registers); the memory side is at three quarters of
+// the copy rate (256^3: 262 us a step, 76 B a node, 4.9 TB/s; 440 us and 5.8 TB/s one step at a time; moment
+// storage 236 us, 80 B, 5.7 TB/s).
 //
-// Points: the entries of a plane in the point lists are looked up, fetched and staged in LDS over the planes before
-// it; more than RPT of them at once are fetched in rounds.  Every iteration issues the same loads for them,
-// needed or not: on a path with fewer loads in flight a wait for one is a wait for all that came after it too (256^3
-// with 1000 colloids and moment storage: 350 us a step with loads where needed, 290 so).  Where two steps are taken of
-// cut planes, whose rim touches the lists of twelve tiles, the force density is laid out once as a field instead
-// (launch_force_field) and read with the plane before it where the lists have points near the block (128^3 with 600
-// points: 60.8 -> 42 us a step; 512 whole boxes of 32^3 lose with it, 255 -> 277, to its three registers), and only
-// velocities that are wanted need the records.  Interpolation partials are taken after the plane's last barrier, beside the
-// next plane.  Runs without points have kernels of their own (256^3: 274 -> 259, moment storage 259 -> 236).
+// Points stay outside: a block has all points of its column, one plane after another, so that work per point
+// in it is serial (2000 points within 32^3 nodes of 128^3 with moment storage: 899 us a step with records staged and
+// velocities summed here, 85 so, 78 in the kernel of one node per thread).  launch_force_field lays the force
+// density out in the list tiles that have points, once for fixed points and before every step otherwise; the kernel
+// reads it there with the plane before (elsewhere the counter-force stands) and leaves the velocity there, which
+// launch_partials sums per point.  Every iteration issues the same loads for it, needed or not: on a path with
+// fewer loads in flight a wait for one is a wait for all that came after it too (256^3 with 1000 colloids and
+// moment storage: 350 us a step with loads where needed, 290 so).  Runs without points have kernels of their own.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -56,7 +55,6 @@ constexpr int NE_CUT = EX * EY;
 constexpr int NE_MAX = 1024;               // nodes of the largest plane taken whole
 constexpr int LY = 2, LX = 6;              // point-list tiles of cut planes: 64 x 4 x 1 nodes (base-2 logarithms)
 constexpr unsigned NOWHERE = 1u << 31;     // offset past every descriptor's range: loads give 0, stores are dropped
-constexpr int RW = int(sizeof(PRec<float>) / 16), RPT = 48;   // staged records of a plane
 
 // populations that change column, and their place in LDS
 constexpr bool moves(int i) { return cvel(i, 0) != 0 || cvel(i, 1) != 0; }
@@ -74,23 +72,16 @@ struct MarchArgs {
     const float* src;
     float* dst;
     const BoxDev* boxes;
-    const int *toff, *tlist;
-    const PRec<float>* rec;
-    const float* field;            // two steps of cut planes: force density of the fixed points, [box][z][y][component][x]
-    float *part0, *part1;          // interpolation partials of the (first, second) step, or NULL
+    const int* toff;
+    const float* field;            // force density, [box][z][y][component][x], where the lists have points
+    float *vel0, *vel1;            // velocity of the (first, second) step there, or NULL
 };
 
 template <int KIND, int COLL, int NE, bool CUT, bool LISTS>
 __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, const MarchArgs A)
 {
     constexpr int NV = KIND == KIND_PAIR ? NQ : MP_N;   // values a thread loads per plane
-    constexpr int NU = KIND == KIND_PAIR ? 2 : 1;       // velocities per iteration
-    constexpr bool FIELD = KIND == KIND_PAIR && CUT;    // forces from the laid-out field
-    constexpr bool EARLY = KIND == KIND_PAIR && !CUT;   // a plane's records are needed at its first collision
     __shared__ float pops[NP][NE];
-    __shared__ float su[2][NU][3][NE];
-    __shared__ uint4 sraw[3][RPT * RW];
-    __shared__ int sent[3][RPT], stile[3][RPT];
 
     // block -> (columns, chunk of planes, box); neighbours on one XCD
     int b = xcd_tile(int(blockIdx.x), int(gridDim.x));
@@ -100,7 +91,7 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
     b /= A.nby;
     const int ch = b % A.nchunk, box = b / A.nchunk;
     const int x0 = CUT ? bx * MX : 0, y0 = CUT ? by * MY : 0, z0 = ch * A.zc, nzc = min(A.zc, G.nz - z0);
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
 
     // The thread's column, whether it makes output, and where its values (e) and those of its neighbours lie in LDS.
     // Of a cut plane each wave takes the inner nodes of one row, so that its loads start on a line, and the last
@@ -176,125 +167,46 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
         for (int l = 0; l < 11; ++l)               // a tile met twice round a narrow box counts once
             if (lane > l && lane < 12 && mytile == __builtin_amdgcn_readlane(mytile, l)) mytile = -1;
     }
+    // the lane that has the thread's own tile (one without any where the block does not need it)
     const int nodetile = tile_of(x, y);
-    auto mine = [&](int t) { return !CUT || t == own0 || t == own1; };
-    // whether points' records are needed: for spreading without a field, for velocities in any case
-    const bool stages = !FIELD || A.part0;
+    int slot = 63;
+    for (int l = 0; l < 16; ++l)
+        if (__builtin_amdgcn_readlane(mytile, l) == nodetile) slot = l;
 
     struct List {
         int a, c;        // this lane's tile: entries a .. c - 1
     };
     const rsrc_t rtoff = plane_rsrc(A.toff, A.toff ? unsigned(G.ntiles + 1) * 4u : 0u);
-    const rsrc_t rlist = plane_rsrc(A.tlist, NOWHERE), rrec = plane_rsrc(A.rec, NOWHERE);   // (offsets from the lists)
+    const unsigned tiles_at = mytile >= 0 ? unsigned(mytile) * 4u : NOWHERE;
     auto entries = [&](int k) {                    // of plane z0 + k (none past the last plane)
         typedef int i32x2 __attribute__((ext_vector_type(2)));
-        const unsigned t = unsigned((box * G.ntz + plane(z0 + k)) * G.nty * G.ntx + mytile);
+        const unsigned first = unsigned((box * G.ntz + plane(z0 + k)) * G.nty * G.ntx) * 4u;
         const i32x2 v = __builtin_bit_cast(
-            i32x2, __builtin_amdgcn_raw_buffer_load_b64(rtoff, mytile >= 0 && k <= nzc ? t * 4u : NOWHERE, 0, 0));
+            i32x2, __builtin_amdgcn_raw_buffer_load_b64(rtoff, tiles_at | (k <= nzc ? 0u : NOWHERE), first, 0));
         return List{v.x, v.y};
     };
-    // force density of plane z0 + k at the thread's node, where the lists have points near the block: from the field
-    // that launch_force_field left
-    auto force = [&](int k, bool any, float (&g)[3]) {
-        const unsigned row = unsigned(G.nx) * 4u, size = unsigned(G.ny) * 3u * row;
-        const rsrc_t r = plane_rsrc(reinterpret_cast<const char*>(A.field) +
-                                        (unsigned long long)(box * G.nz + plane(z0 + k)) * size, size);
-        const unsigned off = any ? unsigned(y) * 3u * row + unsigned(x) * 4u : NOWHERE;
+    auto listed = [](const List& l) { return __ballot(l.c > l.a); };
+    // the force field and the velocities at the thread's node of plane z0 + k, if its tile is among the listed
+    const unsigned frow = unsigned(G.nx) * 4u, fsize = unsigned(G.ny) * 3u * frow;
+    const unsigned fown = unsigned(y) * 3u * frow + unsigned(x) * 4u;
+    auto field_plane = [&](const float* f, int k) {
+        return plane_rsrc(reinterpret_cast<const char*>(f) + (unsigned long long)(box * G.nz + plane(z0 + k)) * fsize, fsize);
+    };
+    auto mine = [&](unsigned long long tiles) { return unsigned(tiles >> slot) & 1u; };
+    // (offsets past the range by a bit, not by a choice: the compiler makes a branch of a choice, and with it
+    // vector registers of what both sides compute)
+    auto force = [&](int k, unsigned long long tiles, float (&g)[3]) {
+        const rsrc_t r = field_plane(A.field, k);
+        const unsigned at = fown | ((mine(tiles) ^ 1u) << 31);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) g[q] = bload<float, 0>(r, off, unsigned(q) * row);
+        for (int q = 0; q < 3; ++q) g[q] = bload<float, 0>(r, at, unsigned(q) * frow);
     };
-    // the thread's word of the plane's staged records: entry index and tile (or -1), and how many there are
-    const int sp = tid / RW, sw = tid - sp * RW;
-    auto assign = [&](const List& l, int& idx, int& tile) {
-        int total = 0;
-        idx = -1;
-        tile = -1;
-        for (unsigned long long m = __ballot(l.c > l.a && mine(mytile)); m; m &= m - 1) {
-            const int q = __ffsll(m) - 1, e0 = __builtin_amdgcn_readlane(l.a, q);
-            const int n = __builtin_amdgcn_readlane(l.c, q) - e0;
-            if (sp >= total && sp < total + n) {
-                idx = e0 + sp - total;
-                tile = __builtin_amdgcn_readlane(mytile, q);
-            }
-            total += n;
-        }
-        if (sp >= RPT) idx = -1;
-        return total;
-    };
-    auto entry = [&](int idx) { return bload<int, 0>(rlist, idx >= 0 ? unsigned(idx) * 4u : NOWHERE); };
-    auto record = [&](int idx, int ent) {
-        const unsigned at = unsigned(pk_point(ent)) * unsigned(sizeof(PRec<float>)) + unsigned(sw) * 16u;
-        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rrec, idx >= 0 ? at : NOWHERE, 0, 0));
-    };
-    auto put = [&](int buf, int idx, int ent, int tile, const uint4& w) {
-        if (idx >= 0) {
-            sraw[buf][tid] = w;
-            if (sw == 0) {
-                sent[buf][sp] = ent;
-                stile[buf][sp] = tile;
-            }
-        }
-    };
-    auto staged = [&](int buf, int p) -> const PRec<float>& { return reinterpret_cast<const PRec<float>*>(sraw[buf])[p]; };
-    // f(record, entry, tile, number) for every entry of a plane whose records are not all staged
-    auto in_rounds = [&](int buf, const List& l, auto f) {
-        for (unsigned long long m = __ballot(l.c > l.a && mine(mytile)); m; m &= m - 1) {
-            const int q = __ffsll(m) - 1, e0 = __builtin_amdgcn_readlane(l.a, q), e1 = __builtin_amdgcn_readlane(l.c, q);
-            const int tile = __builtin_amdgcn_readlane(mytile, q);
-            for (int kb = e0; kb < e1; kb += RPT) {
-                const int n = min(RPT, e1 - kb);
-                __syncthreads();
-                if (sp < n) {
-                    const int ent = entry(kb + sp);
-                    put(buf, kb + sp, ent, tile, record(kb + sp, ent));
-                }
-                __syncthreads();
-                for (int p = 0; p < n; ++p) f(staged(buf, p), sent[buf][p], tile, p);
-            }
-        }
-    };
-    // force density of the plane's points at this node
-    auto spread = [&](int buf, const List& l, int total, int z, float (&g)[3]) {
-        auto add = [&](const PRec<float>& r, int, int tile, int) {
-            if (tile == nodetile) add_point(G, r, x, y, z, g[0], g[1], g[2]);
-        };
-        if (total > RPT)
-            in_rounds(buf, l, add);
-        else
-            for (int p = 0; p < total; ++p) add(staged(buf, p), 0, stile[buf][p], p);
-    };
-    // partial sums of the plane's velocity for the points of the output tiles, one wave per point (all 64 stencil
-    // nodes, those of other planes and tiles with weight zero: the sums of the single-step kernel, in its order)
-    auto interpolate = [&](int buf, const List& l, int total, int z, const float (&v)[3][NE], float* part) {
-        const int dx = lane & 3, dy = (lane >> 2) & 3, dz = lane >> 4;
-        auto sum = [&](const PRec<float>& r, int ent, int tile, int p) {
-            if (p % nw != wave) return;
-            int px = r.bx + dx, py = r.by + dy, pz = r.bz + dz;
-            if (px >= G.nx) px -= G.nx;
-            if (py >= G.ny) py -= G.ny;
-            if (pz >= G.nz) pz -= G.nz;
-            const bool in = pz == z && tile_of(px, py) == tile;
-            const int li = in ? (CUT ? px - x0 + 1 + EX * (py - y0 + 1) : px + G.nx * py) : 0;
-            const float w = in ? r.wx[dx] * r.wy[dy] * r.wz[dz] : 0.0f;
-            const float sx = wave_sum(v[0][li] * w), sy = wave_sum(v[1][li] * w), sz = wave_sum(v[2][li] * w);
-            float* o = part + ((long long)pk_point(ent) * G.maxp + pk_slot(ent)) * 3;
-            if (lane == 0) {
-                o[0] = sx;
-                o[1] = sy;
-                o[2] = sz;
-            }
-        };
-        if (total > RPT)
-            in_rounds(buf, l, sum);
-        else
-            for (int p = wave; p < total; p += nw) sum(staged(buf, p), sent[buf][p], stile[buf][p], p);
-    };
-    auto keep = [&](float (&v)[3][NE], const float (&u)[3]) {
-        if (tid < ne) {
-            v[0][e] = u[0];
-            v[1][e] = u[1];
-            v[2][e] = u[2];
-        }
+    auto keep = [&](float* vel, int k, unsigned long long tiles, const float (&u)[3]) {
+        if (!vel || tiles == 0) return;
+        const rsrc_t r = field_plane(vel, k);
+        const unsigned at = fown | ((mine(tiles) ^ 1u) << 31) | (out ? 0u : NOWHERE);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) bstore<float, 0>(u[q], r, at, unsigned(q) * frow);
     };
 
     // nxt: what the next iteration starts from; lev: level populations of the plane before; up1, up2: upward ones of
@@ -303,39 +215,17 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
 #pragma unroll
     for (int i = 0; i < NQ; ++i) lev[i] = up1[i] = up2[i] = 0.0f;
     bool bad = false;
-    // lists: l0, l1 of planes k and k - 1 with t0, t1 entries (staged in buffers b0, b1), la of plane k + 1
-    List l0 = LISTS ? entries(-1) : List{0, 0}, l1{0, 0}, la = LISTS ? entries(0) : List{0, 0};
-    int t0 = 0, t1 = 0, b0 = 0, b1 = 2;
-    auto look = [&](const List& l, int& idx, int& tile) {
-        const int total = stages ? assign(l, idx, tile) : 0;
-        if (!stages || total > RPT) idx = -1;
-        return total;
-    };
-    int idx = -1, tile = -1, ent = 0;          // the thread's word: its entry's index, tile and value
+    // tiles with points of plane k - 1 (m1) and k (m0); la: the lists of plane k + 1
+    List la{0, 0};
+    unsigned long long m0 = 0, m1 = 0;
+    float gn[3];                               // the next plane's force density
     if constexpr (LISTS) {
-        t0 = look(l0, idx, tile);
-        ent = entry(idx);
-        if constexpr (EARLY) put(b0, idx, ent, tile, record(idx, ent));
+        m0 = listed(entries(-1));
+        la = entries(0);
+        force(-1, m0, gn);
     }
-    float gn[3];                               // plane k + 1's force density (from the field), if there is any
-    bool any = __ballot(l0.c > l0.a) != 0;
-    if constexpr (FIELD && LISTS) force(-1, any, gn);
     load(-1, nxt);
-    __syncthreads();
     for (int k = -1; k <= nzc; ++k) {
-        // Point lists: the records of plane k, whose entries are here (EARLY: those of plane k + 1 at the end), the
-        // entries of plane k + 1, the tile offsets of plane k + 2.
-        const int idx0 = idx, tile0 = tile, ent0 = ent;
-        uint4 word{};
-        const List lc = la;
-        int ta = 0;
-        if constexpr (LISTS) {
-            if constexpr (!EARLY) word = record(idx0, ent0);
-            ta = look(lc, idx, tile);
-            if (!EARLY || ta > 0) ent = entry(idx);
-            la = entries(k + 2);
-        }
-
         float cur[NQ], u[3];
         if constexpr (KIND == KIND_PAIR) {
 #pragma unroll
@@ -349,24 +239,24 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
             for (int i = 1; i < NQ; i += 2) rebuild_pair(p, i, cur[i], cur[i + 1]);
         }
         float g[3] = {gc[0], gc[1], gc[2]};
-        if constexpr (FIELD) {
+        unsigned long long ma = 0;
+        if constexpr (LISTS) {
+            // plane k + 1's forces and plane k + 2's lists, the same loads in every iteration
 #pragma unroll
-            for (int q = 0; q < 3; ++q) g[q] = LISTS && any ? gn[q] : gc[q];
-            if constexpr (LISTS) {
-                any = __ballot(lc.c > lc.a) != 0;
-                force(k + 1, any, gn);
-            }
+            for (int q = 0; q < 3; ++q) g[q] = mine(m0) ? gn[q] : gc[q];
+            ma = listed(la);
+            la = entries(k + 2);
+            force(k + 1, ma, gn);
         }
         load(k + 1, nxt);
         if constexpr (KIND == KIND_PAIR) {
             // the first step's collision of plane k
-            if constexpr (!FIELD) spread(b0, l0, t0, plane(z0 + k), g);
             const Node<float> m = moments_of(cur);
             float p[MP_N];
             pieces_of<0>(m, g, R, p, u);
             if (out && k >= 0 && k < nzc) bad = bad || !finite_node(m, g);
             populations_of(p, cur);
-            if (A.part0 && t0 > 0) keep(su[k & 1][0], u);
+            if (LISTS && k >= 0 && k < nzc) keep(A.vel0, k, m0, u);
         }
 
         // pull of plane k - 1 and its collision
@@ -376,7 +266,6 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
                 if (moves(i)) pops[place(i)][e] = cvel(i, 2) > 0 ? up2[i] : (cvel(i, 2) == 0 ? lev[i] : cur[i]);
         }
         __syncthreads();
-        if constexpr (KIND == KIND_MOM) spread(b1, l1, t1, z0 + k - 1, g);
         if (active && k >= 1) {
             float f[NQ];
 #pragma unroll
@@ -406,26 +295,14 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
 #pragma unroll
                 for (int i = 0; i < NQ; ++i) q[i] = float(wgt(i)) * f[i];
                 const Node<float> m = moments_of(q);
-                pieces_of<COLL>(m, g, R, p, u);
-                bad = bad || (out && !finite_node(m, g));
+                pieces_of<COLL>(m, gp, R, p, u);
+                bad = bad || (out && !finite_node(m, gp));
 #pragma unroll
                 for (int v = 0; v < MP_N; ++v) bstore<float, 2>(p[v], r, dest, unsigned(v) * kp);
             }
-            if ((KIND == KIND_PAIR ? A.part1 : A.part0) && t1 > 0) keep(su[k & 1][NU - 1], u);
-        }
-        const int bn = 3 - b0 - b1;                // the third buffer
-        if constexpr (EARLY) {
-            if (ta > 0) put(bn, idx, ent, tile, record(idx, ent));
-        } else {
-            put(b0, idx0, ent0, tile0, word);
+            if constexpr (LISTS) keep(KIND == KIND_PAIR ? A.vel1 : A.vel0, k - 1, m1, u);
         }
         __syncthreads();
-        if constexpr (KIND == KIND_PAIR) {
-            if (A.part0 && t0 > 0 && k >= 0 && k < nzc) interpolate(b0, l0, t0, z0 + k, su[k & 1][0], A.part0);
-            if (A.part1 && t1 > 0 && k >= 1) interpolate(b1, l1, t1, z0 + k - 1, su[k & 1][1], A.part1);
-        } else {
-            if (A.part0 && t1 > 0 && k >= 1) interpolate(b1, l1, t1, z0 + k - 1, su[k & 1][0], A.part0);
-        }
 
 #pragma unroll
         for (int i = 0; i < NQ; ++i) {
@@ -436,12 +313,8 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
         gp[0] = g[0];
         gp[1] = g[1];
         gp[2] = g[2];
-        l1 = l0;
-        l0 = lc;
-        t1 = t0;
-        t0 = ta;
-        b1 = b0;
-        b0 = bn;
+        m1 = m0;
+        m0 = ma;
     }
     if (__any(bad) && lane == 0) atomicOr(&G.nf[box], 1);
     if (blockIdx.x == 0 && tid == 0) *G.rebin = 0;   // as the other step kernels
@@ -449,28 +322,71 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
 
 }  // namespace
 
-// Force density of fixed points and counter-force at every node, for the two-step kernel: the sums of the
-// single-step kernel, in its order, once per change of the points.  One block per list tile.
+// Force density (counter-force and points, the sums of the single-step kernel, in its order) at the nodes of list
+// tiles that have points, for the marching kernels.  A block looks through FT tiles, one per lane, and takes those
+// that have any with all its threads, a node each.  Their entries are consecutive in the lists; the records are staged
+// in LDS, RPT at a time, so that a tile waits for one chain of loads and not for one per point.
+constexpr int FT = 4, RW = int(sizeof(PRec<float>) / 16), RPT = BLOCK / RW;
+
 __global__ __launch_bounds__(BLOCK) void k_force_field(const Geom G, const BoxDev* __restrict__ boxes,
                                                        const int* __restrict__ toff, const int* __restrict__ tlist,
                                                        const PRec<float>* __restrict__ rec, float* __restrict__ field)
 {
-    const long long t = blockIdx.x;
-    const int tx = int(t % G.ntx), ty = int(t / G.ntx % G.nty), box = int(t / G.tiles_per_box);
-    const int z = int(t / ((long long)G.ntx * G.nty) % G.ntz);
-    const int x = (tx << LX) + (threadIdx.x & 63), y = (ty << LY) + (threadIdx.x >> 6);
-    if (x >= G.nx || y >= G.ny) return;
-    const BoxDev& B = boxes[box];
-    float g[3] = {float(B.gc[0]), float(B.gc[1]), float(B.gc[2])};
-    for (int k = toff[t]; k < toff[t + 1]; ++k) add_point(G, rec[pk_point(tlist[k])], x, y, z, g[0], g[1], g[2]);
-    float* f = field + (((long long)box * G.nz + z) * G.ny + y) * 3 * G.nx + x;
-    for (int q = 0; q < 3; ++q) f[q * G.nx] = g[q];
+    __shared__ uint4 sraw[RPT * RW];
+    const PRec<float>* staged = reinterpret_cast<const PRec<float>*>(sraw);
+    const long long first = (long long)blockIdx.x * FT;
+    const int lane = threadIdx.x & 63, sp = int(threadIdx.x) / RW, sw = int(threadIdx.x) - sp * RW;
+    const bool has = lane < FT && first + lane < G.ntiles;
+    const int a = has ? toff[first + lane] : 0, c = has ? toff[first + lane + 1] : 0;
+    const unsigned long long tiles = __ballot(c > a);
+    if (tiles == 0) return;
+    const int end = __builtin_amdgcn_readlane(c, 63 - __builtin_clzll(tiles));   // past the last tile's entries
+    int s0 = 0, s1 = 0;                                                        // entries staged
+    for (unsigned long long m = tiles; m; m &= m - 1) {
+        const int l = __ffsll(m) - 1;
+        const unsigned t = unsigned(first + l);
+        const int tx = int(t % G.ntx), ty = int(t / G.ntx % G.nty), box = int(t / G.tiles_per_box);
+        const int z = int(t / unsigned(G.ntx * G.nty) % G.ntz);
+        const int x = (tx << G.ltx) + (threadIdx.x & (G.tx - 1)), y = (ty << G.lty) + (threadIdx.x >> G.ltx);
+        const BoxDev& B = boxes[box];
+        float g[3] = {float(B.gc[0]), float(B.gc[1]), float(B.gc[2])};
+        for (int k = __builtin_amdgcn_readlane(a, l), k1 = __builtin_amdgcn_readlane(c, l); k < k1;) {
+            if (k >= s1) {
+                s0 = k;
+                s1 = min(k + RPT, end);
+                __syncthreads();   // every wave has read the records before
+                if (sp < s1 - s0)
+                    sraw[threadIdx.x] = reinterpret_cast<const uint4*>(rec + pk_point(tlist[s0 + sp]))[sw];
+                __syncthreads();
+            }
+            // a lane looks at each staged point: those that reach the plane (and the row, where a wave has one) are added
+            const int n = min(k1, s1) - k;
+            int4 h{};
+            bool hit = false;
+            if (lane < n) {
+                h = __builtin_bit_cast(int4, sraw[(k - s0 + lane) * RW]);
+                int dy = y - h.y, dz = z - h.z;
+                if (dy < 0) dy += G.ny;
+                if (dz < 0) dz += G.nz;
+                hit = dz <= 3 && (dy <= 3 || G.tx < 64);
+            }
+            for (unsigned long long q = __ballot(hit); q; q &= q - 1) {
+                const int p = __ffsll(q) - 1;
+                add_point(G, __builtin_amdgcn_readlane(h.x, p), __builtin_amdgcn_readlane(h.y, p),
+                          __builtin_amdgcn_readlane(h.z, p), staged[k - s0 + p], x, y, z, g[0], g[1], g[2]);
+            }
+            k += n;
+        }
+        if (x >= G.nx || y >= G.ny) continue;
+        float* f = field + (((long long)box * G.nz + z) * G.ny + y) * 3 * G.nx + x;
+        for (int q = 0; q < 3; ++q) f[q * G.nx] = g[q];
+    }
 }
 
 void launch_force_field(const Geom& G, const BoxDev* boxes, const int* toff, const int* tlist, const void* rec, float* field,
                         hipStream_t s)
 {
-    hipLaunchKernelGGL(k_force_field, dim3((unsigned)G.ntiles), dim3(BLOCK), 0, s, G, boxes, toff, tlist,
+    hipLaunchKernelGGL(k_force_field, dim3((unsigned)((G.ntiles + FT - 1) / FT)), dim3(BLOCK), 0, s, G, boxes, toff, tlist,
                        (const PRec<float>*)rec, field);
 }
 
@@ -483,8 +399,7 @@ void march_tile(int nx, int ny, int& tx, int& ty)
 }
 
 void launch_march(int storage, const Geom& G, int zc, const void* src, void* dst, const BoxDev* boxes, const int* toff,
-                  const int* tlist, const void* rec, const float* field, void* part0, void* part1, hipStream_t s,
-                  hipEvent_t ev0, hipEvent_t ev1)
+                  const float* field, float* vel0, float* vel1, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
     const bool whole = march_whole(G.nx, G.ny);
     MarchArgs A;
@@ -496,11 +411,9 @@ void launch_march(int storage, const Geom& G, int zc, const void* src, void* dst
     A.dst = (float*)dst;
     A.boxes = boxes;
     A.toff = toff;
-    A.tlist = tlist;
-    A.rec = (const PRec<float>*)rec;
     A.field = field;
-    A.part0 = (float*)part0;
-    A.part1 = (float*)part1;
+    A.vel0 = vel0;
+    A.vel1 = vel1;
     const dim3 grid((unsigned)((long long)A.nbx * A.nby * A.nchunk * G.nboxes));
     auto go = [&](auto kern, int nodes) {
         const dim3 block((nodes + 63) / 64 * 64);
@@ -514,7 +427,7 @@ void launch_march(int storage, const Geom& G, int zc, const void* src, void* dst
         constexpr int KIND = decltype(kind)::value, COLL = decltype(coll)::value;
         constexpr bool LISTS = decltype(lists)::value;
         if (!whole) go(k_march<KIND, COLL, NE_CUT, true, LISTS>, NE_CUT);
-        else if (n <= 256) go(k_march<KIND, COLL, 256, false, LISTS>, std::max(n, RPT * RW));
+        else if (n <= 256) go(k_march<KIND, COLL, 256, false, LISTS>, n);
         else if (n <= 576) go(k_march<KIND, COLL, 576, false, LISTS>, n);
         else go(k_march<KIND, COLL, NE_MAX, false, LISTS>, n);
     };

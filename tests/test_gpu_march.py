@@ -144,6 +144,7 @@ def test_checkpoints(shape, nboxes, n):
     ((128, 128, 128), 1, 0, dict(collision="mrt", tau_bulk=0.9)),
     ((128, 128, 128), 1, 300, {}),
     ((160, 100, 190), 1, 400, dict(collision="mrt", tau_bulk=0.9)),
+    ((203, 201, 200), 1, 400, dict(collision="mrt", tau_bulk=0.9)),    # cut planes with moving points
 ])
 def test_moment_storage(shape, nboxes, n, kw):
     kind = lbm.LB_COLLOIDS
@@ -155,3 +156,42 @@ def test_moment_storage(shape, nboxes, n, kw):
         if x.numel():
             assert (x - y).abs().max().item() <= 11 * 32 * EPS * top * (11 if x is a[2] else 1)
     assert all(torch.equal(x, y) for x, y in zip(b, c))
+
+
+@pytest.mark.parametrize("shape,nboxes,n", [((128, 128, 128), 1, 300), ((160, 100, 190), 1, 200), ((24, 24, 24), 300, 400)])
+def test_moment_storage_fixed_points(shape, nboxes, n):
+    """The force field laid out once and the velocities handed out, over splits of the run and a change of the sets."""
+    a = _run(shape, nboxes, "mom32", n, (64, 4, 1), [11], 70, flow=True)
+    b = _run(shape, nboxes, "mom32", n, None, [11], 70, flow=True)
+    c = _run(shape, nboxes, "mom32", n, None, [3, 4, 1, 3], 70, flow=True)
+    top = max(a[1].abs().max().item(), (a[0] - 1).abs().max().item())
+    for x, y in zip(a, b):
+        assert (x - y).abs().max().item() <= 11 * 32 * EPS * top * (11 if x is a[2] else 1)
+    assert all(torch.equal(x, y) for x, y in zip(b, c))
+
+
+@pytest.mark.parametrize("storage", ["fp32", "mom32"])
+def test_points_in_one_place(storage):
+    """More points in a list tile than are staged at once, several tiles of them (all of 900 within 12 x 9 x 7 nodes)."""
+    shape, n = (128, 128, 128), 900
+    g = np.random.default_rng(11)
+    out = []
+    for tile in ((64, 4, 1), None):
+        g = np.random.default_rng(11)
+        pos = torch.tensor(g.uniform(0, 1, (n, 3)) * np.array([12.0, 9.0, 7.0]) + [58.0, 123.0, 60.0], device="cuda")
+        frc = torch.tensor(g.normal(scale=1e-6, size=(n, 3)), device="cuda")
+        lat = lbm.Lattice(shape, storage, tau=0.7, max_points=n, tile=tile, variant=64 if tile else 0)
+        model = lbm.PointModel()
+        model.vel_sum = vel = torch.zeros_like(pos)
+        lat.add_point_forces(pos, frc, None, lbm.LB_FORCES_STATIC, model)
+        lat.step(8)
+        _, u = lat.moments()
+        lat.sync()
+        lat.close()
+        out.append((u, vel))
+    (ua, va), (ub, vb) = out
+    top = ua.abs().max().item()
+    if storage == "fp32":
+        assert torch.equal(ua, ub)
+    assert (ua - ub).abs().max().item() <= 8 * 32 * EPS * top
+    assert (va - vb).abs().max().item() <= 8 * 64 * EPS * top * 8
