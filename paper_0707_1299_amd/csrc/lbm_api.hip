@@ -73,6 +73,8 @@ struct Plan {
     int chunks;
     long long cap;
     int march;         // z planes per block of the marching step kernels (see choose_march); 0: none
+    int march_rows;    // ... and rows of a plane (0: all)
+    double march_us, other_us;   // estimated time of a step without points: marching, other kernels (moment storage)
     int variant;       // the step kernel's variant bits (the caller's, or choose_default's)
     int plain[3];      // a second tile whose checkpoints are accepted: plain_tile's, for a caller who named none
 };
@@ -220,17 +222,19 @@ int fill_geometry(const lb_params* p, int variant, long long cap, int tx, int ty
 
 // Planes per block of the marching kernels (lbm_march.hip), or 0 where the kernels of one node per thread are
 // faster.  A launch takes as many rounds as its blocks fill the chip; a round costs the block's planes and two
-// repeated ones; the planes per block are chosen for the fewest.  Time of one plane of a block, measured: 8.4 us for
-// whole planes of up to 1024 nodes, 5.9 up to 576, 5.3 up to 256 (three blocks per compute unit), 4.1 for a cut of
-// 64 x 8 nodes with rim; half of it with moment storage.  The other kernels: 4 us and 40 nodes per ns, by
-// their tiles' lanes for whole planes, 1.3 times as long where the rows of small boxes do not fill cache lines.
+// repeated ones; the planes per block are chosen for the fewest.  Time of one plane of a block, measured: 7.2 us for
+// whole planes of up to 1024 nodes, 5.4 up to 576, 5.3 up to 256 (three blocks per compute unit), 4.1 for a cut of
+// 64 x 8 nodes with rim, 5.3 for one of 64 x 12; half of it with moment storage.  The other kernels: 4 us and 40 nodes
+// per ns, by their tiles' lanes for whole planes, 1.3 (cut planes 1.15) times as long where rows do not fill cache lines.
 // (us per step, other kernels -> two FP32 steps per launch: 512 boxes of 32^3 404 -> 264, of 24^3 323 -> 138, of 16^3
 // 65.5 -> 52, 200 of 25 x 30 x 20 157 -> 82; 128^3 with 149 points 55.8 -> 42.0, 256^3 with 1000 439 -> 260; left
-// alone: 64^3 9.0 / 10.6, 96^3 25 / 32, one box of 32^3 4.3 / 9.0.  Moment storage without points: 128^3
+// alone: 64^3 9.0 / 10.6, one box of 32^3 4.3 / 9.0; 64 x 12 against 64 x 8 nodes: 96^3 24.1 (not marching) -> 17.9,
+// 192^3 124 -> 114, 128^3 37.1 / 38.4, 256^3 266 / 284.  Moment storage without points: 128^3
 // 53.5 -> 37, 256^3 415 -> 236, 512 boxes of 32^3 495 -> 286, of 16^3 112 -> 50; with a few colloids the estimate
 // is short by a tenth: left alone 250 x 60 x 33 26.2 / 26.9.)
-int choose_march(const lb_params* p, const Geom& G)
+int choose_march(const lb_params* p, Plan& P)
 {
+    const Geom& G = P.Gp;
     const bool fp32 = p->storage == LB_STORAGE_FP32 && p->collision == LB_COLLISION_PROJECTED && !(p->kT > 0.0);
     const bool mom = p->storage == LB_STORAGE_MOM32;
     const double nodes = double(G.N) * G.nboxes;
@@ -238,23 +242,28 @@ int choose_march(const lb_params* p, const Geom& G)
     if (!(fp32 || mom) || double(G.ny) * G.rb * 4.0 >= 2.0e9 || double(p->max_points) * 1024.0 > nodes || nodes > 1.1e9) return 0;
     const bool whole = march_whole(G.nx, G.ny);
     const int plane = G.nx * G.ny;
-    const double cols = whole ? 1.0 : double((G.nx + 63) / 64) * ((G.ny + 7) / 8);
     const double slots = whole && plane <= 256 ? 768 : 256;
-    const double unit = whole ? (plane > 576 ? 8.4 : plane > 256 ? 5.9 : 5.3) * (mom ? 0.5 : 1.0) : mom ? 2.0 : 4.1;
     int best = 0;
     double t = 0;
-    for (int n = 1; n <= (G.nz + 3) / 4; ++n) {
-        const int zc = (G.nz + n - 1) / n;
-        const double blocks = cols * ((G.nz + zc - 1) / zc) * G.nboxes, cost = ceil(blocks / slots) * (zc + 2) * unit;
-        if (blocks < 2.0e9 && (best == 0 || cost < t)) {
-            best = zc;
-            t = cost;
+    for (int my : {8, 12}) {
+        const double cols = whole ? 1.0 : double((G.nx + 63) / 64) * ((G.ny + my - 1) / my);
+        const double unit = (whole ? (plane > 576 ? 7.2 : plane > 256 ? 5.4 : 5.3) : my == 8 ? 4.1 : 5.3) * (mom ? 0.5 : 1.0);
+        for (int n = 1; n <= (G.nz + 3) / 4; ++n) {
+            const int zc = (G.nz + n - 1) / n;
+            const double blocks = cols * ((G.nz + zc - 1) / zc) * G.nboxes, cost = ceil(blocks / slots) * (zc + 2) * unit;
+            if (blocks < 2.0e9 && (best == 0 || cost < t)) {
+                best = zc;
+                P.march_rows = whole ? 0 : my;
+                t = cost;
+            }
         }
     }
-    const bool rows = (long long)G.nx * 4 % 128 == 0;
-    const double lanes = whole ? double(G.ntiles) * BLOCK * (rows ? 1.0 : 1.3) : nodes;
+    const bool aligned = (long long)G.nx * 4 % 128 == 0;
+    const double lanes = whole ? double(G.ntiles) * BLOCK * (aligned ? 1.0 : 1.3) : nodes * (aligned ? 1.0 : 1.15);
     const double other = (4.0 + lanes / 40.0e3) * (mom ? 1.0 : 2.0);
-    return best > 0 && t < (mom ? 0.85 : 0.93) * other ? best : 0;
+    P.march_us = t;
+    P.other_us = other;
+    return best > 0 && t < (mom && !whole ? 0.85 : 0.93) * other ? best : 0;
 }
 
 int make_plan(const lb_params* p, Plan& P, std::string& why)
@@ -305,7 +314,9 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     if (!tile_supported(tx, ty, tz)) { why = "unsupported tile shape"; return LB_ERR_ARG; }
     P.cap = p->max_points;
     if (int r = fill_geometry(p, P.variant, P.cap, tx, ty, tz, P.Gp, why)) return r;
-    P.march = p->tile_x == 0 && p->variant == 0 ? choose_march(p, P.Gp) : 0;
+    P.march_us = P.other_us = 0.0;
+    P.march_rows = 0;
+    P.march = p->tile_x == 0 && p->variant == 0 ? choose_march(p, P) : 0;
     std::string none;
     int mx, my;
     march_tile(p->nx, p->ny, mx, my);
@@ -482,19 +493,20 @@ bool has_kind(const lb_ctx* c, int kind)
 }
 
 // Whether the marching kernels take the steps of the registered sets: two FP32 steps per launch where no point
-// moves, moment storage with any sets, but with moving ones, whose forces and velocities cost two launches more a
-// step, only whole planes and large lattices.  Up to the bound of choose_march they gain with any number of
-// points, spread out or in one place (us per step, other kernels -> marching; fixed points: FP32 256^3 with
-// 16000 425 -> 279, 128^3 with 2000 57 -> 40, 512 boxes of 32^3 with 512 and their velocities 410 -> 264, all in one
-// box 411 -> 261; moment storage 128^3 with 100 56 -> 41; colloids: moment storage 256^3 with 1000 432 -> 309, 10^4 437
-// -> 389, 10^4 within 32^3 nodes 503 -> 362, 512 boxes of 24^3 with 2000 327 -> 184; left alone: 192^3 with 3000
-// 196 / 190, 6000 196 / 204, 128^3 with 500 65 / 67).
+// moves, moment storage with any sets, but with moving ones on cut planes, whose forces and velocities cost two launches
+// more a step and 10 ns a point (the other kernels: 12 us), only where that leaves a gain.  Up to the bound of
+// choose_march the others gain with any number of points, spread out or in one place (us per step, other kernels ->
+// marching; fixed points: FP32 256^3 with 16000 425 -> 279, 128^3 with 2000 57 -> 40, 512 boxes of 32^3 with 512 and their
+// velocities 410 -> 264, all in one box 411 -> 261; moment storage 128^3 with 100 56 -> 41; colloids: moment storage
+// 256^3 with 1000 432 -> 309, 10^4 437 -> 389, 10^4 within 32^3 nodes 503 -> 362, 300 x 200 x 100 with 9 197 -> 129,
+// 512 boxes of 24^3 with 2000 327 -> 184; left alone: 192^3 with 6000 196 / 204, 128^3 with 500 65 / 67).
 bool marches(const lb_ctx* c)
 {
-    if (c->P.march == 0) return false;
-    const Geom& G = c->P.Gm;
+    const Plan& P = c->P;
+    if (P.march == 0) return false;
     if (!has_kind(c, LB_COLLOIDS) && !has_kind(c, KIND_ELASTIC)) return true;
-    return c->p.storage == LB_STORAGE_MOM32 && (march_whole(G.nx, G.ny) || double(G.N) * G.nboxes >= 8.0e6);
+    if (c->p.storage != LB_STORAGE_MOM32) return false;
+    return P.march_rows == 0 || P.march_us + 23.0 + 0.01 * double(total_points(c)) < 0.93 * (P.other_us + 12.0);
 }
 
 // The geometry (tiles of the point lists) for the registered sets; called when they change, which also
@@ -682,7 +694,7 @@ void enqueue_step(lb_ctx* c, hipStream_t s, bool rebuild, bool after = false, bo
     if (c->p.storage == LB_STORAGE_MOM32 && marches(c)) {
         float* v = npts > 0 && wants_velocity(c) ? c->vel(0) : nullptr;
         if (npts > 0 && rebuild) launch_force_field(G, c->boxes(), toff, c->tlist(), c->rec(), c->field(), s);
-        launch_march(c->p.storage, G, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->field(), v, nullptr,
+        launch_march(c->p.storage, G, c->P.march_rows, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->field(), v, nullptr,
                      s, e0, e1);
         if (v) launch_partials(G, npts, c->rec(), v, nullptr, (float*)c->partial(), nullptr, s);
     } else
@@ -705,7 +717,7 @@ void enqueue_steps(lb_ctx* c, hipStream_t s, bool rebuild, int n)
         float *v0 = p0 ? c->vel(0) : nullptr, *v1 = p0 ? c->vel(1) : nullptr;
         for (int pairs = n / 4 * 2; pairs > 0; --pairs) {
             box_update(c, s, true);
-            launch_march(c->p.storage, c->P.G, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->field(), v0,
+            launch_march(c->p.storage, c->P.G, c->P.march_rows, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->field(), v0,
                          v1, s);
             if (p0) {
                 launch_partials(c->P.G, npts, c->rec(), v0, v1, p0, p1, s);

@@ -49,10 +49,10 @@ bool launch_lattice(int storage, const Geom& G, int mode, int variant, const voi
                     const unsigned long long* tin, unsigned long long* tout, hipStream_t s, hipEvent_t ev0 = nullptr,
                     hipEvent_t ev1 = nullptr);
 // marching step kernels: one step of moment storage, two steps of FP32 populations with fixed points or
-// none; zc planes per block.  march_whole: planes are taken whole; march_tile: tx x ty x 1 tiles of the point lists
+// none; zc planes per block, my rows of a plane (0: all).  march_whole: planes are taken whole; march_tile: tx x ty x 1 tiles of the point lists
 bool march_whole(int nx, int ny);
 void march_tile(int nx, int ny, int& tx, int& ty);
-void launch_march(int storage, const Geom& G, int zc, const void* src, void* dst, const BoxDev* boxes, const int* toff,
+void launch_march(int storage, const Geom& G, int my, int zc, const void* src, void* dst, const BoxDev* boxes, const int* toff,
                   const float* field, float* vel0, float* vel1, hipStream_t s, hipEvent_t ev0 = nullptr,
                   hipEvent_t ev1 = nullptr);
 void launch_partials(const Geom& G, long long n, const void* rec, const float* vel0, const float* vel1, float* part0,

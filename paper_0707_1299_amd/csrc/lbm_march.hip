@@ -15,8 +15,8 @@
 //              and pulled from LDS, where the gather from memory needs 91 values of 18 neighbours per node.
 //
 // Planes of at most 1024 nodes are taken whole (the column's neighbours wrap round inside the block); larger
-// ones are cut into MX x MY output nodes with a rim of one node, whose first step is repeated by
-// every block that shares it (29 % more of it).  A block makes zc planes and repeats one below and above.  The inner
+// ones are cut into 64 x 8 or 64 x 12 output nodes with a rim of one node, whose first step is repeated by
+// every block that shares it (29 or 20 % more of it; which one is left to the cost model).  A block makes zc planes and repeats one below and above.  The inner
 // nodes of a cut row are one wave's, the two outer columns the last wave's: loads start on a cache line, and
 // the waves of the rim skip the second half (256^3: 297 -> 268 us a step, moment storage 307 -> 258, against threads
 // in the order of the 66 x 10 nodes; cuts of 32 x 8 or 32 x 16, two blocks per compute unit, 387 and 430).
@@ -49,9 +49,7 @@ namespace {
 
 enum Kind { KIND_PAIR = 0, KIND_MOM = 1 };
 
-constexpr int MX = 64, MY = 8;             // output nodes of a block and plane where planes are cut
-constexpr int EX = MX + 2, EY = MY + 2;    // ... with the rim
-constexpr int NE_CUT = EX * EY;
+constexpr int MX = 64, EX = MX + 2;        // output nodes of a block along x where planes are cut, ... with the rim
 constexpr int NE_MAX = 1024;               // nodes of the largest plane taken whole
 constexpr int LY = 2, LX = 6;              // point-list tiles of cut planes: 64 x 4 x 1 nodes (base-2 logarithms)
 constexpr unsigned NOWHERE = 1u << 31;     // offset past every descriptor's range: loads give 0, stores are dropped
@@ -77,9 +75,12 @@ struct MarchArgs {
     float *vel0, *vel1;            // velocity of the (first, second) step there, or NULL
 };
 
-template <int KIND, int COLL, int NE, bool CUT, bool LISTS>
+// NE nodes of a block and plane; MY: output rows of a cut plane (0: planes taken whole)
+template <int KIND, int COLL, int NE, int MY, bool LISTS>
 __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, const MarchArgs A)
 {
+    constexpr bool CUT = MY > 0;
+    constexpr int EY = MY + 2;
     constexpr int NV = KIND == KIND_PAIR ? NQ : MP_N;   // values a thread loads per plane
     __shared__ float pops[NP][NE];
 
@@ -149,23 +150,22 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
         }
     };
 
-    // The list tiles the block needs, one per lane (the same in every wave): those of its output nodes (own0, own1,
-    // or all of a whole plane) and, where the first of two steps collides the rim too, those around them.
+    // The list tiles the block needs, one per lane (the same in every wave): those of its output nodes (all of a whole
+    // plane) and, where the first of two steps collides the rim too, those around them.
     auto tile_of = [&](int px, int py) { return CUT ? (py >> LY) * G.ntx + (px >> LX) : py >> G.lty; };
-    const int own0 = tile_of(x0, y0);
-    const int own1 = CUT && (y0 >> LY) + 1 < G.nty ? own0 + G.ntx : own0;
+    constexpr int TW = KIND == KIND_PAIR ? 3 : 1, TN = CUT ? TW * ((MY >> LY) + TW - 1) : 0;
+    static_assert(MY % (1 << LY) == 0 && TN <= 16, "list tiles of a block");
     int mytile = -1;
     if constexpr (!CUT) {
         if (lane < G.nty) mytile = lane;           // a tile spans the rows
-    } else if constexpr (KIND == KIND_MOM) {
-        if (lane == 0 || (lane == 1 && own1 != own0)) mytile = lane == 0 ? own0 : own1;
     } else {
-        if (lane < 12) {
-            const int tx = ((x0 >> LX) + lane % 3 - 1 + G.ntx) % G.ntx, ty = ((y0 >> LY) + lane / 3 - 1 + G.nty) % G.nty;
+        if (lane < TN) {
+            const int tx = ((x0 >> LX) + lane % TW - TW / 2 + G.ntx) % G.ntx;
+            const int ty = ((y0 >> LY) + lane / TW - TW / 2 + G.nty) % G.nty;
             mytile = ty * G.ntx + tx;
         }
-        for (int l = 0; l < 11; ++l)               // a tile met twice round a narrow box counts once
-            if (lane > l && lane < 12 && mytile == __builtin_amdgcn_readlane(mytile, l)) mytile = -1;
+        for (int l = 0; l < TN - 1; ++l)           // a tile met twice round a narrow box counts once
+            if (lane > l && lane < TN && mytile == __builtin_amdgcn_readlane(mytile, l)) mytile = -1;
     }
     // the lane that has the thread's own tile (one without any where the block does not need it)
     const int nodetile = tile_of(x, y);
@@ -398,14 +398,13 @@ void march_tile(int nx, int ny, int& tx, int& ty)
     ty = BLOCK / tx;
 }
 
-void launch_march(int storage, const Geom& G, int zc, const void* src, void* dst, const BoxDev* boxes, const int* toff,
+void launch_march(int storage, const Geom& G, int my, int zc, const void* src, void* dst, const BoxDev* boxes, const int* toff,
                   const float* field, float* vel0, float* vel1, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
-    const bool whole = march_whole(G.nx, G.ny);
     MarchArgs A;
     A.zc = zc;
-    A.nbx = whole ? 1 : (G.nx + MX - 1) / MX;
-    A.nby = whole ? 1 : (G.ny + MY - 1) / MY;
+    A.nbx = my == 0 ? 1 : (G.nx + MX - 1) / MX;
+    A.nby = my == 0 ? 1 : (G.ny + my - 1) / my;
     A.nchunk = (G.nz + zc - 1) / zc;
     A.src = (const float*)src;
     A.dst = (float*)dst;
@@ -426,10 +425,11 @@ void launch_march(int storage, const Geom& G, int zc, const void* src, void* dst
     auto by_size = [&](auto kind, auto coll, auto lists) {
         constexpr int KIND = decltype(kind)::value, COLL = decltype(coll)::value;
         constexpr bool LISTS = decltype(lists)::value;
-        if (!whole) go(k_march<KIND, COLL, NE_CUT, true, LISTS>, NE_CUT);
-        else if (n <= 256) go(k_march<KIND, COLL, 256, false, LISTS>, n);
-        else if (n <= 576) go(k_march<KIND, COLL, 576, false, LISTS>, n);
-        else go(k_march<KIND, COLL, NE_MAX, false, LISTS>, n);
+        if (my == 8) go(k_march<KIND, COLL, EX * 10, 8, LISTS>, EX * 10);
+        else if (my == 12) go(k_march<KIND, COLL, EX * 14, 12, LISTS>, EX * 14);
+        else if (n <= 256) go(k_march<KIND, COLL, 256, 0, LISTS>, n);
+        else if (n <= 576) go(k_march<KIND, COLL, 576, 0, LISTS>, n);
+        else go(k_march<KIND, COLL, NE_MAX, 0, LISTS>, n);
     };
     auto by_kind = [&](auto lists) {
         using std::integral_constant;
