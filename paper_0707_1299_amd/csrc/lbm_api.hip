@@ -62,7 +62,7 @@ struct Layout {
     size_t pop[2], boxes, rec, psum, count, cursor, toff, bsum, tlist, tlist_tmp, partial, fpart, pmax, tmax, smax, ticket,
         tctr,
         err, nf, rebin, rebox, win,
-        diag, diagout, field, vel[2];
+        diag, diagout, field, vel[2], groups;
     size_t total;
 };
 
@@ -358,6 +358,7 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     L.diagout = take(sizeof(double) * LBD_N * p->nboxes);
     // the marching kernels' force density and velocities (of one step or two) near points
     const size_t field = P.march > 0 && P.cap > 0 ? sizeof(float) * 3 * G.N * p->nboxes : 0;
+    L.groups = take(field ? sizeof(unsigned) * P.Gm.ntiles : 0);
     L.field = take(field);
     L.vel[0] = take(field);
     L.vel[1] = take(p->storage == LB_STORAGE_FP32 ? field : 0);
@@ -451,6 +452,7 @@ struct lb_ctx {
     int4* win() const { return (int4*)(ws + P.L.win); }
     double* diag() const { return (double*)(ws + P.L.diag); }
     double* diagout() const { return (double*)(ws + P.L.diagout); }
+    unsigned* groups() const { return (unsigned*)(ws + P.L.groups); }
     float* field() const { return (float*)(ws + P.L.field); }
     float* vel(int k) const { return (float*)(ws + P.L.vel[k]); }
 };
@@ -693,8 +695,8 @@ void enqueue_step(lb_ctx* c, hipStream_t s, bool rebuild, bool after = false, bo
     const int* toff = npts > 0 ? c->toff() : nullptr;
     if (c->p.storage == LB_STORAGE_MOM32 && marches(c)) {
         float* v = npts > 0 && wants_velocity(c) ? c->vel(0) : nullptr;
-        if (npts > 0 && rebuild) launch_force_field(G, c->boxes(), toff, c->tlist(), c->rec(), c->field(), s);
-        launch_march(c->p.storage, G, c->P.march_rows, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->field(), v, nullptr,
+        if (npts > 0 && rebuild) launch_force_field(G, c->boxes(), toff, c->tlist(), c->rec(), c->groups(), c->field(), s);
+        launch_march(c->p.storage, G, c->P.march_rows, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->groups(), c->field(), v, nullptr,
                      s, e0, e1);
         if (v) launch_partials(G, npts, c->rec(), v, nullptr, (float*)c->partial(), nullptr, s);
     } else
@@ -717,7 +719,7 @@ void enqueue_steps(lb_ctx* c, hipStream_t s, bool rebuild, int n)
         float *v0 = p0 ? c->vel(0) : nullptr, *v1 = p0 ? c->vel(1) : nullptr;
         for (int pairs = n / 4 * 2; pairs > 0; --pairs) {
             box_update(c, s, true);
-            launch_march(c->p.storage, c->P.G, c->P.march_rows, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->field(), v0,
+            launch_march(c->p.storage, c->P.G, c->P.march_rows, c->P.march, c->pop(c->cur), c->pop(c->cur ^ 1), c->boxes(), toff, c->groups(), c->field(), v0,
                          v1, s);
             if (p0) {
                 launch_partials(c->P.G, npts, c->rec(), v0, v1, p0, p1, s);
@@ -1039,7 +1041,7 @@ int lb_step(lb_ctx* c, int32_t nsteps)
         box_update(c, c->stream, false);
         if (pts && marches(c) && !c->field_valid &&
             (c->p.storage == LB_STORAGE_MOM32 || (left >= 4 && !c->timing))) {
-            launch_force_field(c->P.G, c->boxes(), c->toff(), c->tlist(), c->rec(), c->field(), c->stream);
+            launch_force_field(c->P.G, c->boxes(), c->toff(), c->tlist(), c->rec(), c->groups(), c->field(), c->stream);
             c->field_valid = true;
         }
     }

@@ -272,6 +272,18 @@ __device__ __forceinline__ float wave_max_nonneg(float v)
     return __uint_as_float(unsigned(__builtin_amdgcn_readlane(int(u), 63)));
 }
 
+// Bitwise or over the wave (the same steps; lanes without a source take zero).
+__device__ __forceinline__ unsigned wave_or(unsigned u)
+{
+    u |= unsigned(__builtin_amdgcn_update_dpp(0, int(u), 0x111, 0xf, 0xf, true));
+    u |= unsigned(__builtin_amdgcn_update_dpp(0, int(u), 0x112, 0xf, 0xf, true));
+    u |= unsigned(__builtin_amdgcn_update_dpp(0, int(u), 0x114, 0xf, 0xf, true));
+    u |= unsigned(__builtin_amdgcn_update_dpp(0, int(u), 0x118, 0xf, 0xf, true));
+    u |= unsigned(__builtin_amdgcn_update_dpp(0, int(u), 0x142, 0xa, 0xf, false));
+    u |= unsigned(__builtin_amdgcn_update_dpp(0, int(u), 0x143, 0xc, 0xf, false));
+    return unsigned(__builtin_amdgcn_readlane(int(u), 63));
+}
+
 // Peskin's 4-point kernel at the four nodes floor(r)-1 .. floor(r)+2 for a
 // point at fractional offset f = r - floor(r) in [0, 1): Eq. deltadef at
 // distances 1+f, f, 1-f, 2-f, which share the root q = sqrt(1 + 4f - 4f^2).

@@ -53,12 +53,12 @@ bool launch_lattice(int storage, const Geom& G, int mode, int variant, const voi
 bool march_whole(int nx, int ny);
 void march_tile(int nx, int ny, int& tx, int& ty);
 void launch_march(int storage, const Geom& G, int my, int zc, const void* src, void* dst, const BoxDev* boxes, const int* toff,
-                  const float* field, float* vel0, float* vel1, hipStream_t s, hipEvent_t ev0 = nullptr,
+                  const unsigned* groups, const float* field, float* vel0, float* vel1, hipStream_t s, hipEvent_t ev0 = nullptr,
                   hipEvent_t ev1 = nullptr);
 void launch_partials(const Geom& G, long long n, const void* rec, const float* vel0, const float* vel1, float* part0,
                      float* part1, hipStream_t s);
-void launch_force_field(const Geom& G, const BoxDev* boxes, const int* toff, const int* tlist, const void* rec, float* field,
-                        hipStream_t s);
+void launch_force_field(const Geom& G, const BoxDev* boxes, const int* toff, const int* tlist, const void* rec, unsigned* groups,
+                        float* field, hipStream_t s);
 void launch_equilibrium(int storage, const Geom& G, void* dst, const BoxDev* boxes, const double* rho,
                         const double* u, hipStream_t s);
 

@@ -71,7 +71,8 @@ struct MarchArgs {
     float* dst;
     const BoxDev* boxes;
     const int* toff;
-    const float* field;            // force density, [box][z][y][component][x], where the lists have points
+    const unsigned* groups;        // per list tile: which of its 32 groups of eight nodes along x points reach
+    const float* field;            // force density, [box][z][y][component][x], in those groups
     float *vel0, *vel1;            // velocity of the (first, second) step there, or NULL
 };
 
@@ -173,38 +174,46 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
     for (int l = 0; l < 16; ++l)
         if (__builtin_amdgcn_readlane(mytile, l) == nodetile) slot = l;
 
+    const int group = CUT ? ((y & ((1 << LY) - 1)) << LX | (x & ((1 << LX) - 1))) >> 3
+                          : ((y & (G.ty - 1)) << G.ltx | x) >> 3;
+
     struct List {
         int a, c;        // this lane's tile: entries a .. c - 1
+        unsigned g;      // ... and the groups of nodes they reach, if there are any
     };
     const rsrc_t rtoff = plane_rsrc(A.toff, A.toff ? unsigned(G.ntiles + 1) * 4u : 0u);
+    const rsrc_t rgroups = plane_rsrc(A.groups, A.toff ? unsigned(G.ntiles) * 4u : 0u);
     const unsigned tiles_at = mytile >= 0 ? unsigned(mytile) * 4u : NOWHERE;
     auto entries = [&](int k) {                    // of plane z0 + k (none past the last plane)
         typedef int i32x2 __attribute__((ext_vector_type(2)));
         const unsigned first = unsigned((box * G.ntz + plane(z0 + k)) * G.nty * G.ntx) * 4u;
-        const i32x2 v = __builtin_bit_cast(
-            i32x2, __builtin_amdgcn_raw_buffer_load_b64(rtoff, tiles_at | (k <= nzc ? 0u : NOWHERE), first, 0));
-        return List{v.x, v.y};
+        const unsigned at = tiles_at | (k <= nzc ? 0u : NOWHERE);
+        const i32x2 v = __builtin_bit_cast(i32x2, __builtin_amdgcn_raw_buffer_load_b64(rtoff, at, first, 0));
+        return List{v.x, v.y, bload<unsigned, 0>(rgroups, at, first)};
     };
-    auto listed = [](const List& l) { return __ballot(l.c > l.a); };
-    // the force field and the velocities at the thread's node of plane z0 + k, if its tile is among the listed
+    // the lanes whose nodes points reach
+    auto reached = [&](const List& l) {
+        return __ballot((unsigned(__shfl(int(l.c > l.a ? l.g : 0u), slot)) >> group & 1u) != 0);
+    };
+    // the force field and the velocities at the thread's node of plane z0 + k, if points reach it
     const unsigned frow = unsigned(G.nx) * 4u, fsize = unsigned(G.ny) * 3u * frow;
     const unsigned fown = unsigned(y) * 3u * frow + unsigned(x) * 4u;
     auto field_plane = [&](const float* f, int k) {
         return plane_rsrc(reinterpret_cast<const char*>(f) + (unsigned long long)(box * G.nz + plane(z0 + k)) * fsize, fsize);
     };
-    auto mine = [&](unsigned long long tiles) { return unsigned(tiles >> slot) & 1u; };
+    auto mine = [&](unsigned long long lanes) { return unsigned(lanes >> lane) & 1u; };
     // (offsets past the range by a bit, not by a choice: the compiler makes a branch of a choice, and with it
     // vector registers of what both sides compute)
-    auto force = [&](int k, unsigned long long tiles, float (&g)[3]) {
+    auto force = [&](int k, unsigned long long lanes, float (&g)[3]) {
         const rsrc_t r = field_plane(A.field, k);
-        const unsigned at = fown | ((mine(tiles) ^ 1u) << 31);
+        const unsigned at = fown | ((mine(lanes) ^ 1u) << 31);
 #pragma unroll
         for (int q = 0; q < 3; ++q) g[q] = bload<float, 0>(r, at, unsigned(q) * frow);
     };
-    auto keep = [&](float* vel, int k, unsigned long long tiles, const float (&u)[3]) {
-        if (!vel || tiles == 0) return;
+    auto keep = [&](float* vel, int k, unsigned long long lanes, const float (&u)[3]) {
+        if (!vel || lanes == 0) return;
         const rsrc_t r = field_plane(vel, k);
-        const unsigned at = fown | ((mine(tiles) ^ 1u) << 31) | (out ? 0u : NOWHERE);
+        const unsigned at = fown | ((mine(lanes) ^ 1u) << 31) | (out ? 0u : NOWHERE);
 #pragma unroll
         for (int q = 0; q < 3; ++q) bstore<float, 0>(u[q], r, at, unsigned(q) * frow);
     };
@@ -215,12 +224,12 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
 #pragma unroll
     for (int i = 0; i < NQ; ++i) lev[i] = up1[i] = up2[i] = 0.0f;
     bool bad = false;
-    // tiles with points of plane k - 1 (m1) and k (m0); la: the lists of plane k + 1
-    List la{0, 0};
+    // lanes whose nodes points reach in plane k - 1 (m1) and k (m0); la: the lists of plane k + 1
+    List la{0, 0, 0};
     unsigned long long m0 = 0, m1 = 0;
     float gn[3];                               // the next plane's force density
     if constexpr (LISTS) {
-        m0 = listed(entries(-1));
+        m0 = reached(entries(-1));
         la = entries(0);
         force(-1, m0, gn);
     }
@@ -244,7 +253,7 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
             // plane k + 1's forces and plane k + 2's lists, the same loads in every iteration
 #pragma unroll
             for (int q = 0; q < 3; ++q) g[q] = mine(m0) ? gn[q] : gc[q];
-            ma = listed(la);
+            ma = reached(la);
             la = entries(k + 2);
             force(k + 1, ma, gn);
         }
@@ -322,15 +331,18 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
 
 }  // namespace
 
-// Force density (counter-force and points, the sums of the single-step kernel, in its order) at the nodes of list
-// tiles that have points, for the marching kernels.  A block looks through FT tiles, one per lane, and takes those
-// that have any with all its threads, a node each.  Their entries are consecutive in the lists; the records are staged
-// in LDS, RPT at a time, so that a tile waits for one chain of loads and not for one per point.
+// Force density (counter-force and points, the sums of the single-step kernel, in its order) near points, for the
+// marching kernels.  A block looks through FT tiles, one per lane, and takes those that have any with all its threads, a
+// node each.  Their entries are consecutive in the lists; the records are staged in LDS, RPT at a time, so that a tile
+// waits for one chain of loads and not for one per point.  Of a tile's 256 nodes only the groups of eight along x that a
+// stencil reaches are written (and read): a tenth of them where points are spread out (256^3, FP32, 10^4 points and their
+// velocities 317 -> 297 us a step, 512 boxes of 32^3 with 5900 298 -> 277, 10^4 colloids with moment storage 390 -> 383).
 constexpr int FT = 4, RW = int(sizeof(PRec<float>) / 16), RPT = BLOCK / RW;
 
 __global__ __launch_bounds__(BLOCK) void k_force_field(const Geom G, const BoxDev* __restrict__ boxes,
                                                        const int* __restrict__ toff, const int* __restrict__ tlist,
-                                                       const PRec<float>* __restrict__ rec, float* __restrict__ field)
+                                                       const PRec<float>* __restrict__ rec, unsigned* __restrict__ groups,
+                                                       float* __restrict__ field)
 {
     __shared__ uint4 sraw[RPT * RW];
     const PRec<float>* staged = reinterpret_cast<const PRec<float>*>(sraw);
@@ -350,6 +362,7 @@ __global__ __launch_bounds__(BLOCK) void k_force_field(const Geom G, const BoxDe
         const int x = (tx << G.ltx) + (threadIdx.x & (G.tx - 1)), y = (ty << G.lty) + (threadIdx.x >> G.ltx);
         const BoxDev& B = boxes[box];
         float g[3] = {float(B.gc[0]), float(B.gc[1]), float(B.gc[2])};
+        unsigned near = 0;
         for (int k = __builtin_amdgcn_readlane(a, l), k1 = __builtin_amdgcn_readlane(c, l); k < k1;) {
             if (k >= s1) {
                 s0 = k;
@@ -369,6 +382,18 @@ __global__ __launch_bounds__(BLOCK) void k_force_field(const Geom G, const BoxDe
                 if (dy < 0) dy += G.ny;
                 if (dz < 0) dz += G.nz;
                 hit = dz <= 3 && (dy <= 3 || G.tx < 64);
+                unsigned row = 0;                  // groups of a row
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int sx = h.x + i - (h.x + i >= G.nx ? G.nx : 0);
+                    row |= unsigned(sx >> G.ltx == tx) << ((sx & (G.tx - 1)) >> 3);
+                }
+                if (dz > 3) row = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int sy = h.y + j - (h.y + j >= G.ny ? G.ny : 0);
+                    near |= (sy >> G.lty == ty ? row : 0u) << ((sy & (G.ty - 1)) << (G.ltx - 3));
+                }
             }
             for (unsigned long long q = __ballot(hit); q; q &= q - 1) {
                 const int p = __ffsll(q) - 1;
@@ -377,17 +402,19 @@ __global__ __launch_bounds__(BLOCK) void k_force_field(const Geom G, const BoxDe
             }
             k += n;
         }
-        if (x >= G.nx || y >= G.ny) continue;
+        near = wave_or(near);
+        if (threadIdx.x == 0) groups[t] = near;
+        if (x >= G.nx || y >= G.ny || !(near >> (threadIdx.x >> 3) & 1u)) continue;
         float* f = field + (((long long)box * G.nz + z) * G.ny + y) * 3 * G.nx + x;
         for (int q = 0; q < 3; ++q) f[q * G.nx] = g[q];
     }
 }
 
-void launch_force_field(const Geom& G, const BoxDev* boxes, const int* toff, const int* tlist, const void* rec, float* field,
-                        hipStream_t s)
+void launch_force_field(const Geom& G, const BoxDev* boxes, const int* toff, const int* tlist, const void* rec, unsigned* groups,
+                        float* field, hipStream_t s)
 {
     hipLaunchKernelGGL(k_force_field, dim3((unsigned)((G.ntiles + FT - 1) / FT)), dim3(BLOCK), 0, s, G, boxes, toff, tlist,
-                       (const PRec<float>*)rec, field);
+                       (const PRec<float>*)rec, groups, field);
 }
 
 bool march_whole(int nx, int ny) { return nx <= 64 && ny <= 64 && nx * ny <= NE_MAX; }
@@ -399,7 +426,7 @@ void march_tile(int nx, int ny, int& tx, int& ty)
 }
 
 void launch_march(int storage, const Geom& G, int my, int zc, const void* src, void* dst, const BoxDev* boxes, const int* toff,
-                  const float* field, float* vel0, float* vel1, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
+                  const unsigned* groups, const float* field, float* vel0, float* vel1, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
     MarchArgs A;
     A.zc = zc;
@@ -410,6 +437,7 @@ void launch_march(int storage, const Geom& G, int my, int zc, const void* src, v
     A.dst = (float*)dst;
     A.boxes = boxes;
     A.toff = toff;
+    A.groups = groups;
     A.field = field;
     A.vel0 = vel0;
     A.vel1 = vel1;
