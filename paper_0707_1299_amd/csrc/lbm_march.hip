@@ -332,88 +332,168 @@ __global__ __launch_bounds__((NE + 63) / 64 * 64) void k_march(const Geom G, con
 }  // namespace
 
 // Force density (counter-force and points, the sums of the single-step kernel, in its order) near points, for the
-// marching kernels.  A block looks through FT tiles, one per lane, and takes those that have any with all its threads, a
-// node each.  Their entries are consecutive in the lists; the records are staged in LDS, RPT at a time, so that a tile
-// waits for one chain of loads and not for one per point.  Of a tile's 256 nodes only the groups of eight along x that a
-// stencil reaches are written (and read): a tenth of them where points are spread out (256^3, FP32, 10^4 points and their
-// velocities 317 -> 297 us a step, 512 boxes of 32^3 with 5900 298 -> 277, 10^4 colloids with moment storage 390 -> 383).
-constexpr int FT = 4, RW = int(sizeof(PRec<float>) / 16), RPT = BLOCK / RW;
+// marching kernels.  Of a tile's 256 nodes only the groups of eight along x that a stencil reaches are written (and read): a
+// tenth of them where points are spread out (256^3, FP32, 10^4 points and their velocities 317 -> 297 us a step, 512 boxes
+// of 32^3 with 5900 298 -> 277).  A wave looks through FT tiles, one per lane; their entries are consecutive in the lists.
+// Where they are few (WPT), the wave fetches all their records at once and takes the reached groups of each tile, eight at a
+// time, a node per lane: two chains of loads for FT tiles (256^3 with 10^4 colloids and moment storage 383 -> 343 us a
+// step against a block per FT tiles; FT = 8 352).  Where they are many, the block takes the tiles one by one, a node
+// per thread, with the records staged RPT at a time.  (The waves of a block have tiles far apart, so that points in one
+// place are many blocks'.)
+constexpr int FT = 4, RW = int(sizeof(PRec<float>) / 16), RPT = BLOCK / RW, WPT = 128 / RW;
+
+// the groups of tile (tx, ty) that a stencil starting at (bx, by) reaches
+__device__ __forceinline__ unsigned stencil_groups(const Geom& G, int bx, int by, int tx, int ty)
+{
+    unsigned row = 0, near = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int sx = bx + i - (bx + i >= G.nx ? G.nx : 0);
+        row |= unsigned(sx >> G.ltx == tx) << ((sx & (G.tx - 1)) >> 3);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int sy = by + j - (by + j >= G.ny ? G.ny : 0);
+        near |= (sy >> G.lty == ty ? row : 0u) << ((sy & (G.ty - 1)) << (G.ltx - 3));
+    }
+    return near;
+}
 
 __global__ __launch_bounds__(BLOCK) void k_force_field(const Geom G, const BoxDev* __restrict__ boxes,
                                                        const int* __restrict__ toff, const int* __restrict__ tlist,
                                                        const PRec<float>* __restrict__ rec, unsigned* __restrict__ groups,
                                                        float* __restrict__ field)
 {
+    constexpr int NW = BLOCK / 64;
     __shared__ uint4 sraw[RPT * RW];
-    const PRec<float>* staged = reinterpret_cast<const PRec<float>*>(sraw);
-    const long long first = (long long)blockIdx.x * FT;
-    const int lane = threadIdx.x & 63, sp = int(threadIdx.x) / RW, sw = int(threadIdx.x) - sp * RW;
+    __shared__ uint4 wraw[NW][128];
+    __shared__ int many[NW];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    auto first_of = [&](int w) { return ((long long)w * gridDim.x + blockIdx.x) * FT; };
+    struct Tile {
+        int tx, ty, z, box;
+    };
+    auto tile_at = [&](unsigned t) {
+        return Tile{int(t % G.ntx), int(t / G.ntx % G.nty), int(t / unsigned(G.ntx * G.nty) % G.ntz),
+                    int(t / G.tiles_per_box)};
+    };
+    auto reaches = [&](int z, int bz) {
+        const int dz = z - bz + (z < bz ? G.nz : 0);
+        return dz <= 3;
+    };
+    auto store = [&](const Tile& T, int x, int y, const float (&g)[3]) {
+        float* f = field + (((long long)T.box * G.nz + T.z) * G.ny + y) * 3 * G.nx + x;
+        for (int q = 0; q < 3; ++q) f[q * G.nx] = g[q];
+    };
+
+    // the wave's tiles
+    const long long first = first_of(wave);
     const bool has = lane < FT && first + lane < G.ntiles;
     const int a = has ? toff[first + lane] : 0, c = has ? toff[first + lane + 1] : 0;
     const unsigned long long tiles = __ballot(c > a);
-    if (tiles == 0) return;
-    const int end = __builtin_amdgcn_readlane(c, 63 - __builtin_clzll(tiles));   // past the last tile's entries
-    int s0 = 0, s1 = 0;                                                        // entries staged
-    for (unsigned long long m = tiles; m; m &= m - 1) {
-        const int l = __ffsll(m) - 1;
-        const unsigned t = unsigned(first + l);
-        const int tx = int(t % G.ntx), ty = int(t / G.ntx % G.nty), box = int(t / G.tiles_per_box);
-        const int z = int(t / unsigned(G.ntx * G.nty) % G.ntz);
-        const int x = (tx << G.ltx) + (threadIdx.x & (G.tx - 1)), y = (ty << G.lty) + (threadIdx.x >> G.ltx);
-        const BoxDev& B = boxes[box];
-        float g[3] = {float(B.gc[0]), float(B.gc[1]), float(B.gc[2])};
-        unsigned near = 0;
-        for (int k = __builtin_amdgcn_readlane(a, l), k1 = __builtin_amdgcn_readlane(c, l); k < k1;) {
-            if (k >= s1) {
-                s0 = k;
-                s1 = min(k + RPT, end);
-                __syncthreads();   // every wave has read the records before
-                if (sp < s1 - s0)
-                    sraw[threadIdx.x] = reinterpret_cast<const uint4*>(rec + pk_point(tlist[s0 + sp]))[sw];
-                __syncthreads();
-            }
-            // a lane looks at each staged point: those that reach the plane (and the row, where a wave has one) are added
-            const int n = min(k1, s1) - k;
-            int4 h{};
-            bool hit = false;
-            if (lane < n) {
-                h = __builtin_bit_cast(int4, sraw[(k - s0 + lane) * RW]);
-                int dy = y - h.y, dz = z - h.z;
-                if (dy < 0) dy += G.ny;
-                if (dz < 0) dz += G.nz;
-                hit = dz <= 3 && (dy <= 3 || G.tx < 64);
-                unsigned row = 0;                  // groups of a row
+    const int e0 = tiles ? __builtin_amdgcn_readlane(a, __ffsll(tiles) - 1) : 0;
+    const int n = tiles ? __builtin_amdgcn_readlane(c, 63 - __builtin_clzll(tiles)) - e0 : 0;
+    if (lane == 0) many[wave] = n > WPT;
+    if (n > 0 && n <= WPT) {
+        const PRec<float>* staged = reinterpret_cast<const PRec<float>*>(wraw[wave]);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int sx = h.x + i - (h.x + i >= G.nx ? G.nx : 0);
-                    row |= unsigned(sx >> G.ltx == tx) << ((sx & (G.tx - 1)) >> 3);
-                }
-                if (dz > 3) row = 0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int sy = h.y + j - (h.y + j >= G.ny ? G.ny : 0);
-                    near |= (sy >> G.lty == ty ? row : 0u) << ((sy & (G.ty - 1)) << (G.ltx - 3));
-                }
-            }
-            for (unsigned long long q = __ballot(hit); q; q &= q - 1) {
-                const int p = __ffsll(q) - 1;
-                add_point(G, __builtin_amdgcn_readlane(h.x, p), __builtin_amdgcn_readlane(h.y, p),
-                          __builtin_amdgcn_readlane(h.z, p), staged[k - s0 + p], x, y, z, g[0], g[1], g[2]);
-            }
-            k += n;
+        for (int i = 0; i < 2; ++i) {
+            const int word = lane + 64 * i, sp = word / RW, sw = word - sp * RW;
+            if (sp < n) wraw[wave][word] = reinterpret_cast<const uint4*>(rec + pk_point(tlist[e0 + sp]))[sw];
         }
-        near = wave_or(near);
-        if (threadIdx.x == 0) groups[t] = near;
-        if (x >= G.nx || y >= G.ny || !(near >> (threadIdx.x >> 3) & 1u)) continue;
-        float* f = field + (((long long)box * G.nz + z) * G.ny + y) * 3 * G.nx + x;
-        for (int q = 0; q < 3; ++q) f[q * G.nx] = g[q];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        int4 h{};
+        if (lane < n) h = __builtin_bit_cast(int4, wraw[wave][lane * RW]);
+        for (unsigned long long m = tiles; m; m &= m - 1) {
+            const int l = __ffsll(m) - 1;
+            const unsigned t = unsigned(first + l);
+            const Tile T = tile_at(t);
+            const bool hit = lane >= __builtin_amdgcn_readlane(a, l) - e0 && lane < __builtin_amdgcn_readlane(c, l) - e0 &&
+                             reaches(T.z, h.z);
+            const unsigned near = wave_or(hit ? stencil_groups(G, h.x, h.y, T.tx, T.ty) : 0u);
+            const unsigned long long hits = __ballot(hit);
+            if (lane == 0) groups[t] = near;
+            const BoxDev& B = boxes[T.box];
+            for (unsigned left = near; left;) {
+                // lane -> node of the eight next groups
+                int group = -1;
+                for (int j = 0; j < 8 && left; ++j, left &= left - 1)
+                    if (lane >> 3 == j) group = __ffs(left) - 1;
+                const int node = max(group, 0) * 8 + (lane & 7);
+                const int x = (T.tx << G.ltx) + (node & (G.tx - 1)), y = (T.ty << G.lty) + (node >> G.ltx);
+                float g[3] = {float(B.gc[0]), float(B.gc[1]), float(B.gc[2])};
+                for (unsigned long long q = hits; q; q &= q - 1) {
+                    const int p = __ffsll(q) - 1;
+                    add_point(G, __builtin_amdgcn_readlane(h.x, p), __builtin_amdgcn_readlane(h.y, p),
+                              __builtin_amdgcn_readlane(h.z, p), staged[p], x, y, T.z, g[0], g[1], g[2]);
+                }
+                if (group >= 0 && x < G.nx && y < G.ny) store(T, x, y, g);
+            }
+        }
+    }
+    __syncthreads();
+
+    // tiles with many entries
+    const PRec<float>* staged = reinterpret_cast<const PRec<float>*>(sraw);
+    const int sp = int(threadIdx.x) / RW, sw = int(threadIdx.x) - sp * RW;
+    for (int w = 0; w < NW; ++w) {
+        if (!many[w]) continue;
+        const long long f0 = first_of(w);
+        const bool in = lane < FT && f0 + lane < G.ntiles;
+        const int ta = in ? toff[f0 + lane] : 0, tc = in ? toff[f0 + lane + 1] : 0;
+        const unsigned long long some = __ballot(tc > ta);
+        const int end = __builtin_amdgcn_readlane(tc, 63 - __builtin_clzll(some));   // past the last tile's entries
+        int s0 = 0, s1 = 0;                                                          // entries staged
+        for (unsigned long long m = some; m; m &= m - 1) {
+            const int l = __ffsll(m) - 1;
+            const unsigned t = unsigned(f0 + l);
+            const Tile T = tile_at(t);
+            const int x = (T.tx << G.ltx) + (threadIdx.x & (G.tx - 1)), y = (T.ty << G.lty) + (threadIdx.x >> G.ltx);
+            const BoxDev& B = boxes[T.box];
+            float g[3] = {float(B.gc[0]), float(B.gc[1]), float(B.gc[2])};
+            unsigned near = 0;
+            for (int k = __builtin_amdgcn_readlane(ta, l), k1 = __builtin_amdgcn_readlane(tc, l); k < k1;) {
+                if (k >= s1) {
+                    s0 = k;
+                    s1 = min(k + RPT, end);
+                    __syncthreads();   // every wave has read the records before
+                    if (sp < s1 - s0)
+                        sraw[threadIdx.x] = reinterpret_cast<const uint4*>(rec + pk_point(tlist[s0 + sp]))[sw];
+                    __syncthreads();
+                }
+                // a lane looks at each staged point: those that reach the plane (and the row, where a wave has one)
+                // are added
+                const int np = min(k1, s1) - k;
+                int4 h{};
+                bool hit = false;
+                if (lane < np) {
+                    h = __builtin_bit_cast(int4, sraw[(k - s0 + lane) * RW]);
+                    int dy = y - h.y;
+                    if (dy < 0) dy += G.ny;
+                    hit = reaches(T.z, h.z);
+                    near |= hit ? stencil_groups(G, h.x, h.y, T.tx, T.ty) : 0u;
+                    hit = hit && (dy <= 3 || G.tx < 64);
+                }
+                for (unsigned long long q = __ballot(hit); q; q &= q - 1) {
+                    const int p = __ffsll(q) - 1;
+                    add_point(G, __builtin_amdgcn_readlane(h.x, p), __builtin_amdgcn_readlane(h.y, p),
+                              __builtin_amdgcn_readlane(h.z, p), staged[k - s0 + p], x, y, T.z, g[0], g[1], g[2]);
+                }
+                k += np;
+            }
+            near = wave_or(near);
+            if (threadIdx.x == 0) groups[t] = near;
+            if (x < G.nx && y < G.ny && (near >> (threadIdx.x >> 3) & 1u)) store(T, x, y, g);
+        }
     }
 }
 
 void launch_force_field(const Geom& G, const BoxDev* boxes, const int* toff, const int* tlist, const void* rec, unsigned* groups,
                         float* field, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_force_field, dim3((unsigned)((G.ntiles + FT - 1) / FT)), dim3(BLOCK), 0, s, G, boxes, toff, tlist,
+    hipLaunchKernelGGL(k_force_field, dim3((unsigned)((G.ntiles + FT * (BLOCK / 64) - 1) / (FT * (BLOCK / 64)))),
+                       dim3(BLOCK), 0, s, G, boxes, toff, tlist,
                        (const PRec<float>*)rec, groups, field);
 }
 
