@@ -129,6 +129,10 @@ void choose_default(const lb_params* p, int& tx, int& ty, int& tz, int& variant)
     const bool dense = double(p->max_points) * 1024.0 > N * p->nboxes;
     plain_tile(p, tx, ty, tz);
     if (fp16 && p->nboxes > 1) {
+    } else if (p->nx > 16 && p->nx < 32) {
+        tx = 32; ty = 4; tz = 2;
+    } else if (p->storage == LB_STORAGE_FP64 && p->kT > 0.0 && p->nx > 32 && (p->nx % 32 == 0 || p->nx % 32 >= 8)) {
+        tx = 32; ty = 4; tz = 2;
     } else if (mom) {
         if (p->nx >= 64) { tx = 64; ty = 4; tz = 1; }
         else if (p->nx > 32) { tx = 64; ty = 2; tz = 2; }
@@ -495,20 +499,21 @@ bool has_kind(const lb_ctx* c, int kind)
 }
 
 // Whether the marching kernels take the steps of the registered sets: two FP32 steps per launch where no point
-// moves, moment storage with any sets, but with moving ones on cut planes, whose forces and velocities cost two launches
-// more a step and 6 ns a point (the other kernels: 12 us), only where that leaves a gain.  Up to the bound of
+// moves, moment storage with any sets, but with moving ones, whose forces and velocities cost two launches more a
+// step (15 to 25 us by the planes) and 6 ns a point (the other kernels: 12 us), only where that leaves a gain.  Up to the bound of
 // choose_march the others gain with any number of points, spread out or in one place (us per step, other kernels ->
 // marching; fixed points: FP32 256^3 with 16000 425 -> 267, 128^3 with 2000 57 -> 39, 512 boxes of 32^3 with 512 and their
 // velocities 410 -> 259, all in one box 411 -> 259; moment storage 128^3 with 100 56 -> 41; colloids: moment storage
 // 256^3 with 1000 432 -> 302, 10^4 437 -> 343, 10^4 within 32^3 nodes 503 -> 372, 16000 440 -> 363, 192^3 with 6000 197 ->
-// 170, 300 x 200 x 100 with 9 197 -> 132, 512 boxes of 24^3 with 2000 327 -> 173; left alone: 128^3 with 500 65 / 67).
+// 170, 300 x 200 x 100 with 9 197 -> 132, 512 boxes of 24^3 with 2000 327 -> 173; left alone: 128^3 with 500 65 / 67, 40 boxes of 25^3 29 / 38).
 bool marches(const lb_ctx* c)
 {
     const Plan& P = c->P;
     if (P.march == 0) return false;
     if (!has_kind(c, LB_COLLOIDS) && !has_kind(c, KIND_ELASTIC)) return true;
     if (c->p.storage != LB_STORAGE_MOM32) return false;
-    return P.march_rows == 0 || P.march_us + 25.0 + 0.006 * double(total_points(c)) < 0.93 * (P.other_us + 12.0);
+    const double more = P.march_rows > 0 ? 25.0 : P.Gm.nx * P.Gm.ny > 256 ? 22.0 : 15.0;
+    return P.march_us + more + 0.006 * double(total_points(c)) < 0.93 * (P.other_us + 12.0);
 }
 
 // The geometry (tiles of the point lists) for the registered sets; called when they change, which also

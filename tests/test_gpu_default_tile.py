@@ -42,6 +42,12 @@ def _run(shape, storage, tile, kw, npts, steps=6, nboxes=1):
     ((16, 16, 16), "fp16", {}, 200, 200),                      # a batch of FP16 boxes
     ((64, 64, 96), "fp32", dict(kT=1e-5, seed=4), 9, 1),       # thermal
     ((9, 9, 9), "fp32", {}, 5, 1),
+    ((14, 18, 25), "fp64", {}, 9, 1),                          # rows of 17 .. 31 nodes
+    ((14, 18, 29), "mom32", {}, 9, 1),
+    ((14, 18, 26), "fp16", {}, 9, 1),
+    ((20, 16, 31), "fp16", {}, 9, 1),                          # one node per lane, small
+    ((20, 21, 75), "fp64", dict(kT=1e-5, seed=4), 9, 1),       # thermal, 32-node tiles
+    ((20, 21, 36), "fp64", dict(kT=1e-5, seed=4), 9, 1),       # ... the last too empty
 ])
 def test_same_fields_as_plain_tile(shape, storage, kw, npts, nboxes):
     plain = (64, 2, 2) if shape[2] >= 64 else (32, 4, 2) if shape[2] >= 32 else (16, 4, 4)
