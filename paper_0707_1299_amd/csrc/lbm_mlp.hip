@@ -282,31 +282,32 @@ __global__ __launch_bounds__(256) void k_grad(const uint16_t* __restrict__ w16, 
 }
 
 // Sums of nb partial gradients: a block takes 64 parameters, its wave w the w-th quarter of the
-// partials in order; the four quarters are then added in order.
+// partials in order; the four quarters are then added in order, all in FP64: the partials are FP32 sums of up to a few
+// hundred samples, and their sum adds one rounding.
 __global__ __launch_bounds__(256) void k_grad_sum(const float* __restrict__ part, int nb, long long n,
                                                   float* __restrict__ grad, float* __restrict__ loss)
 {
-    __shared__ float q[4][64];
+    __shared__ double q[4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, p = blockIdx.x * 64 + lane;   // p < NPART
     const int per = (nb + 3) / 4, k0 = wave * per, k1 = min(nb, k0 + per);
-    float v = 0.0f;
+    double v = 0.0;
     int k = k0;
     for (; k + 8 <= k1; k += 8) {
         float t[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) t[j] = part[NPART * (long long)(k + j) + p];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v += t[j];
+        for (int j = 0; j < 8; ++j) v += double(t[j]);
     }
-    for (; k < k1; ++k) v += part[NPART * (long long)k + p];
+    for (; k < k1; ++k) v += double(part[NPART * (long long)k + p]);
     q[wave][lane] = v;
     __syncthreads();
     if (wave != 0) return;
     v = ((q[0][lane] + q[1][lane]) + q[2][lane]) + q[3][lane];
     if (p < NP)
-        grad[p] = v;
+        grad[p] = float(v);
     else if (p == NP)
-        *loss = v / float(n);
+        *loss = float(v / double(n));
 }
 
 __global__ void k_adam(float* __restrict__ m0, float* __restrict__ m1, float* __restrict__ v1,
