@@ -138,18 +138,18 @@ void choose_default(const lb_params* p, int& tx, int& ty, int& tz, int& variant)
         else if (p->nx > 32) { tx = 64; ty = 2; tz = 2; }
     } else if (pairs) {
         if (p->nx >= 128) { tx = 128; ty = 2; tz = 1; }
-        else if (p->nx > 32 && p->nx < 64) { tx = 64; ty = 2; tz = 2; }
+        else if (p->nx > 32 && p->nx < 64 && !(dense && general)) { tx = 64; ty = 2; tz = 2; }
     } else if (p->nx > 64 && p->nx <= 128 && !dense && !(p->kT > 0.0)) {
         tx = 128; ty = 2; tz = 1;
     } else if (p->storage == LB_STORAGE_FP32 && p->nx >= 192 && !dense && !general &&
                3 * ((p->nx + 255) / 256 * 256) <= 4 * p->nx) {
         tx = 256; ty = 1; tz = 1;
-    } else if (p->nx > 32 && p->nx < 64) {
+    } else if (p->nx > 32 && p->nx < 64 && !(dense && general)) {
         tx = 64; ty = 2; tz = 2;
     }
     const bool aligned = (long long)(p->nx * esz) % 128 == 0, narrow = !aligned && p->nx < 32;
     if (copies <= (narrow ? 48.0e6 : 70.0e6)) {
-        variant = fp16 && !pairs && p->nx < 64 ? 2 : 128;
+        variant = fp16 && !pairs && !general && p->nx < 64 ? 2 : 128;
         if (copies <= 9.0e6) variant |= 2;
     } else {
         const double plane = double(p->nx) * p->ny * planes * esz;
