@@ -317,7 +317,14 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     }
     if (!tile_supported(tx, ty, tz)) { why = "unsupported tile shape"; return LB_ERR_ARG; }
     P.cap = p->max_points;
-    if (int r = fill_geometry(p, P.variant, P.cap, tx, ty, tz, P.Gp, why)) return r;
+    int r = fill_geometry(p, P.variant, P.cap, tx, ty, tz, P.Gp, why);
+    if (r && p->tile_x <= 0 && p->variant == 0) {
+        // choose_default goes by speed; what its tile does not serve (a box of 4 GiB and more on narrow rows of lanes,
+        // rows of 256 k + 1 ... 3 nodes on 256-node tiles, whose windows meet 75 tiles) takes the plain tile
+        P.variant = 0;
+        r = fill_geometry(p, 0, P.cap, P.plain[0], P.plain[1], P.plain[2], P.Gp, why);
+    }
+    if (r) return r;
     P.march_us = P.other_us = 0.0;
     P.march_rows = 0;
     P.march = p->tile_x == 0 && p->variant == 0 ? choose_march(p, P) : 0;

@@ -1,0 +1,27 @@
+"""The library's own choice of tile on the host (no GPU): what the plain tile takes (64 x 2 x 2, 32 x 4 x 2, 16 x 4 x 4, or 128
+nodes along x for boxes of 4 GiB and more) is not refused because another tile would be faster for sizes like it."""
+import pytest
+
+lbm = pytest.importorskip("paper_0707_1299_amd.lbm", reason="liblbm.so not built")
+
+
+@pytest.mark.parametrize("shape,storage,kw", [
+    # boxes of 4 GiB and more: tiles with fewer than 64 lanes along x cannot address them
+    ((320, 320, 320), "fp64", dict(kT=1e-5)),
+    ((384, 384, 384), "fp64", dict(kT=1e-5)),
+    ((200, 400, 512), "fp64", dict(kT=1e-5, max_points=1000)),
+    ((1500, 1500, 31), "fp32", {}),
+    ((1600, 1600, 24), "fp32", dict(kT=1e-5)),
+    ((2600, 2000, 24), "mom32", {}),
+    ((1400, 1400, 60), "fp16", {}),
+    ((1300, 2000, 48), "fp16", {}),
+    # a last 256-node tile of one to three nodes: a point's window would meet 3 x 5 x 5 tiles, more than 64
+    ((16, 16, 769), "fp32", {}),
+    ((16, 16, 771), "fp32", dict(max_points=10)),
+    ((32, 16, 1026), "fp32", {}),
+    ((16, 16, 1283), "fp32", {}),
+])
+def test_what_the_plain_tile_takes_is_accepted(shape, storage, kw):
+    assert lbm.lb_workspace_bytes(lbm.make_params(shape, storage, **kw)) > 0
+    # a larger lattice takes no less
+    assert lbm.lb_workspace_bytes(lbm.make_params((shape[0] + 4,) + shape[1:], storage, **kw)) > 0
