@@ -333,6 +333,9 @@ int lb_sync(lb_ctx* ctx);
  * run then continues bit for bit as the uninterrupted run would.
  * lb_checkpoint_save needs the registered points to have been binned (a step,
  * or lb_moments, since the sets last changed): LB_ERR_STATE otherwise.
+ * A checkpoint names the tile the caller named, or the plain one of the box for a
+ * caller who named none (whatever tile the library chose: it also goes by noise,
+ * max_points and the registered sets, which may differ).
  * lb_checkpoint_load waits for the stream, checks the saved header against
  * the context (LB_ERR_ARG on a mismatch) and sets lb_steps_taken to the saved
  * count.

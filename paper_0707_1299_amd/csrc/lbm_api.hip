@@ -76,11 +76,13 @@ struct Plan {
     int march_rows;    // ... and rows of a plane (0: all)
     double march_us, other_us;   // estimated time of a step without points: marching, other kernels (moment storage)
     int variant;       // the step kernel's variant bits (the caller's, or choose_default's)
-    int plain[3];      // a second tile whose checkpoints are accepted: plain_tile's, for a caller who named none
+    int plain[3];      // the tile that checkpoints name: the caller's, or plain_tile's for a caller who named none
+    long long plain_tiles;
 };
 
-// Tile of a caller who names a variant but no tile (and, before the rules of choose_default, of every
-// caller who named no tile: checkpoints of such contexts carry it).
+// Tile of a caller who names a variant but no tile, and the one that checkpoints name for every caller who named no
+// tile: it follows from the box and the storage alone, where choose_default's goes by noise, operator and max_points too, and
+// the marching kernels' by the registered sets.
 void plain_tile(const lb_params* p, int& tx, int& ty, int& tz)
 {
     const double box_bytes = double(p->nx) * p->ny * p->nz * planes_of(p->storage) * storage_bytes(p->storage);
@@ -224,6 +226,12 @@ int fill_geometry(const lb_params* p, int variant, long long cap, int tx, int ty
     return LB_OK;
 }
 
+// Tiles of shape t that cover the lattice.
+long long tiles_of(const Geom& G, const int (&t)[3])
+{
+    return (long long)((G.nx + t[0] - 1) / t[0]) * ((G.ny + t[1] - 1) / t[1]) * ((G.nz + t[2] - 1) / t[2]) * G.nboxes;
+}
+
 // Planes per block of the marching kernels (lbm_march.hip), or 0 where the kernels of one node per thread are
 // faster.  A launch takes as many rounds as its blocks fill the chip; a round costs the block's planes and two
 // repeated ones; the planes per block are chosen for the fewest.  Time of one plane of a block, measured: 7.2 us for
@@ -337,6 +345,7 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     const Geom& G = P.Gp;
     const long long ntiles = std::max(P.Gp.ntiles, P.Gm.ntiles);     // the lists serve both geometries
     const long long maxp = std::max(P.Gp.maxp, P.Gm.maxp);
+    P.plain_tiles = tiles_of(G, P.plain);
     P.chunks = std::max(P.Gp.bchunks, P.Gm.bchunks);
     Layout& L = P.L;
     size_t o = 0;
@@ -356,7 +365,7 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     L.partial = take(sizeof(double) * 3 * P.cap * maxp);
     L.fpart = take(sizeof(double) * 3 * p->nboxes * P.chunks);
     L.pmax = take(sizeof(float) * p->nboxes * P.chunks);
-    L.tmax = take(sizeof(float) * ntiles);
+    L.tmax = take(sizeof(float) * std::max(ntiles, P.plain_tiles));   // (zeros but for batches of FP16 boxes)
     L.smax = take(sizeof(unsigned) * SMAX_SLOTS * SMAX_STRIDE);
     L.ticket = take(sizeof(unsigned) * p->nboxes);
     L.tctr = take(2 * sizeof(unsigned long long));
@@ -899,7 +908,7 @@ int lb_init(const lb_params* p, void* d_workspace, size_t bytes, void* hip_strea
     launch_fill_u32(c->toff(), ntiles + 1, 0u, s);
     launch_fill_u32(c->ticket(), p->nboxes, 0u, s);
     launch_fill_u32(c->tctr(), 4, 0u, s);
-    launch_fill_u32(c->tmax(), ntiles, 0u, s);
+    launch_fill_u32(c->tmax(), std::max(ntiles, c->P.plain_tiles), 0u, s);
     launch_fill_u32(c->smax(), SMAX_SLOTS * SMAX_STRIDE, 0u, s);
     launch_fill_u32(c->errw(), 4, 0u, s);
     launch_fill_u32(c->nf(), p->nboxes, 0u, s);
@@ -1202,8 +1211,8 @@ int lb_sync(lb_ctx* c)
     return read_flags(c);
 }
 
-// Layout of a checkpoint of this context, or of one whose tile list has `tiles` entries.
-static CkptHeader ckpt_layout(const lb_ctx* c, int64_t tiles)
+// Layout of a checkpoint that names tile t: this context's own (P.plain), or one it accepts.
+static CkptHeader ckpt_layout(const lb_ctx* c, const int (&t)[3])
 {
     CkptHeader h;
     memset(&h, 0, sizeof(h));
@@ -1211,11 +1220,11 @@ static CkptHeader ckpt_layout(const lb_ctx* c, int64_t tiles)
     const Geom& G = c->P.G;
     h.nx = G.nx; h.ny = G.ny; h.nz = G.nz; h.nboxes = G.nboxes;
     h.storage = c->p.storage; h.collision = c->p.collision;
-    h.tx = G.tx; h.ty = G.ty; h.tz = G.tz;
+    h.tx = t[0]; h.ty = t[1]; h.tz = t[2];
     h.steps = c->steps;
     h.npoints = total_points(c);
     h.pop_bytes = (int64_t)G.sbox * G.nboxes * (int64_t)storage_bytes(c->p.storage);
-    h.tiles = tiles;
+    const int64_t tiles = h.tiles = tiles_of(G, t);
     size_t o = align_up(sizeof(CkptHeader));
     auto take = [&](size_t b) { const size_t at = o; o = align_up(o + std::max<size_t>(b, 1)); return (int64_t)at; };
     h.off_pop = take(h.pop_bytes);
@@ -1232,7 +1241,7 @@ static CkptHeader ckpt_layout(const lb_ctx* c, int64_t tiles)
 int lb_checkpoint_bytes(const lb_ctx* c, size_t* bytes)
 {
     if (!c || !bytes) return LB_ERR_ARG;
-    *bytes = (size_t)ckpt_layout(c, c->P.G.ntiles).total;
+    *bytes = (size_t)ckpt_layout(c, c->P.plain).total;
     return LB_OK;
 }
 
@@ -1244,7 +1253,7 @@ int lb_checkpoint_save(lb_ctx* c, void* dst)
     // the binning windows are part of the state once the registered sets have been binned
     if (total_points(c) > 0 && c->binned_gen != c->gen)
         return fail(c, LB_ERR_STATE, "checkpoint: step once after changing the point sets");
-    c->ckpt = ckpt_layout(c, c->P.G.ntiles);
+    c->ckpt = ckpt_layout(c, c->P.plain);
     const CkptHeader& h = c->ckpt;
     char* d = (char*)dst;
     hipStream_t s = c->stream;
@@ -1255,7 +1264,7 @@ int lb_checkpoint_save(lb_ctx* c, void* dst)
     cp(0, &c->ckpt, sizeof(CkptHeader));
     cp(h.off_pop, c->pop(c->cur), (size_t)h.pop_bytes);
     cp(h.off_boxes, c->boxes(), sizeof(BoxDev) * c->p.nboxes);
-    cp(h.off_tmax, c->tmax(), sizeof(float) * c->P.G.ntiles);
+    cp(h.off_tmax, c->tmax(), sizeof(float) * h.tiles);
     cp(h.off_smax, c->smax(), sizeof(unsigned) * SMAX_SLOTS * SMAX_STRIDE);
     cp(h.off_tctr, c->tctr() + c->cur, sizeof(unsigned long long));
     cp(h.off_nf, c->nf(), sizeof(int) * c->p.nboxes);
@@ -1273,23 +1282,20 @@ int lb_checkpoint_load(lb_ctx* c, const void* src)
     if (!r) r = hip_check(c, hipMemcpy(&h, src, sizeof(h), hipMemcpyDefault), "checkpoint header");
     if (r) return r;
     if (memcmp(h.magic, CKPT_MAGIC, 8) != 0) return fail(c, LB_ERR_ARG, "not a checkpoint");
-    // the tile in use, or another one that contexts of these parameters have used (only the per-tile maxima depend on
-    // the tile, and those matter for batches of FP16 boxes alone, whose default is the plain tile)
-    const Geom& G = c->P.G;
-    const int* q = c->P.plain;
-    const int tiles[4][3] = {{G.tx, G.ty, G.tz}, {c->P.Gp.tx, c->P.Gp.ty, c->P.Gp.tz}, {c->P.Gm.tx, c->P.Gm.ty, c->P.Gm.tz},
-                             {q[0], q[1], q[2]}};
-    const bool same = h.tx == G.tx && h.ty == G.ty && h.tz == G.tz;
-    CkptHeader want = ckpt_layout(c, G.ntiles);
-    bool known = false;
+    // The tile that checkpoints of this context name or, where the caller named none, one that the library chooses
+    // for it (such contexts have written their own tile).  Only the per-tile maxima depend on the tile, and those
+    // matter for batches of FP16 boxes alone, whose default is the plain tile.
+    const Plan& P = c->P;
+    const int tiles[3][3] = {{P.plain[0], P.plain[1], P.plain[2]}, {P.Gp.tx, P.Gp.ty, P.Gp.tz}, {P.Gm.tx, P.Gm.ty, P.Gm.tz}};
+    const int* known = nullptr;
+    CkptHeader want{};
     for (auto& t : tiles)
         if (!known && h.tx == t[0] && h.ty == t[1] && h.tz == t[2]) {
-            known = true;
-            want = ckpt_layout(c, (int64_t)((G.nx + t[0] - 1) / t[0]) * ((G.ny + t[1] - 1) / t[1]) *
-                                      ((G.nz + t[2] - 1) / t[2]) * G.nboxes);
+            known = t;
+            want = ckpt_layout(c, t);
         }
-    if (h.nx != want.nx || h.ny != want.ny || h.nz != want.nz || h.nboxes != want.nboxes ||
-        h.storage != want.storage || h.collision != want.collision || !known || h.tiles != want.tiles ||
+    if (!known || h.nx != want.nx || h.ny != want.ny || h.nz != want.nz || h.nboxes != want.nboxes ||
+        h.storage != want.storage || h.collision != want.collision || h.tiles != want.tiles ||
         h.npoints != want.npoints || h.total != want.total)
         return fail(c, LB_ERR_ARG, "checkpoint of another lattice, tiling or point count");
     const char* d = (const char*)src;
@@ -1299,11 +1305,11 @@ int lb_checkpoint_load(lb_ctx* c, const void* src)
     };
     cp(c->pop(c->cur), want.off_pop, (size_t)want.pop_bytes);
     cp(c->boxes(), want.off_boxes, sizeof(BoxDev) * c->p.nboxes);
-    if (same) cp(c->tmax(), h.off_tmax, sizeof(float) * G.ntiles);
-    cp(c->smax(), h.off_smax, sizeof(unsigned) * SMAX_SLOTS * SMAX_STRIDE);
-    cp(c->tctr() + c->cur, h.off_tctr, sizeof(unsigned long long));
-    cp(c->nf(), h.off_nf, sizeof(int) * c->p.nboxes);
-    if (h.npoints > 0) cp(c->win(), h.off_win, sizeof(int4) * h.npoints);
+    if (known == tiles[0]) cp(c->tmax(), want.off_tmax, sizeof(float) * want.tiles);
+    cp(c->smax(), want.off_smax, sizeof(unsigned) * SMAX_SLOTS * SMAX_STRIDE);
+    cp(c->tctr() + c->cur, want.off_tctr, sizeof(unsigned long long));
+    cp(c->nf(), want.off_nf, sizeof(int) * c->p.nboxes);
+    if (want.npoints > 0) cp(c->win(), want.off_win, sizeof(int4) * want.npoints);
     if (r) return r;
     // rebuild the tile lists at the next step with the saved windows: the lists flag raised,
     // no box choosing new windows unless one of its points has left its window

@@ -1,0 +1,127 @@
+"""Checkpoints between contexts of the same lattice whose tiles differ.  A context that names no tile gets one by
+max_points, noise and the registered sets too; none of these is part of the state, so its checkpoints load into contexts
+that differ in them, into a context that names the plain tile, or a variant alone, and the other way.  Files that carry the
+library's own tile load where the library would choose it; any other tile is refused."""
+import struct
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_0707_1299_amd import lbm  # noqa: E402
+
+EPS = {"fp64": 2.0 ** -53, "fp32": 2.0 ** -24, "mom32": 2.0 ** -24}
+NPTS, STEPS = 11, 8
+
+
+def _context(shape, storage, kind=lbm.LB_FORCES_STATIC, nboxes=1, max_points=NPTS, **kw):
+    g = np.random.default_rng(8)
+    pos = torch.tensor(g.uniform(0, 1, (NPTS, 3)) * np.array(shape[::-1], dtype=np.float64), device="cuda")
+    frc = torch.tensor(g.normal(scale=1e-6, size=(NPTS, 3)), device="cuda")
+    box = torch.tensor(g.integers(0, nboxes, NPTS).astype(np.int32), device="cuda")
+    lat = lbm.Lattice(shape, storage, nboxes=nboxes, tau=0.7, max_points=max_points, **kw)
+    lat.add_point_forces(pos, frc, box, kind, lbm.PointModel(inv_a=1.4, inv_aL=0.7))
+    return lat
+
+
+def _save(lat):
+    buf = torch.zeros(lat.checkpoint_bytes() + 256, dtype=torch.uint8, device="cuda")
+    off = lat.checkpoint_save(buf) - buf.data_ptr()
+    lat.sync()
+    return buf, off
+
+
+def _resumes(a, b, storage):
+    """a takes STEPS steps and a checkpoint, b continues from it; both take STEPS more and agree to the rounding of a step"""
+    a.step(STEPS)
+    buf, _ = _save(a)
+    a.step(STEPS)
+    b.step(3)
+    b.checkpoint_load(buf)
+    assert b.steps_taken() == STEPS
+    b.step(STEPS)
+    (ra, ua), (rb, ub) = a.moments(), b.moments()
+    a.sync()
+    b.sync()
+    top = max(ua.abs().max().item(), (ra - 1).abs().max().item())
+    assert top > 0 and max((ua - ub).abs().max().item(), (ra - rb).abs().max().item()) <= STEPS * 64 * EPS[storage] * top
+
+
+@pytest.mark.parametrize("shape,nboxes,storage,first,second", [
+    ((20, 12, 101), 1, "fp64", {}, dict(max_points=500)),              # many points: compact tiles
+    ((20, 12, 101), 1, "fp64", dict(max_points=500), {}),
+    ((20, 16, 256), 1, "fp32", {}, dict(max_points=500)),
+    ((20, 12, 101), 1, "fp64", {}, dict(tile=(64, 2, 2))),             # the plain tile by name
+    ((20, 12, 101), 1, "fp64", {}, dict(variant=64)),                  # a variant alone: the plain tile
+    ((20, 12, 101), 1, "fp64", dict(variant=64), {}),
+    ((24, 24, 24), 300, "fp32", {}, dict(tile=(16, 4, 4))),            # from the marching kernels' lists
+    ((24, 24, 24), 300, "fp32", {}, dict(max_points=9000)),
+    ((24, 24, 24), 300, "fp32", dict(tile=(16, 4, 4)), {}),
+    ((128, 128, 128), 1, "mom32", {}, dict(tile=(128, 1, 2))),
+])
+def test_loads_into_another_tile(shape, nboxes, storage, first, second):
+    _resumes(_context(shape, storage, nboxes=nboxes, **first), _context(shape, storage, nboxes=nboxes, **second), storage)
+
+
+@pytest.mark.parametrize("shape,storage", [((20, 12, 101), "fp32"), ((20, 12, 75), "fp64")])
+def test_noise_is_no_part_of_the_state(shape, storage):
+    a = _context(shape, storage)
+    a.step(STEPS)
+    buf, _ = _save(a)
+    b = _context(shape, storage, kT=1e-9, seed=3)
+    b.checkpoint_load(buf)
+    assert b.steps_taken() == STEPS
+    a2 = _context(shape, storage)
+    a2.checkpoint_load(buf)
+    assert torch.equal(a.moments()[1], a2.moments()[1]) and torch.equal(a.moments()[1], b.moments()[1])
+
+
+HEADER = struct.Struct("<8s10i12q")     # magic; sizes, storage, collision, tile, padding; steps ... offsets
+
+
+def _with_own_tile(buf, off, tile):
+    """The same state in a file that carries `tile` (one list entry per tile in its section of maxima)."""
+    raw = buf.cpu().numpy()[off:]
+    h = list(HEADER.unpack_from(raw))
+    nx, ny, nz, nb = h[1:5]
+    old, start = h[14], h[18]           # tiles; offset of the maxima
+    new = -(-nx // tile[0]) * -(-ny // tile[1]) * -(-nz // tile[2]) * nb
+    size = lambda n: -(-max(4 * n, 1) // 256) * 256     # noqa: E731
+    shift = size(new) - size(old)
+    h[7:10], h[14], h[15] = tile, new, h[15] + shift
+    h[19:] = [o + shift for o in h[19:]]
+    out = np.concatenate([raw[:start], np.zeros(size(new), np.uint8), raw[start + size(old):]])
+    out[:HEADER.size] = np.frombuffer(HEADER.pack(*h), np.uint8)
+    return torch.tensor(np.concatenate([out, np.zeros(512, np.uint8)]), device="cuda")
+
+
+@pytest.mark.parametrize("shape,nboxes,storage,tile,known", [
+    ((20, 12, 101), 1, "fp64", (128, 2, 1), True),          # choose_default's
+    ((24, 24, 24), 300, "fp32", (32, 4, 2), True),
+    ((24, 24, 24), 300, "fp32", (32, 8, 1), True),          # the marching kernels'
+    ((20, 12, 101), 1, "fp64", (64, 1, 4), False),
+])
+def test_files_with_the_librarys_own_tile(shape, nboxes, storage, tile, known):
+    a = _context(shape, storage, nboxes=nboxes)
+    a.step(STEPS)
+    buf, off = _save(a)
+    own = _with_own_tile(buf, off, tile)
+    assert own.data_ptr() % 256 == 0    # as torch allocates
+    b = _context(shape, storage, nboxes=nboxes)
+    if not known:
+        with pytest.raises(lbm.LBError) as e:
+            b.checkpoint_load(own)
+        assert e.value.status == lbm.LB_ERR_ARG
+        return
+    b.checkpoint_load(own)
+    a.step(STEPS)
+    b.step(STEPS)
+    assert b.steps_taken() == 2 * STEPS and torch.equal(a.moments()[1], b.moments()[1])
+    named = _context(shape, storage, nboxes=nboxes, tile=(64, 2, 2) if shape[2] >= 64 else (16, 4, 4))
+    with pytest.raises(lbm.LBError):            # a named tile takes its own files alone
+        named.checkpoint_load(own)
