@@ -1014,15 +1014,18 @@ void launch_prep(int storage, const Geom& G, long long n, long long off, const d
 
 long long scan_blocks(long long ntiles) { return (ntiles + CHUNK - 1) / CHUNK; }
 
-// Blocks of the list build for `slots` (point, slot) lanes: at most one per compute unit of the current
+// Blocks of the list build for `slots` (point, slot) lanes and a scan over ntiles tiles: at most one per compute unit of the current
 // device and BIN_GRID, so that the grid is resident at once even on a partition of the GPU.  A grid
 // barrier costs about 0.05 us per block (12 us of the build at 16 blocks, 60 us at 256), a round of 256
 // lanes about 1 us per phase, so small builds take few blocks: 200 points of 128 x 96 x 80 ran in 82 us on
 // 256 blocks, 35 us on 16; 1000 points of 128^3 89 / 44 us on 256 / 32; 10^4 points of 256^3 106 / 84 us on
-// 256 / 128; 65536 points of 256^3 192 / 236 us on 256 / 128 (with the call's other launches).
-static unsigned rebin_grid(long long slots)
+// 256 / 128; 65536 points of 256^3 192 / 236 us on 256 / 128 (with the call's other launches).  Two tiles ask for as much
+// as one lane: 100 points of 512^3 (524288 tiles) 237 us on 16 blocks, 89 on 64, 74 on 128, 94 on 256; of 256^3 (65536)
+// 48 us on 16, 38 on 32 and 64, 48 on 128.
+static unsigned rebin_grid(long long slots, long long ntiles)
 {
-    const unsigned want = slots >= (1LL << 20) ? BIN_GRID : (unsigned)std::clamp<long long>(slots >> 10, 16, 128);
+    const long long work = std::max(slots, ntiles >> 1);
+    const unsigned want = work >= (1LL << 20) ? BIN_GRID : (unsigned)std::clamp<long long>(work >> 10, 16, 128);
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
@@ -1038,7 +1041,7 @@ void launch_bins(int storage, const Geom& G, long long npts, const void* rec, in
     if (npts <= 0) return;
     const int lg = log_lanes(G.maxp);
     const long long max_entries = npts * G.maxp;
-    const unsigned nb = rebin_grid(npts << lg);
+    const unsigned nb = rebin_grid(npts << lg, G.ntiles);
     if (storage == ST_FP64)
         hipLaunchKernelGGL(k_rebin<double>, dim3(nb), dim3(256), 0, s, G, npts, lg, (const PRec<double>*)rec, count,
                            bsum, toff, cursor, tlist_tmp, tlist, max_entries, err);
