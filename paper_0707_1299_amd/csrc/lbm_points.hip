@@ -1115,11 +1115,20 @@ void launch_advect(int storage, const Geom& G, const AdvectLaunch& a, BoxDev* bo
     }
 }
 
+// Points of one launch: 64 slabs of them take 2^31 threads, and a launch of 2^32 and more leaves points out.
+constexpr long long INTERP_POINTS = 1LL << 23;
+
 void launch_interp_points(int storage, const Geom& G, long long n, const double* pos, const int* boxid, double* out,
                           const void* src, const BoxDev* boxes, const int* toff, const int* tlist, const void* rec,
                           hipStream_t s)
 {
     if (n <= 0) return;
+    if (n > INTERP_POINTS) {
+        launch_interp_points(storage, G, INTERP_POINTS, pos, boxid, out, src, boxes, toff, tlist, rec, s);
+        launch_interp_points(storage, G, n - INTERP_POINTS, pos + 3 * INTERP_POINTS, boxid ? boxid + INTERP_POINTS : nullptr,
+                             out + 3 * INTERP_POINTS, src, boxes, toff, tlist, rec, s);
+        return;
+    }
     // slabs pay where the points' line fetches (39 KB each in FP32, by storage size) are several times the
     // lattice and the lattice is several times an XCD's 4 MB L2: 20000 points took 54 us in slabs and 110 us
     // in plain order at 128 x 96 x 80 (75 MB, 10 x), 34 and 31 us at 32^3 (2.5 MB); at 256^3 (1.3 GB, 0.6 x)
