@@ -916,7 +916,7 @@ __device__ __forceinline__ void interp_point(const Geom& G, long long q, const d
 }
 
 // Plain order (nslab == 1): wave q takes point q.  With nslab > 1 the z planes of all boxes are cut into
-// nslab slabs of about 2 MB, half an XCD's L2: the blocks that the dispatcher sends to XCD j work
+// nslab slabs (see interp_slabs): the blocks that the dispatcher sends to XCD j work
 // through slabs j, j + 8, ... in order, `per` blocks a slab, one for each group of 64 points: its waves
 // look for those whose base plane lies in the slab and take them in turn.  A point's stencil touches 19 x 16 cache lines of 128 B, eight times
 // its data; in plain order every XCD fetches most of them over the fabric (20000 points of 128 x 96 x 80: 113 us,
@@ -1115,6 +1115,22 @@ void launch_advect(int storage, const Geom& G, const AdvectLaunch& a, BoxDev* bo
     }
 }
 
+// Slabs pay where the points' line fetches (39 KB each in FP32, by storage size) are several times the lattice
+// and the lattice is several times an XCD's 4 MB L2: 20000 points took 54 us in slabs and 110 us in plain order at
+// 128 x 96 x 80 (75 MB, 10 x), 34 and 31 us at 32^3 (2.5 MB); at 256^3 (1.3 GB, 0.6 x) nothing is shared.
+// Slabs of 2 MB, half the L2, as far as 64 slabs go (every slab's blocks look at every point); larger lattices gain with thicker ones too, if less (140000 points of 256^3, 20 MB slabs: 697 us, 819 in plain order; moment storage
+// 1183 / 1509; 600000 points of 512^3 FP16 3172 / 3830), but in FP64 slabs of fewer than four planes lose it
+// again: 200^3 831 us with 64 slabs, 733 with 40, 816 in plain order (100^3 364 / 350 / 594, 160^3 382 / 362 / 425).
+static int interp_slabs(int storage, const Geom& G, long long n)
+{
+    const double esize = storage == ST_FP64 ? 8 : storage == ST_FP16 ? 2 : 4;
+    const double lattice = double(G.sbox) * G.nboxes * esize, lines = double(n) * planes_of(storage) * 16 * 128;
+    if (!(lattice > 16.0e6 && lines >= 4.0 * lattice)) return 1;
+    int nslab = 8 * (int)std::min(8.0, ceil(lattice / 16.0e6));
+    if (storage == ST_FP64 && 4LL * nslab > (long long)G.nz * G.nboxes) nslab = std::min(nslab, 40);
+    return nslab;
+}
+
 // Points of one launch: 64 slabs of them take 2^31 threads, and a launch of 2^32 and more leaves points out.
 constexpr long long INTERP_POINTS = 1LL << 23;
 
@@ -1129,14 +1145,7 @@ void launch_interp_points(int storage, const Geom& G, long long n, const double*
                              out + 3 * INTERP_POINTS, src, boxes, toff, tlist, rec, s);
         return;
     }
-    // slabs pay where the points' line fetches (39 KB each in FP32, by storage size) are several times the
-    // lattice and the lattice is several times an XCD's 4 MB L2: 20000 points took 54 us in slabs and 110 us
-    // in plain order at 128 x 96 x 80 (75 MB, 10 x), 34 and 31 us at 32^3 (2.5 MB); at 256^3 (1.3 GB, 0.6 x)
-    // nothing is shared.  At most 64 slabs: every slab's blocks look at every point.
-    const double esize = storage == ST_FP64 ? 8 : storage == ST_FP16 ? 2 : 4;
-    const double lattice = double(G.sbox) * G.nboxes * esize, lines = double(n) * planes_of(storage) * 16 * 128;
-    const int nslab = lattice > 16.0e6 && lines >= 4.0 * lattice ? 8 * (int)std::min(8.0, ceil(lattice / 16.0e6)) : 1;
-    const int per = (int)nblk(n, 64);
+    const int nslab = interp_slabs(storage, G, n), per = (int)nblk(n, 64);
     const unsigned nb = nslab > 1 ? (unsigned)nslab * per : nblk(n, 4);
     switch (storage) {
     case ST_FP64:

@@ -28,3 +28,19 @@ def test_many_points(n):
         part = lat.interp_velocity(pos[a:a + (1 << 22)], box[a:a + (1 << 22)])
         assert torch.equal(whole[a:a + (1 << 22)], part)
     assert whole.abs().max().item() > 1e-4
+
+
+@pytest.mark.parametrize("shape,storage", [
+    ((64, 64, 64), "fp64"), ((40, 96, 128), "fp64"), ((300, 30, 36), "fp64"), ((70, 64, 64), "fp32"),
+])
+def test_slabs_of_all_heights(shape, storage):
+    """40 slabs of FP64 lattices with fewer than four planes a slab, 64 of others, against plain order (few points)."""
+    n = 40000
+    g = torch.Generator(device="cuda").manual_seed(5)
+    lat = lbm.Lattice(shape, storage, tau=0.7)
+    u = 1e-3 * torch.randn((1, 3) + shape, dtype=torch.float64, device="cuda", generator=g)
+    lat.set_equilibrium(torch.ones((1,) + shape, dtype=torch.float64, device="cuda"), u)
+    pos = 400 * torch.rand((n, 3), dtype=torch.float64, device="cuda", generator=g) - 50
+    whole = lat.interp_velocity(pos)
+    for a in range(0, n, 500):
+        assert torch.equal(whole[a:a + 500], lat.interp_velocity(pos[a:a + 500]))
