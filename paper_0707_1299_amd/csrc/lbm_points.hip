@@ -982,10 +982,13 @@ __global__ __launch_bounds__(256) void k_diag_reduce(const Geom G, const double*
             c == 10 ? fmax(fmax(red[0], red[1]), fmax(red[2], red[3])) : ((red[0] + red[1]) + red[2]) + red[3];
 }
 
+// (a launch of 2^32 threads and more, a population copy of 17 GB, would leave words out: the grid is bounded)
+constexpr unsigned FILL_BLOCKS = 1u << 20;
+
 __global__ void k_fill_u32(uint32_t* __restrict__ p, long long n, uint32_t v)
 {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -995,7 +998,8 @@ static unsigned nblk(long long n, int b) { return (unsigned)((n + b - 1) / b); }
 
 void launch_fill_u32(void* p, long long n, uint32_t v, hipStream_t s)
 {
-    if (n > 0) hipLaunchKernelGGL(k_fill_u32, dim3(nblk(n, 256)), dim3(256), 0, s, (uint32_t*)p, n, v);
+    const long long blocks = std::min<long long>((n + 255) / 256, FILL_BLOCKS);
+    if (n > 0) hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)blocks), dim3(256), 0, s, (uint32_t*)p, n, v);
 }
 
 long long prep_blocks(long long n) { return n > 0 ? nblk(n, 256) : 0; }
@@ -1118,8 +1122,9 @@ void launch_advect(int storage, const Geom& G, const AdvectLaunch& a, BoxDev* bo
 // Slabs pay where the points' line fetches (39 KB each in FP32, by storage size) are several times the lattice
 // and the lattice is several times an XCD's 4 MB L2: 20000 points took 54 us in slabs and 110 us in plain order at
 // 128 x 96 x 80 (75 MB, 10 x), 34 and 31 us at 32^3 (2.5 MB); at 256^3 (1.3 GB, 0.6 x) nothing is shared.
-// Slabs of 2 MB, half the L2, as far as 64 slabs go (every slab's blocks look at every point); larger lattices gain with thicker ones too, if less (140000 points of 256^3, 20 MB slabs: 697 us, 819 in plain order; moment storage
-// 1183 / 1509; 600000 points of 512^3 FP16 3172 / 3830), but in FP64 slabs of fewer than four planes lose it
+// Slabs of 2 MB, half the L2, as far as 64 slabs go (every slab's blocks look at every point); larger lattices
+// gain with thicker ones too, if less (140000 points of 256^3, 20 MB slabs: 697 us, 819 in plain order; moment
+// storage 1183 / 1509; 600000 points of 512^3 FP16 3172 / 3830), but in FP64 slabs of fewer than four planes lose it
 // again: 200^3 831 us with 64 slabs, 733 with 40, 816 in plain order (100^3 364 / 350 / 594, 160^3 382 / 362 / 425).
 static int interp_slabs(int storage, const Geom& G, long long n)
 {
