@@ -199,7 +199,8 @@ int fill_geometry(const lb_params* p, int variant, long long cap, int tx, int ty
     G.ntiles = G.tiles_per_box * p->nboxes;
     G.rho0 = p->rho0 > 0.0 ? p->rho0 : 1.0;
     G.maxp = max_axis_tiles(p->nx, tx) * max_axis_tiles(p->ny, ty) * max_axis_tiles(p->nz, tz);
-    if (G.ntiles >= (1LL << 31) - 1) { why = "too many tiles"; return LB_ERR_SIZE; }
+    // one block of BLOCK threads per tile: a launch of 2^32 threads and more would leave tiles out
+    if (G.ntiles >= (1LL << 32) / BLOCK) { why = "too many tiles"; return LB_ERR_SIZE; }
     if (cap * G.maxp >= (1LL << 31) - 1 || cap >= (1LL << (31 - PK_SHIFT))) {
         why = "max_points too large";
         return LB_ERR_SIZE;

@@ -101,7 +101,8 @@ bool launch_lattice(int storage, const Geom& G, int mode, int variant, const voi
 void launch_equilibrium(int storage, const Geom& G, void* dst, const BoxDev* boxes, const double* rho,
                         const double* u, hipStream_t s)
 {
-    const int per = G.nx <= 64 && storage != ST_FP16 ? 64 / G.nx * G.nx : 64;
+    // (whole rows may leave half the lanes idle: not where that would take the launch to 2^32 threads)
+    const int per = G.nx <= 64 && storage != ST_FP16 && G.N * G.nboxes < 1LL << 31 ? 64 / G.nx * G.nx : 64;
     const long long waves = (G.N * G.nboxes + per - 1) / per;
     const dim3 nb((unsigned)((waves + BLOCK / 64 - 1) / (BLOCK / 64)));
     switch (storage) {

@@ -25,3 +25,12 @@ def test_what_the_plain_tile_takes_is_accepted(shape, storage, kw):
     assert lbm.lb_workspace_bytes(lbm.make_params(shape, storage, **kw)) > 0
     # a larger lattice takes no less
     assert lbm.lb_workspace_bytes(lbm.make_params((shape[0] + 4,) + shape[1:], storage, **kw)) > 0
+
+
+@pytest.mark.parametrize("storage", ["fp16", "fp32", "mom32"])
+def test_no_more_tiles_than_a_launch_has_threads_for(storage):
+    """A tile is a block of 256 threads, and a launch of 2 ** 32 threads leaves some out without an error."""
+    assert lbm.lb_workspace_bytes(lbm.make_params((4, 4, 4), storage, nboxes=(1 << 24) - 1)) > 0
+    with pytest.raises(lbm.LBError) as e:
+        lbm.lb_workspace_bytes(lbm.make_params((4, 4, 4), storage, nboxes=1 << 24))
+    assert e.value.status == lbm.LB_ERR_SIZE
