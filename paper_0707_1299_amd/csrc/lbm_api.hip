@@ -69,6 +69,7 @@ struct Layout {
 struct Plan {
     Geom G;            // the geometry in use: Gp, or Gm while the marching kernels may take the steps (see set_geometry)
     Geom Gp, Gm;
+    Geom Gr;           // that of reads without points (see read_geometry)
     Layout L;
     int chunks;
     long long cap;
@@ -342,6 +343,10 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     march_tile(p->nx, p->ny, mx, my);
     if (P.march > 0 && fill_geometry(p, P.variant, P.cap, mx, my, 1, P.Gm, none)) P.march = 0;
     if (P.march == 0) P.Gm = P.Gp;
+    P.Gr = P.Gp;
+    if (p->storage == LB_STORAGE_FP16 && P.Gp.tx == 128 && p->nx % 128 != 0 && P.variant != p->variant &&
+        fill_geometry(p, 0, P.cap, P.plain[0], P.plain[1], P.plain[2], P.Gr, none))
+        P.Gr = P.Gp;
     P.G = P.Gp;
     const Geom& G = P.Gp;
     const long long ntiles = std::max(P.Gp.ntiles, P.Gm.ntiles);     // the lists serve both geometries
@@ -375,7 +380,7 @@ int make_plan(const lb_params* p, Plan& P, std::string& why)
     L.rebin = take(sizeof(int));
     L.rebox = take(sizeof(int) * p->nboxes);
     L.win = take(sizeof(int4) * P.cap);
-    L.diag = take(sizeof(double) * LBD_N * ntiles);
+    L.diag = take(sizeof(double) * LBD_N * std::max(ntiles, P.Gr.ntiles));
     L.diagout = take(sizeof(double) * LBD_N * p->nboxes);
     // the marching kernels' force density and velocities (of one step or two) near points
     const size_t field = P.march > 0 && P.cap > 0 ? sizeof(float) * 3 * G.N * p->nboxes : 0;
@@ -536,6 +541,31 @@ bool marches(const lb_ctx* c)
 // The geometry (tiles of the point lists) for the registered sets; called when they change, which also
 // makes the lists be built again.
 void set_geometry(lb_ctx* c) { c->P.G = marches(c) ? c->P.Gm : c->P.Gp; }
+
+// Geometry of the moments and the diagnostics between steps.  Without points any tile serves: that of single steps, or the
+// plain one in FP16 where a read's one node per lane would leave lanes of a 128-node tile idle (moments of 160^3 56 ->
+// 45 us); the diagnostics, bound by arithmetic, keep the marching kernels' tile, which leaves none idle (192^3
+// FP32 159 against 193).  Block order of a caller who leaves the choice to the library (choose_default's is for steps):
+// contiguous runs per XCD, as with variant 0, but for the moments of populations on whole cache lines from 400 MB a
+// copy on and for moment storage on whole lines or narrow rows.  (Tile rows on one XCD -> contiguous runs: moments FP32
+// 300 x 200 x 100 133 -> 117 us, 160^3 79 -> 70, 300 boxes of 24^3 92 -> 78, FP16 300 x 64 x 60 19 -> 16.5; left: FP32 192^3
+// with 4000 points 123 / 129, 256^3 302 / 324, moment storage 256^3 397 / 433, 100 boxes of 48^3 305 / 318.
+// Diagnostics FP64 192^3 254 -> 225, FP32 1000 boxes of 16^3 132 -> 119; left: moment storage 512^3 3091 / 3300.)
+Geom read_geometry(const lb_ctx* c, bool diagnostics)
+{
+    const lb_params& p = c->p;
+    Geom G = total_points(c) > 0 || (diagnostics && c->P.march > 0) ? c->P.G : c->P.Gr;
+    G.tpb = 1;
+    if (p.tile_x > 0 || p.variant != 0) return G;
+    const bool mom = p.storage == LB_STORAGE_MOM32;
+    const bool lines = (long long)(G.nx * storage_bytes(p.storage)) % 128 == 0;
+    const double copy = double(G.sbox) * G.nboxes * storage_bytes(p.storage);
+    if (mom ? !lines && G.nx > 64 : diagnostics || !lines || copy < 400.0e6) {
+        G.order = 0;
+        G.lgrp = 0;
+    }
+    return G;
+}
 
 // After the sets change, the next list build must run whatever the positions:
 // raise the rebuild flag once per change.  Enqueued eagerly, never into a
@@ -843,7 +873,7 @@ int lb_init(const lb_params* p, void* d_workspace, size_t bytes, void* hip_strea
     c->p.tau_bulk = nullptr;   // read below, not kept
     c->P = P;
     c->ws = (char*)d_workspace;
-    for (Geom* g : {&c->P.Gp, &c->P.Gm}) {
+    for (Geom* g : {&c->P.Gp, &c->P.Gm, &c->P.Gr}) {
         g->nf = c->nf();
         g->rebin = c->rebin();
         g->rebox = c->rebox();
@@ -1128,9 +1158,7 @@ int lb_moments(lb_ctx* c, double* d_rho, double* d_u)
     clear_stale_error();
     if (!d_u) return fail(c, LB_ERR_ARG, "lb_moments: d_u is NULL");
     prepare_fields(c);
-    Geom G1 = c->P.G;
-    G1.tpb = 1;
-    launch_lattice(c->p.storage, G1, 1, 0, c->pop(c->cur), nullptr, c->boxes(),
+    launch_lattice(c->p.storage, read_geometry(c, false), 1, 0, c->pop(c->cur), nullptr, c->boxes(),
                    total_points(c) > 0 ? c->toff() : nullptr, c->tlist(), c->rec(), d_rho, d_u, nullptr, nullptr,
                    c->stream);
     return check_async(c);
@@ -1183,10 +1211,8 @@ int lb_diagnostics(lb_ctx* c, double* h_out)
     clear_stale_error();
     if (!h_out) return fail(c, LB_ERR_ARG, "h_out is NULL");
     prepare_fields(c);
-    const Geom& G = c->P.G;
-    Geom G1 = G;
-    G1.tpb = 1;
-    launch_lattice(c->p.storage, G1, 2, 0, c->pop(c->cur), nullptr, c->boxes(), total_points(c) > 0 ? c->toff() : nullptr,
+    const Geom G = read_geometry(c, true);
+    launch_lattice(c->p.storage, G, 2, 0, c->pop(c->cur), nullptr, c->boxes(), total_points(c) > 0 ? c->toff() : nullptr,
                    c->tlist(), c->rec(), c->diag(), nullptr, nullptr, nullptr, c->stream);
     launch_diag_reduce(G, c->diag(), c->diagout(), c->stream);
     int r = check_async(c);
