@@ -109,14 +109,17 @@ void plain_tile(const lb_params* p, int& tx, int& ty, int& tz)
 //    565, one row per block 940).  33 .. 63 nodes: one 64-node tile instead of two of 32 (100 boxes of
 //    48^3: 458 -> 283).  Two FP16 nodes per lane: a whole wave per row from 128 nodes on (256^3: 292 -> 240;
 //    64 x 2 x 2 250).  Moment storage: rows of a z plane together (256^3: 524 -> 460).
-//  - Block order.  Tile rows on one XCD (bit 64) except for lattices near the L2 size, where
-//    nothing is gained (64^3: 19.0 against 19.4; two boxes of 61^3 21.6 / 22.1).
+//  - Block order.  Tile rows on one XCD (bit 64) except for lattices near the L2s' 32 MB.  Both copies up to 70 MB, in FP16
+//    without noise 50 MB, narrow rows off the lines 48 MB: the orders cross between 60 and 75 MB in FP32 and FP64
+//    with every operator (contiguous runs / tile rows: FP32 70^3, 52 MB, 13.6 / 14.0; 75^3, 64 MB, 16.6 / 16.4; 79^3, 75
+//    MB, 20.6 / 18.0; 60 x 60 x 128, 70 MB, 13.9 / 14.1; 64 x 80 x 100, 78 MB, 15.3 / 14.5; with noise 79^3 26.8 / 23.3; FP64
+//    57^3, 56 MB, 12.6 / 13.4; 63^3, 76 MB, 15.5 / 15.4; 79^3, 150 MB, 36.2 / 32.1) and at 45 in FP16 (85^3, 47 MB, 18.1 / 17.9;
+//    90^3, 55 MB, 24.9 / 22.4; with noise 90^3 27.6 / 27.6, 95^3, 65 MB, 30.1 / 30.6).
 //  - Loads.  Cached (bit 2) where neighbouring rows are read again after more than the L2 has passed (planes
 //    over 2.6 MB: 256^3 455 -> 448; 128^3 67.5 -> 66.6 the other way) or where rows do not
-//    start on a cache line, so that two rows share one (300 x 60 x 40: 47.6 -> 41.1; boxes of 16^3: 75 -> 65), unless
-//    rows of 32 nodes and more are in the L2 all the same (61^3 FP64 22.8 -> 20.4, 75^3 FP32 23.5 -> 22.3, the other
-//    way from 0.46e6 nodes on: 90^3 FP32 33.1 -> 31.1, 101 x 75 x 62 with the general operator 34.3 -> 30.8); and in
-//    the smallest lattices (20^3 FP32 10.0 -> 9.8).
+//    start on a cache line, so that two rows share one (300 x 60 x 40: 47.6 -> 41.1; boxes of 16^3: 75 -> 65; 90^3 FP32
+//    27.1 -> 24.5), unless the L2s hold them all the same: in FP64 up to 100 MB (2 boxes of 60 x 50 x 52, 95 MB, 20.6 ->
+//    19.7 the other way; 70^3, 104 MB, 24.7 -> 24.2; 77^3 31.6 -> 30.2); and in the smallest lattices (20^3 FP32 10.0 -> 9.8).
 //  - The kernel for one tile per block (bit 128) where its missing tile loop saves registers: FP16, moment
 //    storage, the general and thermal operators, many points, small lattices; the FP32 and FP64 projected
 //    step is memory bound and faster with the loop (256^3 FP32: 429 against 447).  FP16 with one node per
@@ -151,13 +154,13 @@ void choose_default(const lb_params* p, int& tx, int& ty, int& tz, int& variant)
         tx = 64; ty = 2; tz = 2;
     }
     const bool aligned = (long long)(p->nx * esz) % 128 == 0, narrow = !aligned && p->nx < 32;
-    if (copies <= (narrow ? 48.0e6 : 70.0e6)) {
+    if (copies <= (narrow ? 48.0e6 : fp16 && !(p->kT > 0.0) ? 50.0e6 : 70.0e6)) {
         variant = fp16 && !pairs && !general && p->nx < 64 ? 2 : 128;
         if (copies <= 9.0e6) variant |= 2;
     } else {
         const double plane = double(p->nx) * p->ny * planes * esz;
         variant = 64;
-        if ((!aligned && (narrow || N * p->nboxes > 0.46e6)) || (plane > 2.6e6 && !dense)) variant |= 2;
+        if ((!aligned && (esz < 8.0 || narrow || copies > 100.0e6)) || (plane > 2.6e6 && !dense)) variant |= 2;
         if (fp16 || mom || general || dense) variant |= 128;
     }
 }
