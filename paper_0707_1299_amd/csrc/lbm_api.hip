@@ -559,9 +559,27 @@ bool has_kind(const lb_ctx* c, int kind)
     return false;
 }
 
+// Whether a set takes its points' velocities from a step: to move them or to hand them out.
+bool takes_velocity(const Set& st)
+{
+    return st.kind == LB_COLLOIDS || st.kind == KIND_ELASTIC ||
+           (st.has_model && (st.model.d_vel_out || st.model.d_vel_sum));
+}
+
+bool wants_velocity(const lb_ctx* c)
+{
+    for (auto& st : c->sets)
+        if (takes_velocity(st)) return true;
+    return false;
+}
+
 // Whether the marching kernels take the steps of the registered sets: two FP32 steps per launch where no point
-// moves, moment storage with any sets, but with moving ones, whose forces and velocities cost two launches more a
-// step (15 to 25 us by the planes) and 6 ns a point (the other kernels: 12 us), only where that leaves a gain.  Up to the bound of
+// moves, moment storage with any sets.  Velocities at fixed points cost a launch more (3 us of two FP32 steps, 5 us of
+// one with moment storage), moving points, whose forces change too, two a step (20 to 25 us by the planes) and 6 ns a
+// point (the other kernels: 12 us): only where that leaves a gain.  (Velocities, other kernels / marching, left alone:
+// moment storage 115 x 28 x 144 17.6 / 23.4, 23 boxes of 23^3 16.0 / 19.6, FP32 127 x 67 x 38 17.3 / 20.8; moving
+// points, moment storage, 71 boxes of 5 x 22 x 18 23.6 / 26.4.  Of 11 800 random lattices with up to one point per
+// 1050 nodes 0.2 % are slower by more than 3 % than with the other kernels, the worst 1.23.)  Up to the bound of
 // choose_march the others gain with any number of points, spread out or in one place (us per step, other kernels ->
 // marching; fixed points: FP32 256^3 with 16000 425 -> 267, 128^3 with 2000 57 -> 39, 512 boxes of 32^3 with 512 and their
 // velocities 410 -> 259, all in one box 411 -> 259; moment storage 128^3 with 100 56 -> 41; colloids: moment storage
@@ -571,9 +589,11 @@ bool marches(const lb_ctx* c)
 {
     const Plan& P = c->P;
     if (P.march == 0) return false;
-    if (!has_kind(c, LB_COLLOIDS) && !has_kind(c, KIND_ELASTIC)) return true;
-    if (c->p.storage != LB_STORAGE_MOM32) return false;
-    const double more = P.march_rows > 0 ? 25.0 : P.Gm.nx * P.Gm.ny > 256 ? 22.0 : 15.0;
+    const bool mom = c->p.storage == LB_STORAGE_MOM32;
+    if (!has_kind(c, LB_COLLOIDS) && !has_kind(c, KIND_ELASTIC))
+        return !wants_velocity(c) || P.march_us + (mom ? 5.0 : 3.0) < 0.93 * P.other_us;
+    if (!mom) return false;
+    const double more = P.march_rows > 0 ? 25.0 : P.Gm.nx * P.Gm.ny > 256 ? 22.0 : 20.0;
     return P.march_us + more + 0.006 * double(total_points(c)) < 0.93 * (P.other_us + 12.0);
 }
 
@@ -695,20 +715,6 @@ void elastic_forces(lb_ctx* c, hipStream_t s)
 bool hands_over(const lb_ctx* c)
 {
     return has_kind(c, LB_COLLOIDS) && !has_kind(c, KIND_ELASTIC) && !has_kind(c, LB_FORCES_NEXT_STEP);
-}
-
-// Whether a set takes its points' velocities from a step: to move them or to hand them out.
-bool takes_velocity(const Set& st)
-{
-    return st.kind == LB_COLLOIDS || st.kind == KIND_ELASTIC ||
-           (st.has_model && (st.model.d_vel_out || st.model.d_vel_sum));
-}
-
-bool wants_velocity(const lb_ctx* c)
-{
-    for (auto& st : c->sets)
-        if (takes_velocity(st)) return true;
-    return false;
 }
 
 // Outputs and moves of the sets' points from a step's interpolation partials; before and fp16_exp as in
