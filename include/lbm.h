@@ -364,6 +364,23 @@ int lb_kernel_timing(lb_ctx* ctx, int enable);
 int lb_kernel_time(lb_ctx* ctx, double* total_ms, int64_t* launches);
 
 /*
+ * The kernel, tile and variant that a context of these parameters steps with
+ * (a measurement aid; on the host, no GPU needed) when npoints points are
+ * registered: velocities = 0 if they are fixed, 1 if they are fixed and a set
+ * hands out velocities, 2 if points move.  march_planes > 0: the marching
+ * kernels, with that many planes per block and march_rows rows (0: whole
+ * planes); the tile is then that of the point lists.  (FP32 runs march in
+ * groups of four steps of a call, and step the rest with the one-node kernel.)
+ * Errors: LB_ERR_ARG, and those of lb_workspace_bytes.
+ */
+typedef struct {
+    int32_t tile_x, tile_y, tile_z;
+    int32_t variant;
+    int32_t march_planes, march_rows;
+} lb_plan_info;
+int lb_plan(const lb_params* p, int64_t npoints, int32_t velocities, lb_plan_info* out);
+
+/*
  * Streaming-copy probe (a measurement aid, not an operation of the method):
  * copies `bytes` from d_src to d_dst (device pointers, both 16-byte aligned,
  * non-overlapping, bytes a positive multiple of 16), 16 bytes per thread with

@@ -585,16 +585,19 @@ bool wants_velocity(const lb_ctx* c)
 // velocities 410 -> 259, all in one box 411 -> 259; moment storage 128^3 with 100 56 -> 41; colloids: moment storage
 // 256^3 with 1000 432 -> 302, 10^4 437 -> 343, 10^4 within 32^3 nodes 503 -> 372, 16000 440 -> 363, 192^3 with 6000 197 ->
 // 170, 300 x 200 x 100 with 9 197 -> 132, 512 boxes of 24^3 with 2000 327 -> 173; left alone: 128^3 with 500 65 / 67, 40 boxes of 25^3 29 / 38).
-bool marches(const lb_ctx* c)
+bool marches(const Plan& P, int storage, long long points, bool velocities, bool moving)
 {
-    const Plan& P = c->P;
     if (P.march == 0) return false;
-    const bool mom = c->p.storage == LB_STORAGE_MOM32;
-    if (!has_kind(c, LB_COLLOIDS) && !has_kind(c, KIND_ELASTIC))
-        return !wants_velocity(c) || P.march_us + (mom ? 5.0 : 3.0) < 0.93 * P.other_us;
+    const bool mom = storage == LB_STORAGE_MOM32;
+    if (!moving) return !velocities || P.march_us + (mom ? 5.0 : 3.0) < 0.93 * P.other_us;
     if (!mom) return false;
     const double more = P.march_rows > 0 ? 25.0 : P.Gm.nx * P.Gm.ny > 256 ? 22.0 : 20.0;
-    return P.march_us + more + 0.006 * double(total_points(c)) < 0.93 * (P.other_us + 12.0);
+    return P.march_us + more + 0.006 * double(points) < 0.93 * (P.other_us + 12.0);
+}
+
+bool marches(const lb_ctx* c)
+{
+    return marches(c->P, c->p.storage, total_points(c), wants_velocity(c), has_kind(c, LB_COLLOIDS) || has_kind(c, KIND_ELASTIC));
 }
 
 // The geometry (tiles of the point lists) for the registered sets; called when they change, which also
@@ -889,6 +892,25 @@ int lb_workspace_bytes(const lb_params* p, size_t* bytes)
     const int r = make_plan(p, P, why);
     if (r) return fail(nullptr, r, why);
     *bytes = P.L.total;
+    return LB_OK;
+}
+
+int lb_plan(const lb_params* p, int64_t npoints, int32_t velocities, lb_plan_info* out)
+{
+    if (!out) return fail(nullptr, LB_ERR_ARG, "out is NULL");
+    if (npoints < 0 || velocities < 0 || velocities > 2) return fail(nullptr, LB_ERR_ARG, "npoints or velocities out of range");
+    Plan P;
+    std::string why;
+    const int r = make_plan(p, P, why);
+    if (r) return fail(nullptr, r, why);
+    const bool m = marches(P, p->storage, npoints, npoints > 0 && velocities > 0, npoints > 0 && velocities == 2);
+    const Geom& G = m ? P.Gm : P.Gp;
+    out->tile_x = G.tx;
+    out->tile_y = G.ty;
+    out->tile_z = G.tz;
+    out->variant = P.variant;
+    out->march_planes = m ? P.march : 0;
+    out->march_rows = m ? P.march_rows : 0;
     return LB_OK;
 }
 

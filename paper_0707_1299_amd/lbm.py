@@ -59,6 +59,10 @@ class lb_params(ctypes.Structure):
     ]
 
 
+class lb_plan_info(ctypes.Structure):
+    _fields_ = [(k, ctypes.c_int32) for k in ("tile_x", "tile_y", "tile_z", "variant", "march_planes", "march_rows")]
+
+
 class lb_point_model(ctypes.Structure):
     _fields_ = [
         ("inv_a", ctypes.c_double), ("inv_aL", ctypes.c_double),
@@ -128,6 +132,7 @@ def _load():
         "lb_checkpoint_load": (ctypes.c_int, [vp, vp]),
         "lb_kernel_timing": (ctypes.c_int, [vp, ctypes.c_int]),
         "lb_kernel_time": (ctypes.c_int, [vp, P(dbl), P(i64)]),
+        "lb_plan": (ctypes.c_int, [P(lb_params), i64, i32, P(lb_plan_info)]),
         "lb_copy_probe": (ctypes.c_int, [vp, vp, ctypes.c_size_t, vp]),
         "lb_expand_multipoles": (ctypes.c_int, [i64, vp, vp, vp, vp, vp, dbl, P(i64), vp, vp]),
         "lbml_work_floats": (i64, [i64]),
@@ -205,6 +210,15 @@ def lb_workspace_bytes(p: lb_params) -> int:
     if r != LB_OK:
         raise LBError(r, _L.lb_last_error(None).decode())
     return n.value
+
+
+def lb_plan(p: lb_params, npoints=0, velocities=0) -> lb_plan_info:
+    """Kernel, tile and variant of the steps (see include/lbm.h)."""
+    out = lb_plan_info()
+    r = _L.lb_plan(ctypes.byref(p), npoints, velocities, ctypes.byref(out))
+    if r != LB_OK:
+        raise LBError(r, _L.lb_last_error(None).decode())
+    return out
 
 
 def lb_expand_multipoles(types, centers, axes, e1s, strengths, sep):
