@@ -815,7 +815,7 @@ void enqueue_steps(lb_ctx* c, hipStream_t s, bool rebuild, int n)
         const long long npts = total_points(c);
         const int* toff = npts > 0 ? c->toff() : nullptr;
         float* p0 = wants_velocity(c) ? (float*)c->partial() : nullptr;
-        float* p1 = p0 + 3 * c->P.cap * c->P.G.maxp;
+        float* p1 = p0 ? p0 + 3 * c->P.cap * c->P.G.maxp : nullptr;
         float *v0 = p0 ? c->vel(0) : nullptr, *v1 = p0 ? c->vel(1) : nullptr;
         for (int pairs = n / 4 * 2; pairs > 0; --pairs) {
             box_update(c, s, true);

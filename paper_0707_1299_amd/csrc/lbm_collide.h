@@ -57,16 +57,15 @@ __device__ __forceinline__ void add_point(const Geom& G, int bx, int by, int bz,
 // What the collision needs of a box, in the arithmetic type.
 template <class T> struct Rates {
     T rho0, tau, om;      // reference density, tau, 1 / (tau + 1/2)
-    T tb, omb, kg;        // general operator: bulk mode and ghost factor
+    T tb, omb;            // general operator: bulk mode
 };
 
 template <int COLL, class T> __device__ __forceinline__ Rates<T> rates_of(const Geom& G, const BoxDev& B)
 {
-    Rates<T> r{T(G.rho0), T(B.tau), T(B.omega), T(0), T(0), T(0)};
+    Rates<T> r{T(G.rho0), T(B.tau), T(B.omega), T(0), T(0)};
     if constexpr (COLL != 0) {
         r.tb = T(B.tau_b);
         r.omb = T(B.omega_b);
-        r.kg = T(B.kappa_g);
     }
     return r;
 }
