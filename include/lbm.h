@@ -173,7 +173,15 @@ typedef struct lb_point_model {
 
 typedef struct lb_ctx lb_ctx;
 
-/* Device bytes the workspace must have for these parameters.  Pure function. */
+/*
+ * Device bytes the workspace must have for these parameters.  Pure function.
+ * With max_points > 0, lattices that the marching kernels may step (lb_plan:
+ * projected FP32 without noise, moment storage, no tile or variant named) take
+ * 36 (FP32) or 24 bytes per node (moments) more than the two population copies
+ * of 76 or 40 each, for the force density and velocities near points; FP32 takes
+ * them also where its points turn out to move and the kernels are not used.  A
+ * caller short of memory names a tile.
+ */
 int lb_workspace_bytes(const lb_params* p, size_t* bytes);
 
 /*
@@ -358,7 +366,9 @@ int64_t lb_steps_taken(const lb_ctx* ctx);
  * and every fused-kernel launch carries a pair of HIP events that the runtime
  * stamps at the kernel's own start and end on the context's stream;
  * lb_kernel_time waits for the stream and returns the summed duration (ms)
- * and the number of launches since timing was enabled.
+ * and the number of launches since timing was enabled.  In FP32 the kernel of
+ * single steps is timed, also where untimed calls of four and more steps run
+ * the marching kernel (lb_plan), two steps a launch.
  */
 int lb_kernel_timing(lb_ctx* ctx, int enable);
 int lb_kernel_time(lb_ctx* ctx, double* total_ms, int64_t* launches);
