@@ -1379,15 +1379,20 @@ int lb_checkpoint_load(lb_ctx* c, const void* src)
     if (!r) r = hip_check(c, hipMemcpy(&h, src, sizeof(h), hipMemcpyDefault), "checkpoint header");
     if (r) return r;
     if (memcmp(h.magic, CKPT_MAGIC, 8) != 0) return fail(c, LB_ERR_ARG, "not a checkpoint");
-    // The tile that checkpoints of this context name or, where the caller named none, one that the library chooses
-    // for it (such contexts have written their own tile).  Only the per-tile maxima depend on the tile, and those
-    // matter for batches of FP16 boxes alone, whose default is the plain tile.
+    // The tile that checkpoints of this context name or, where the caller named neither tile nor variant, one that the
+    // library has chosen for lattices of some size (such contexts have written their own tile, and the rules have changed).
+    // Only the per-tile maxima depend on the tile, and those matter for batches of FP16 boxes alone, whose default is the
+    // plain tile.
     const Plan& P = c->P;
-    const int tiles[3][3] = {{P.plain[0], P.plain[1], P.plain[2]}, {P.Gp.tx, P.Gp.ty, P.Gp.tz}, {P.Gm.tx, P.Gm.ty, P.Gm.tz}};
+    int mx, my;
+    march_tile(c->p.nx, c->p.ny, mx, my);
+    const int tiles[][3] = {{P.plain[0], P.plain[1], P.plain[2]}, {64, 2, 2}, {64, 4, 1}, {32, 4, 2}, {16, 4, 4}, {128, 2, 1},
+                            {128, 1, 2}, {256, 1, 1}, {mx, my, 1}};
+    const bool any = c->p.tile_x <= 0 && c->p.variant == 0 && !(c->p.storage == LB_STORAGE_FP16 && c->p.nboxes > 1);
     const int* known = nullptr;
     CkptHeader want{};
     for (auto& t : tiles)
-        if (!known && h.tx == t[0] && h.ty == t[1] && h.tz == t[2]) {
+        if (!known && (any || &t == &tiles[0]) && h.tx == t[0] && h.ty == t[1] && h.tz == t[2]) {
             known = t;
             want = ckpt_layout(c, t);
         }

@@ -125,3 +125,32 @@ def test_files_with_the_librarys_own_tile(shape, nboxes, storage, tile, known):
     named = _context(shape, storage, nboxes=nboxes, tile=(64, 2, 2) if shape[2] >= 64 else (16, 4, 4))
     with pytest.raises(lbm.LBError):            # a named tile takes its own files alone
         named.checkpoint_load(own)
+
+
+@pytest.mark.parametrize("shape,nboxes,storage,tile,kw", [
+    ((10, 10, 104), 1, "fp64", (32, 4, 2), dict(kT=1e-9, seed=3)),      # chosen before for noise and rows like these
+    ((20, 12, 101), 1, "fp64", (32, 4, 2), {}),
+    ((20, 12, 101), 1, "fp32", (64, 4, 1), {}),
+    ((20, 8, 264), 1, "fp32", (256, 1, 1), dict(max_points=500)),
+    ((9, 12, 130), 1, "mom32", (128, 1, 2), {}),
+])
+def test_files_with_a_tile_of_other_rules(shape, nboxes, storage, tile, kw):
+    """A file that carries a tile which the library chooses for other lattices, or chose by rules it no longer has."""
+    a, b = _context(shape, storage, nboxes=nboxes, **kw), _context(shape, storage, nboxes=nboxes, **kw)
+    a.step(STEPS)
+    buf, off = _save(a)
+    b.checkpoint_load(_with_own_tile(buf, off, tile))
+    a.step(STEPS)
+    b.step(STEPS)
+    assert b.steps_taken() == 2 * STEPS and torch.equal(a.moments()[1], b.moments()[1])
+
+
+def test_batches_of_fp16_boxes_keep_their_tile():
+    """Their files hold a maximum per tile."""
+    shape, nboxes = (12, 12, 40), 5
+    a = _context(shape, "fp16", nboxes=nboxes, fp16_exponent=14)
+    a.step(STEPS)
+    buf, off = _save(a)
+    with pytest.raises(lbm.LBError) as e:
+        _context(shape, "fp16", nboxes=nboxes, fp16_exponent=14).checkpoint_load(_with_own_tile(buf, off, (64, 2, 2)))
+    assert e.value.status == lbm.LB_ERR_ARG
