@@ -579,7 +579,7 @@ bool wants_velocity(const lb_ctx* c)
 // point (the other kernels: 12 us): only where that leaves a gain.  (Velocities, other kernels / marching, left alone:
 // moment storage 115 x 28 x 144 17.6 / 23.4, 23 boxes of 23^3 16.0 / 19.6, FP32 127 x 67 x 38 17.3 / 20.8; moving
 // points, moment storage, 71 boxes of 5 x 22 x 18 23.6 / 26.4.  Of 11 800 random lattices with up to one point per
-// 1050 nodes 0.2 % are slower by more than 3 % than with the other kernels, the worst 1.23.)  Up to the bound of
+// 1050 nodes 0.3 % are slower by more than 3 % than with the other kernels, the worst 1.23.)  Up to the bound of
 // choose_march the others gain with any number of points, spread out or in one place (us per step, other kernels ->
 // marching; fixed points: FP32 256^3 with 16000 425 -> 267, 128^3 with 2000 57 -> 39, 512 boxes of 32^3 with 512 and their
 // velocities 410 -> 259, all in one box 411 -> 259; moment storage 128^3 with 100 56 -> 41; colloids: moment storage
