@@ -574,12 +574,13 @@ bool wants_velocity(const lb_ctx* c)
 }
 
 // Whether the marching kernels take the steps of the registered sets: two FP32 steps per launch where no point
-// moves, moment storage with any sets.  Velocities at fixed points cost a launch more (3 us of two FP32 steps, 5 us of
-// one with moment storage), moving points, whose forces change too, two a step (20 to 25 us by the planes) and 6 ns a
-// point (the other kernels: 12 us): only where that leaves a gain.  (Velocities, other kernels / marching, left alone:
-// moment storage 115 x 28 x 144 17.6 / 23.4, 23 boxes of 23^3 16.0 / 19.6, FP32 127 x 67 x 38 17.3 / 20.8; moving
-// points, moment storage, 71 boxes of 5 x 22 x 18 23.6 / 26.4.  Of 11 800 random lattices with up to one point per
-// 1050 nodes 0.3 % are slower by more than 3 % than with the other kernels, the worst 1.23.)  Up to the bound of
+// moves, moment storage with any sets.  Velocities at fixed points cost a launch more, which lattices just large enough
+// to march do not win back: cut planes only from 23 us (moment storage) and 28 us (two FP32 steps) on with the other
+// kernels, whole planes of moment storage above 256 nodes from 27 us on (other kernels / marching, left alone: moment
+// storage 115 x 28 x 144 17.6 / 23.4, 27 boxes of 29 x 28 x 28 22.5 / 26.3, FP32 127 x 67 x 38 17.3 / 20.8; marching: moment
+// storage 93^3 39 -> 32, FP32 80 x 112 x 80 26.3 / 27.8).  Moving points, whose forces change too, cost two launches a
+// step (17 to 25 us by the planes) and 6 ns a point (the other kernels: 12 us): only where that leaves a gain (71 boxes of
+// 5 x 22 x 18 with 68 23.6 / 26.4).  Up to the bound of
 // choose_march the others gain with any number of points, spread out or in one place (us per step, other kernels ->
 // marching; fixed points: FP32 256^3 with 16000 425 -> 267, 128^3 with 2000 57 -> 39, 512 boxes of 32^3 with 512 and their
 // velocities 410 -> 259, all in one box 411 -> 259; moment storage 128^3 with 100 56 -> 41; colloids: moment storage
@@ -589,9 +590,10 @@ bool marches(const Plan& P, int storage, long long points, bool velocities, bool
 {
     if (P.march == 0) return false;
     const bool mom = storage == LB_STORAGE_MOM32;
-    if (!moving) return !velocities || P.march_us + (mom ? 5.0 : 3.0) < 0.93 * P.other_us;
+    const bool cut = P.march_rows > 0, large = P.Gm.nx * P.Gm.ny > 256;
+    if (!moving) return !velocities || P.other_us >= (cut ? (mom ? 23.0 : 28.0) : mom && large ? 27.0 : 0.0);
     if (!mom) return false;
-    const double more = P.march_rows > 0 ? 25.0 : P.Gm.nx * P.Gm.ny > 256 ? 22.0 : 20.0;
+    const double more = cut ? 25.0 : large ? 22.0 : 17.0;
     return P.march_us + more + 0.006 * double(points) < 0.93 * (P.other_us + 12.0);
 }
 
