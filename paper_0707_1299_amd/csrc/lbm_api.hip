@@ -101,46 +101,50 @@ void plain_tile(const lb_params* p, int& tx, int& ty, int& tz)
 }
 
 // Tile and variant of a caller who names neither.  Measured per step on one MI355X (us; the plain tile with variant 0 first
-// where nothing else is said).  "Dense": room for a point per 1024 nodes; "packed": per 128.
+// where nothing else is said).  "Dense": room for a point per 1024 nodes.
 //  - Tiles.  A tile row of 128 nodes where nx fills it (65 .. 128): fewer blocks share a misaligned row
 //    (101 x 75 x 62 FP32 35.4 -> 31.9).  Sparse FP32 rows of 192 and more: one row per block (256^3 with 10^4
 //    points 496 -> 429; 64 x 2 x 2 with the same variant 448), unless its last tile is mostly empty
 //    (300 nodes: 41.9 -> 44.8); many points per node want compact tiles (65536 chain markers at 256^3: 590 ->
 //    565, one row per block 940).  33 .. 63 nodes: one 64-node tile instead of two of 32 (100 boxes of
 //    48^3: 458 -> 283), but for small dense lattices whose points are read one by one and that fill most of it (58^3 FP32
-//    general packed 20.5 / 22.3, 62 x 60 x 20 FP16 11.9 / 13.0; larger: 20 boxes of 45^3 with 2603 points 92 -> 56).  17 .. 31
-//    nodes: 32-node tiles, but for small packed ones likewise (31 x 5 x 100 FP16 12.8 / 14.6; 40 boxes of 25^3 with 10416
-//    55 -> 38).  Two FP16 nodes per lane: a whole wave per row from 128 nodes on (256^3: 292 -> 240; 64 x 2 x 2 250), dense only
-//    where the rows fill it (180 x 22 x 12 with 675 points 35 / 48), and with noise or small and general not where half a
+//    general with a point per 128 nodes 20.5 / 22.3; larger: 20 boxes of 45^3 with 2603 points 92 -> 56).  17 .. 31
+//    nodes: 32-node tiles (40 boxes of 25^3 with 10416 55 -> 38; 17^3 FP64 with noise and room for 5000 points 33 -> 14, filled
+//    with them 12.8 / 14.6).  Two FP16 nodes per lane: a whole wave per row from 128 nodes on (256^3: 292 -> 240; 64 x 2 x 2 250), small
+//    dense ones only where the rows fill it (180 x 22 x 12 with 675 points 35 / 48), and with noise or small and general not where half a
 //    tile stays idle (140 x 100 x 100 with noise 45 / 57; 130 x 60 x 30 11.7 / 12.5).  Moment storage: rows of a
-//    z plane together (256^3: 524 -> 460), up to 70 MB (both copies) the tile that needs fewer blocks (64 x 50 x 100 10.1 ->
-//    9.0), up to 20 MB the plain one (193 x 29 x 43 9.1 / 10.2).  FP64 with noise: 32-node tiles (130 x 146 x 202 498 -> 412,
-//    70 x 60 x 60 56 -> 35), up to 60 MB if they are not more than plain ones (98 x 42 x 22 23 / 31).
+//    z plane together (256^3: 524 -> 460), up to 70 MB (both copies) 64 x 2 x 2 if that needs 5 % fewer blocks (64 x 50 x 100
+//    10.1 -> 9.0; 108 x 9 x 45 5.0 -> 4.0; 81^3 23.3 / 20.7).  FP64 with noise: 32-node tiles (130 x 146 x 202 498 -> 412,
+//    70 x 60 x 60 56 -> 35), but where the last one holds 1 to 6 nodes 64-node ones up to 63 nodes (36^3 30.5 -> 16.6) and
+//    beyond if they are fewer (98 x 14 x 36 18 / 31, 100 x 33 x 48 27 / 29; 66^3 66 -> 40).
 //  - Block order.  Tile rows on one XCD (bit 64) except for lattices near the L2s' 32 MB.  Both copies up to 70 MB, in FP16
 //    without noise 50 MB, narrow rows off the lines 48 MB: the orders cross between 60 and 75 MB in FP32 and FP64
 //    with every operator (contiguous runs / tile rows: FP32 70^3, 52 MB, 13.6 / 14.0; 75^3, 64 MB, 16.6 / 16.4; 79^3, 75
 //    MB, 20.6 / 18.0; 60 x 60 x 128, 70 MB, 13.9 / 14.1; 64 x 80 x 100, 78 MB, 15.3 / 14.5; with noise 79^3 26.8 / 23.3; FP64
 //    57^3, 56 MB, 12.6 / 13.4; 63^3, 76 MB, 15.5 / 15.4; 79^3, 150 MB, 36.2 / 32.1) and at 45 in FP16 (85^3, 47 MB, 18.1 / 17.9;
 //    90^3, 55 MB, 24.9 / 22.4; with noise 90^3 27.6 / 27.6, 95^3, 65 MB, 30.1 / 30.6).
-//    Where the tiles of a row are no power of two, bit 64 means launch order.  64-node tiles then pay from 110 MB on (FP64 130
-//    x 60 x 30, 71 MB, 18.0 / 19.0; 180 x 60 x 30, 98 MB, 22.1 / 22.4; 130 x 60 x 60, 142 MB, 35.7 / 33.1) and, with rows off
-//    the lines, up to 520 MB in FP32 and 980 MB in FP64 (300 x 100 x 100 FP32, 456 MB, 100.0 / 98.8; 153^3, 544 MB, 137 /
-//    148; 180^3 223 / 269; FP64 130^3, 668 MB, 161 / 149; 153^3, 1.1 GB, 272 / 300).
-//    Packed with points that are read one by one: contiguous runs (30 boxes of 34^3 FP32 general with 19652 points 76 / 88).
+//    Where the tiles of a row are no power of two, bit 64 means launch order.  In the projected FP64 step that pays from 110 MB
+//    on (130 x 60 x 30, 71 MB, 18.0 / 19.0; 180 x 60 x 30, 98 MB, 22.1 / 22.4; 130 x 60 x 60, 142 MB, 35.7 / 33.1), otherwise as
+//    above (FP32 137 x 41 x 122, 104 MB, 38.6 / 31.5, general 177 x 17 x 208, 95 MB, 27.6 / 25.5, FP16 149 x 64 x 143 46 /
+//    42).  Contiguous runs come back with 64-node tiles of rows off the 32-byte sectors and large planes (FP32
+//    151^3, 523 MB, 153 / 136, 158^3 173 / 194; 132 x 162 x 198, 644 MB, 209 / 196; 300 x 100 x 100, 456 MB, 100.0 / 98.8; FP64
+//    130^3, 668 MB, 161 / 149; 154^3 262 / 282; on the sectors FP32 152^3 153 / 141, FP64 152^3 218 / 193).
 //    Points crowded in one place would like them too (FP64 general, 2926 in one of 512 boxes of 16 x 44 x 5, 787 / 964), as
 //    many spread out do not (130^3 with 3138 165 / 146).
 //  - Loads.  Cached (bit 2) where neighbouring rows are read again after more than the L2 has passed (planes
 //    over 2.6 MB: 256^3 455 -> 448; 128^3 67.5 -> 66.6 the other way) or where rows do not
 //    start on a cache line, so that two rows share one (300 x 60 x 40: 47.6 -> 41.1; boxes of 16^3: 75 -> 65; 90^3 FP32
 //    27.1 -> 24.5), unless the L2s hold them all the same: in FP64 up to 100 MB (2 boxes of 60 x 50 x 52, 95 MB, 20.6 ->
-//    19.7 the other way; 70^3, 104 MB, 24.7 -> 24.2; 77^3 31.6 -> 30.2); and in
+//    19.7 the other way; 70^3, 104 MB, 24.7 -> 24.2; 77^3 31.6 -> 30.2), rows of up to 64 nodes 140 MB (45 x 43 x 207, 122 MB, 50.6 ->
+//    52.3); and in
 //    the smallest lattices (20^3 FP32 10.0 -> 9.8; off the lines in FP16 up to 32 MB or 63 nodes: 100 boxes of 16^3 13.4 -> 11.0,
 //    70^3 general 14.8 -> 13.1; 80^3, 39 MB, 17.0 -> 18.4).
 //  - The kernel for one tile per block (bit 128) where its missing tile loop saves registers: FP16, moment
 //    storage, the general and thermal operators, many points, small lattices; the FP32 and FP64 projected
 //    step is memory bound and faster with the loop (256^3 FP32: 429 against 447), FP64 with noise on other tiles than 32-node
-//    ones too (300 boxes of 14^3 114 / 156).  FP16 with one node per lane, sparse and with narrow rows likewise, and with cached
-//    loads (18 boxes of 31^3: 25.2 -> 23.4, 40 of 25^3 32.1 -> 27.5).
+//    ones too when they are more than the 256 compute units (300 boxes of 14^3 114 / 156; one of 15^3 9.9 -> 8.6;
+//    tiles an eighth full up to 320, 73 boxes of 5^3 30 -> 17, 83 42 / 43).
+//    FP16 with one node per lane, sparse and with narrow rows likewise, and with cached loads (18 boxes of 31^3: 25.2 -> 23.4, 40 of 25^3 32.1 -> 27.5).
 // Batches of FP16 boxes keep the plain tile: their checkpoints hold a maximum per tile.
 void choose_default(const lb_params* p, int& tx, int& ty, int& tz, int& variant)
 {
@@ -150,26 +154,26 @@ void choose_default(const lb_params* p, int& tx, int& ty, int& tz, int& variant)
     const bool fp64 = p->storage == LB_STORAGE_FP64, fp16 = p->storage == LB_STORAGE_FP16, mom = p->storage == LB_STORAGE_MOM32;
     const bool noise = p->kT > 0.0, general = noise || p->collision != LB_COLLISION_PROJECTED;
     const bool pairs = fp16 && p->nx % 2 == 0;
-    const bool dense = double(p->max_points) * 1024.0 > nodes, packed = double(p->max_points) * 128.0 > nodes;
-    const bool single = fp16 || general;     // a crowded tile's points are read one by one (not staged)
+    const bool dense = double(p->max_points) * 1024.0 > nodes;
     const auto tiles = [&](int a, int b, int c) {
         return double((p->nx + a - 1) / a) * ((p->ny + b - 1) / b) * ((p->nz + c - 1) / c);
     };
     plain_tile(p, tx, ty, tz);
     if (fp16 && p->nboxes > 1) {
     } else if (p->nx > 16 && p->nx < 32) {
-        if (!(packed && single && copies <= 20.0e6)) { tx = 32; ty = 4; tz = 2; }
-    } else if (fp64 && noise && p->nx > 32 && !(copies <= 60.0e6 && tiles(32, 4, 2) > tiles(64, 2, 2))) {
         tx = 32; ty = 4; tz = 2;
-    } else if (mom && p->nx >= 64 && copies <= 20.0e6) {
+    } else if (fp64 && noise && p->nx > 32) {
+        const int last = p->nx % 32;
+        if (last > 0 && last < 7 && (p->nx < 64 || tiles(64, 2, 2) < tiles(32, 4, 2))) { tx = 64; ty = 2; tz = 2; }
+        else { tx = 32; ty = 4; tz = 2; }
     } else if (mom) {
-        if (p->nx >= 64 && !(copies <= 70.0e6 && tiles(64, 2, 2) < tiles(64, 4, 1))) { tx = 64; ty = 4; tz = 1; }
+        if (p->nx >= 64 && !(copies <= 70.0e6 && tiles(64, 2, 2) < 0.95 * tiles(64, 4, 1))) { tx = 64; ty = 4; tz = 1; }
         else if (p->nx > 32) { tx = 64; ty = 2; tz = 2; }
     } else if (pairs) {
         if (p->nx >= 128) {
             const bool idle = (p->nx + 63) / 64 % 2 != 0;     // half a tile of each row
-            if (!(dense && p->nx % 128 != 0) && !(idle && (noise || (general && copies <= 32.0e6)))) { tx = 128; ty = 2; tz = 1; }
-        } else if (p->nx > 32 && p->nx < 64 && !(dense && p->nx >= 48)) {
+            if (!(dense && p->nx % 128 != 0 && copies <= 25.0e6) && !(idle && (noise || (general && copies <= 32.0e6)))) { tx = 128; ty = 2; tz = 1; }
+        } else if (p->nx > 32 && p->nx < 64 && !(dense && general && p->nx >= 48)) {
             tx = 64; ty = 2; tz = 2;
         }
     } else if (p->nx > 64 && p->nx <= 128 && !dense && !noise) {
@@ -183,21 +187,23 @@ void choose_default(const lb_params* p, int& tx, int& ty, int& tz, int& variant)
     const int ntx = (p->nx + tx - 1) / tx;
     const bool rows = (ntx & (ntx - 1)) == 0;
     const bool aligned = (long long)(p->nx * esz) % 128 == 0, narrow = !aligned && p->nx < 32 && !mom;
-    const bool shared = !aligned && (esz < 8.0 || narrow || copies > 100.0e6);   // two rows share a line that is read again
-    if (copies <= (narrow ? 48.0e6 : !rows ? 110.0e6 : fp16 && !noise ? 50.0e6 : 70.0e6)) {
+    // two rows share a line that is read again
+    const bool shared = !aligned && (esz < 8.0 || narrow || copies > (p->nx > 64 ? 100.0e6 : 140.0e6));
+    if (copies <= (narrow ? 48.0e6 : fp64 && !general && !rows ? 110.0e6 : fp16 && !noise ? 50.0e6 : 70.0e6)) {
         variant = fp16 && !pairs && !general && p->nx < 64 && !dense ? 2 : 128;
         if (copies <= 9.0e6 || (fp16 && !aligned && (copies <= 32.0e6 || p->nx < 64))) variant |= 2;
-    } else if (packed && single) {
-        variant = shared ? 130 : 128;
     } else {
         const double plane = double(p->nx) * p->ny * planes * esz;
-        variant = rows || tx > 64 || aligned || fp16 || mom || copies <= (fp64 ? 980.0e6 : 520.0e6) ? 64 : 0;
+        const bool runs = !rows && tx == 64 && (long long)(p->nx * esz) % 32 != 0 && !fp16 && !mom && copies > (fp64 ? 1040.0e6 : 590.0e6) &&
+                          plane > (fp64 ? 2.9e6 : 1.85e6);
+        variant = runs ? 0 : 64;
         if (shared || (plane > 2.6e6 && !dense)) variant |= 2;
         if (fp16 || mom || general || dense) variant |= 128;
     }
-    if (fp64 && noise) {
-        if (tx != 32) variant &= 2;
-        else if (!rows) variant = 128;
+    if (fp64 && noise && !(tx == 32 && rows && copies > 70.0e6)) {
+        const double blocks = tiles(tx, ty, tz) * p->nboxes;
+        variant = tx == 32 || blocks <= (nodes < 0.15 * BLOCK * blocks ? 320.0 : 256.0) ? 128 : 0;
+        if (copies <= 9.0e6) variant |= 2;
     }
 }
 
