@@ -585,8 +585,10 @@ bool wants_velocity(const lb_ctx* c)
 // kernels, whole planes of moment storage above 256 nodes from 27 us on (other kernels / marching, left alone: moment
 // storage 115 x 28 x 144 17.6 / 23.4, 27 boxes of 29 x 28 x 28 22.5 / 26.3, FP32 127 x 67 x 38 17.3 / 20.8; marching: moment
 // storage 93^3 39 -> 32, FP32 80 x 112 x 80 26.3 / 27.8).  Moving points, whose forces change too, cost two launches a
-// step (17 to 25 us by the planes) and 6 ns a point (the other kernels: 12 us): only where that leaves a gain (71 boxes of
-// 5 x 22 x 18 with 68 23.6 / 26.4).  Up to the bound of
+// step (15 to 25 us by the planes) and 6 ns a point (the other kernels: 12 us): only where that leaves a gain (71 boxes of
+// 5 x 22 x 18 with 68 23.6 / 26.4).  Below 256 nodes a plane 2 us less from 60 MB (both copies) on, where the other kernels
+// no longer find them in the caches (380 boxes of 16 x 7 x 44 106 -> 71, 557 of 12^3 58 -> 52; 413 of 12^3 44 / 46, 319 35 /
+// 40).  Up to the bound of
 // choose_march the others gain with any number of points, spread out or in one place (us per step, other kernels ->
 // marching; fixed points: FP32 256^3 with 16000 425 -> 267, 128^3 with 2000 57 -> 39, 512 boxes of 32^3 with 512 and their
 // velocities 410 -> 259, all in one box 411 -> 259; moment storage 128^3 with 100 56 -> 41; colloids: moment storage
@@ -599,7 +601,7 @@ bool marches(const Plan& P, int storage, long long points, bool velocities, bool
     const bool cut = P.march_rows > 0, large = P.Gm.nx * P.Gm.ny > 256;
     if (!moving) return !velocities || P.other_us >= (cut ? (mom ? 23.0 : 28.0) : mom && large ? 27.0 : 0.0);
     if (!mom) return false;
-    const double more = cut ? 25.0 : large ? 22.0 : 17.0;
+    const double more = cut ? 25.0 : large ? 22.0 : double(P.Gm.N) * P.Gm.nboxes > 0.75e6 ? 15.0 : 17.0;
     return P.march_us + more + 0.006 * double(points) < 0.93 * (P.other_us + 12.0);
 }
 
